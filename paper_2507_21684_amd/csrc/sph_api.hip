@@ -1345,8 +1345,10 @@ sph_status export_lists(sph_plan* P, const int32_t* xstat, int64_t* offsets, int
         if (stat[s2] & kFlagOverflow) return fail(SPH_ERR_CAPACITY, "a particle has more neighbours than max_neighbors");
     if (tot > capacity) return fail(SPH_ERR_CAPACITY, "neighbour capacity too small");
     if (N > 0) {
-        k_export_rows<<<(unsigned)N, 64, 0, st>>>(N, P->width, orig, wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt),
-                                                  offsets, nbr);
+        const int cap = std::min<int>(P->width, kExportCap);
+        k_export_rows<<<grid_for(N, kExportRows), 64 * kExportRows,
+                        kExportRows * sizeof(int32_t) * export_lds_ints(cap), st>>>(
+            N, P->width, orig, wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), offsets, nbr, cap);
         LAUNCH_CHECK("export_rows");
     }
     HIP_TRY(hipStreamSynchronize(st));

@@ -2337,35 +2337,156 @@ __global__ __launch_bounds__(256) void k_export_counts(int64_t N, const int32_t*
     rowcnt[orig[q]] = c < width ? c : width;
 }
 
-// one wavefront per row: entries mapped to original indices and written in ascending order
-// (each entry's rank in its row by comparison with every other entry of the row)
-__global__ __launch_bounds__(64) void k_export_rows(int64_t N, int32_t width, const int32_t* __restrict__ orig,
+// One wavefront per row: entries mapped to original indices and written in ascending order.
+// Up to 64 entries (2D supports) a lane holds one entry and counts the smaller ones, taken from the
+// other lanes' registers.  Longer rows (3D) go through a bucket sort in LDS: the bucket is a
+// monotone function of the index between the row's smallest and largest, so a row is sorted once
+// every bucket is, and an entry's place inside its bucket is a count over the bucket's few members
+// (read as aligned quads; cap is a multiple of 4).
+// The comparisons per entry fall from the row's length to the bucket's; rows past `cap` entries
+// (dense clusters) are ranked against the full row, 64 entries at a time.
+// Bound: instruction issue and LDS latency.  3D, 64 000 rows of 257 entries: 107 us against
+// 2108 us with every row ranked against itself.
+constexpr int kExportCap = 1024;      // longest row sorted in LDS
+constexpr int kExportBuckets = 512;
+// LDS ints of a row, for rows of at most `cap` entries (a multiple of 4)
+constexpr int export_lds_ints(int cap) { return 2 * cap + 8 + kExportBuckets + 4; }
+
+// Orders a wavefront's LDS accesses (the LDS serves one wavefront's accesses in order, so only the
+// compiler has to keep them so).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kExportRows = 4;        // wavefronts, each with a row of its own, per workgroup
+
+__global__ __launch_bounds__(64 * kExportRows) void k_export_rows(int64_t N, int32_t width, const int32_t* __restrict__ orig,
                                                     const int32_t* __restrict__ nbr,
                                                     const int32_t* __restrict__ nbr_count,
-                                                    const int64_t* __restrict__ offsets, int32_t* __restrict__ out)
+                                                    const int64_t* __restrict__ offsets, int32_t* __restrict__ out,
+                                                    int cap)
 {
-    __shared__ int32_t row[1024];
-    const int64_t q = (int64_t)xcd_remap(blockIdx.x, gridDim.x);
+    extern __shared__ __align__(16) int32_t export_lds[];
+    // cap + 8: the entries by bucket, read as quads
+    int32_t* tmp = export_lds + (threadIdx.x >> 6) * export_lds_ints(cap);
+    int32_t* row = tmp + cap + 8;
+    int32_t* start = row + cap;
+    const int64_t q = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kExportRows + (threadIdx.x >> 6);
     if (q >= N) return;
+    const int lane = threadIdx.x & 63;
     int c = nbr_count[q];
-    c = c < width ? c : width;
+    c = __builtin_amdgcn_readfirstlane(c < width ? c : width);
     const int32_t* src = nbr + q * (int64_t)width;
     const int64_t base = offsets[orig[q]];
-    for (int m0 = 0; m0 < c; m0 += 1024) {
-        // rows longer than 1024 are handled by ranking each chunk against the full row
-        const int mc = (c - m0 < 1024) ? c - m0 : 1024;
-        for (int m = threadIdx.x; m < mc; m += 64) row[m] = orig[src[m0 + m]];
-        __syncthreads();
-        for (int m = threadIdx.x; m < mc; m += 64) {
-            const int v = row[m];
-            int rank = 0;
-            for (int r2 = 0; r2 < c; ++r2) {
-                const int w = (r2 >= m0 && r2 < m0 + mc) ? row[r2 - m0] : orig[src[r2]];
-                rank += (w < v) ? 1 : 0;
+    if (c <= 64) {
+        const int v = lane < c ? orig[src[lane]] : 0;
+        int rank = 0;
+        for (int k = 0; k < c; ++k) rank += (__builtin_amdgcn_readlane(v, k) < v) ? 1 : 0;
+        if (lane < c) out[base + rank] = v;
+        return;
+    }
+    if (c <= cap) {
+        int lo = INT32_MAX, hi = INT32_MIN;
+        for (int m0 = lane; m0 < c; m0 += 256) {   // four entries of a lane in flight; past the row, its last
+            int v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = src[m0 + 64 * j < c ? m0 + 64 * j : c - 1];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = orig[v[j]];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (m0 + 64 * j < c) row[m0 + 64 * j] = v[j];
+                lo = v[j] < lo ? v[j] : lo;
+                hi = v[j] > hi ? v[j] : hi;
             }
-            out[base + rank] = v;
         }
-        __syncthreads();
+        for (int b = lane; b < kExportBuckets; b += 64) start[b] = 0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const int l2 = __shfl_xor(lo, o, 64), h2 = __shfl_xor(hi, o, 64);
+            lo = l2 < lo ? l2 : lo;
+            hi = h2 > hi ? h2 : hi;
+        }
+        // non-decreasing in v, and at most kExportBuckets - 1 (entries are distinct, so hi > lo)
+        const float scale = float(kExportBuckets - 1) / float(hi - lo);
+        auto bucket = [&](int v) { return (int)(float(v - lo) * scale); };
+        wave_sync();
+        // a lane takes `per` consecutive entries, so that the lanes of one atomic reach across the row:
+        // neighbouring entries (one cell's particles) mostly share a bucket, and atomics on one
+        // address are served one after the other.  per is odd, against bank conflicts.
+        const int per = ((c + 63) >> 6) | 1;
+        const int first = lane * per, last = first + per < c ? first + per : c;
+        for (int m = first; m < last; ++m) atomicAdd(&start[bucket(row[m])], 1);
+        wave_sync();
+        {
+            // bucket counts to bucket ends, in place: eight consecutive buckets a lane
+            constexpr int kPer = kExportBuckets / 64;
+            int n[kPer], sum = 0;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                n[k] = start[kPer * lane + k];
+                sum += n[k];
+            }
+            int end = wave_incl_scan(sum) - sum;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                end += n[k];
+                start[kPer * lane + k] = end;
+            }
+            if (lane == 0) start[kExportBuckets] = c;
+            if (lane < 8) tmp[c + lane] = INT32_MAX;
+        }
+        wave_sync();
+        // filled from the back, so an end becomes its bucket's start
+        for (int m = first; m < last; ++m) {
+            const int v = row[m];
+            tmp[atomicSub(&start[bucket(v)], 1) - 1] = v;
+        }
+        wave_sync();
+        const int pad = (c + 3) & ~3;   // a quad of INT32_MAX
+        for (int m0 = lane; m0 < c; m0 += 256) {
+            // aligned quads over the bucket: an entry of an earlier bucket is smaller and counts, one of
+            // a later bucket (or the padding) is larger and does not
+            int v[4], k[4], e[4], rank[4], more = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = tmp[m0 + 64 * j < c ? m0 + 64 * j : c - 1];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int b = bucket(v[j]);
+                k[j] = rank[j] = start[b] & ~3;
+                e[j] = start[b + 1];
+                more |= k[j] < e[j];
+            }
+            while (more) {
+                more = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int4 w = *reinterpret_cast<const int4*>(&tmp[k[j] < e[j] ? k[j] : pad]);
+                    rank[j] += (w.x < v[j]) + (w.y < v[j]) + (w.z < v[j]) + (w.w < v[j]);
+                    k[j] += 4;
+                    more |= k[j] < e[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (m0 + 64 * j < c) row[rank[j]] = v[j];
+        }
+        wave_sync();
+        for (int m = lane; m < c; m += 64) out[base + m] = row[m];
+        return;
+    }
+    for (int m0 = 0; m0 < c; m0 += 64) {
+        const int v = m0 + lane < c ? orig[src[m0 + lane]] : 0;
+        int rank = 0;
+        for (int k0 = 0; k0 < c; k0 += 64) {
+            const int w = k0 + lane < c ? orig[src[k0 + lane]] : 0;
+            const int kn = c - k0 < 64 ? c - k0 : 64;
+            for (int k = 0; k < kn; ++k) rank += (__builtin_amdgcn_readlane(w, k) < v) ? 1 : 0;
+        }
+        if (m0 + lane < c) out[base + rank] = v;
     }
 }
 
