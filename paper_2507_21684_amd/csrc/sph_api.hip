@@ -48,6 +48,14 @@ sph_status fail(sph_status code, const std::string& msg)
 constexpr double kCellMargin = 1.0 + 1.0 / 1024.0;  // cell side exceeds H/sub by more than rounding
 constexpr int64_t kGroupedBuildCells = 65536;         // 2D plans with this many cell slots build by 2 x 2 groups
 
+// 3D builds with fewer wavefronts than kBuildWaves (eight on every SIMD) let up to four share a cell's
+// particles: a 3D cell holds about ten and streams about 1000 candidates, one serial chain.  FP64 3D
+// 20^3 (1000 cells) 85 us with one wavefront a cell, 38 with eight, 32 with four; FP32 3D 32^3 (4096)
+// 48 and 43 with one and two.  A 2D cell has about five particles and 100 candidates, where the second
+// wavefront repeats the whole setup: 2D 101^2 7.4 us with one, 8.5 with two.
+constexpr int64_t kBuildWaves = 8192;
+constexpr int kMaxBuildSplit = 4;
+
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 uint64_t morton(int bx, int by, int bz, int dim)
@@ -428,38 +436,40 @@ sph_status build_lists(sph_plan* P, int slot, hipStream_t st, bool exact = false
     // group of 2 x 2 cells, which shares the per-wavefront setup of cells with few particles
     const bool group = D == 2 && P->ncell >= kGroupedBuildCells;
     const unsigned groups = (unsigned)(group ? P->ncell / 4 : P->ncell);
+    int split = 1;
+    while (D == 3 && split < kMaxBuildSplit && (int64_t)groups * split < kBuildWaves) split *= 2;
     // lists with speed-scaled skins use the half skins of the sort that preceded this build
     if (group) {
         if (P->filter && P->speed_skins && !exact)
-            launch_k(&prof, k_build_list<T, D, true, true>, dim3(groups), dim3(64), st,
+            launch_k(&prof, k_build_list<T, D, true, true>, dim3(groups * (unsigned)split), dim3(64), st,
                 wsp<int32_t>(P, P->o_cell_sim), wsp<int32_t>(P, P->o_blk_coord), wsp<int32_t>(P, P->o_blk_rank),
                 wsp<SimConst<T>>(P, P->o_simc),
                 wsp<int32_t>(P, P->o_cell_start), wsp<vec4_t<T>>(P, L.jd0), P->width,
                 wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), status, (unsigned long long*)nullptr, 0,
-                (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_uref));
+                (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_uref), split);
         else
-            launch_k(&prof, k_build_list<T, D, false, true>, dim3(groups), dim3(64), st,
+            launch_k(&prof, k_build_list<T, D, false, true>, dim3(groups * (unsigned)split), dim3(64), st,
                 wsp<int32_t>(P, P->o_cell_sim), wsp<int32_t>(P, P->o_blk_coord), wsp<int32_t>(P, P->o_blk_rank),
                 wsp<SimConst<T>>(P, P->o_simc),
                 wsp<int32_t>(P, P->o_cell_start), wsp<vec4_t<T>>(P, L.jd0), P->width,
                 wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), status,
                 P->filter ? nullptr : wsp<unsigned long long>(P, P->o_pairs), exact ? 1 : 0,
-                (const vec4_t<T>*)nullptr);
+                (const vec4_t<T>*)nullptr, split);
     } else if (P->filter && P->speed_skins && !exact)
-        launch_k(&prof, k_build_list<T, D, true, false>, dim3(groups), dim3(64), st,
+        launch_k(&prof, k_build_list<T, D, true, false>, dim3(groups * (unsigned)split), dim3(64), st,
             wsp<int32_t>(P, P->o_cell_sim), wsp<int32_t>(P, P->o_blk_coord), wsp<int32_t>(P, P->o_blk_rank),
             wsp<SimConst<T>>(P, P->o_simc),
             wsp<int32_t>(P, P->o_cell_start), wsp<vec4_t<T>>(P, L.jd0), P->width,
             wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), status, (unsigned long long*)nullptr, 0,
-            (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_uref));
+            (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_uref), split);
     else
-        launch_k(&prof, k_build_list<T, D, false, false>, dim3(groups), dim3(64), st,
+        launch_k(&prof, k_build_list<T, D, false, false>, dim3(groups * (unsigned)split), dim3(64), st,
             wsp<int32_t>(P, P->o_cell_sim), wsp<int32_t>(P, P->o_blk_coord), wsp<int32_t>(P, P->o_blk_rank),
             wsp<SimConst<T>>(P, P->o_simc),
             wsp<int32_t>(P, P->o_cell_start), wsp<vec4_t<T>>(P, L.jd0), P->width,
             wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), status,
             P->filter ? nullptr : wsp<unsigned long long>(P, P->o_pairs), exact ? 1 : 0,
-            (const vec4_t<T>*)nullptr);
+            (const vec4_t<T>*)nullptr, split);
     LAUNCH_CHECK("build_list");
     return SPH_OK;
 }

@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sph {
 
 constexpr int kFlagNonfinite = 1;
@@ -258,13 +260,25 @@ __device__ __forceinline__ T tait_slope(const SimConst<T>& S, T rho)
     return S.c0sq * (s3 * s3);
 }
 
-template <typename I>
-__device__ __forceinline__ I wave_incl_scan(I v)
+// Inclusive scan of 32-bit sums over the wavefront by DPP (row shifts, then the row totals
+// broadcast to the rows above): six dependent adds instead of six LDS round trips.
+__device__ __forceinline__ int32_t wave_incl_scan(int32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+__device__ __forceinline__ int64_t wave_incl_scan(int64_t v)
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        I t = __shfl_up(v, o, 64);
+        int64_t t = __shfl_up(v, o, 64);
         if (lane >= o) v += t;
     }
     return v;
@@ -320,7 +334,7 @@ template <typename I>
 __device__ __forceinline__ I block_excl_scan(I v, I* smem /* >= 5 */, I* total)
 {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    I inc = wave_incl_scan(v);
+    const I inc = wave_incl_scan(v);
     if (lane == 63) smem[wid] = inc;
     __syncthreads();
     I off = 0, tot = 0;
@@ -585,18 +599,23 @@ __global__ __launch_bounds__(256) void k_poll_stage(int32_t nsims, int32_t* __re
 // later ones, in dense clusters only, search the prefix sums.
 constexpr int kCandTable = 2048;
 
-// One wavefront per cell.  The candidates of the cell's particles are the particles of the
-// (2 sub + 1)^dim stencil cells, taken in lexicographic order of the cell offset (the
-// precomputed stencil table lists them in that order), each cell's particles in sorted order
-// (= original index inside a cell), which is the canonical list order.  The candidate stream
-// is cut into chunks of 64; lane l holds candidate 64 c + l of chunk c in registers (the next
-// chunk's gather is issued before the current chunk is tested; a candidate's stencil cell comes
-// from a byte table in LDS, or a search of the prefix sums past it), and the cell's particles,
-// staged in LDS, are taken one after the other with the same address in every lane.  For
-// particle p one round tests all 64 candidates of the chunk; the ballot of the accepted ones
-// gives each its rank, so the round appends a contiguous run to p's row, in candidate order.
-// Lane p keeps p's running count.  Lists are row-major: entry k of particle i is
-// nbr[i * width + k].
+// One wavefront per cell, or `split` wavefronts that share a cell's particles.  The candidates of the
+// cell's particles are the particles of the (2 sub + 1)^dim stencil cells, taken in lexicographic
+// order of the cell offset, each cell's particles in sorted order (= original index inside a cell),
+// which is the canonical list order.  The candidate stream is cut into tiles of kBuildChunks x 64;
+// lane l holds candidates 64 k + l of the tile (k = 0 .. kBuildChunks - 1) in registers (a candidate's
+// stencil cell comes from a byte table in LDS, or a search of the prefix sums past it), and the
+// wavefront's particles, staged in LDS, are taken one after the other with the same address in
+// every lane.  For a particle the tile's chunks are independent tests of 64 candidates each; the
+// ballot of the accepted ones gives each its rank, so a chunk appends a contiguous run to the
+// particle's row, in candidate order.  Lane p keeps p's running count.  Lists are row-major: entry k
+// of particle i is nbr[i * width + k].
+// Bound: instruction issue (the tests; the matrix cores cannot evaluate the predicate's rounding),
+// and in plans of few cells the wavefront's serial chain.  Taking a tile of chunks per particle
+// instead of one reads the particle's position and count once per tile and leaves the chunks' tests
+// independent of each other: 18 vector and about as many scalar instructions per test of 64
+// candidates became 13 and 6.  Measured, one chunk at a time against tiles: 3D 64^3 with skins 267
+// and 195 us, 3D 40^3 exact 110 and 75 us, the 512-simulation 2D batch 285 and 229 us.
 // With GROUP (2D) a wavefront serves a group of 2 x 2 cells (cell slots c, c + 1, c + B,
 // c + B + 1 of a block, B = 4) over their 6 x 6 (or 4 x 4) union stencil, in the same lexicographic order:
 // a particle's own stencil cells are a sub-grid of it in the same relative order, and the extra
@@ -604,6 +623,8 @@ constexpr int kCandTable = 2048;
 // from it, so the strict distance test rejects them (also where a small box repeats a cell in
 // the union under another periodic image).  Each particle's list is therefore the one of its own
 // cell, while the stencil setup and the candidate stream are shared by four cells.
+constexpr int kBuildChunks = 4;
+
 template <typename T, int DIM, bool PERPAIR, bool GROUP>
 __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ cell_sim,
                                                    const int32_t* __restrict__ blk_coord,
@@ -614,20 +635,22 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
                                                    int32_t* __restrict__ nbr, int32_t* __restrict__ nbr_count,
                                                    int32_t* __restrict__ status,
                                                    unsigned long long* __restrict__ pair_counter, int exact,
-                                                   const vec4_t<T>* __restrict__ href)
+                                                   const vec4_t<T>* __restrict__ href, int split)
 {
     // PERPAIR: lists with per-particle half skins; positions and half skins come from href
     // (written by the sort), and the list radius of a pair is H + h_i + h_j
     const vec4_t<T>* __restrict__ rec = PERPAIR ? href : jd0;
-    __shared__ vec4_t<T> pu[64];
+    __shared__ vec4_t<T> pu[65];
     __shared__ int32_t uc_first[128];
     __shared__ int32_t uc_pref[129];
     __shared__ int32_t uc_code[128];
     __shared__ uint8_t uc_of[kCandTable];  // stencil cell of each of the first kCandTable candidates
 
+    constexpr int NC = kBuildChunks;
     constexpr bool kGroup = GROUP && DIM == 2;
     constexpr int kExt = kGroup ? 1 : 0;
-    const int gw = xcd_remap(blockIdx.x, gridDim.x);
+    const unsigned wg = (unsigned)xcd_remap(blockIdx.x, gridDim.x);
+    const int gw = (int)(wg / (unsigned)split), part = (int)(wg % (unsigned)split);
     // lowest cell slot of the wavefront's cells (2D: group gw & 3 of block gw >> 2)
     const int gc = kGroup ? (gw >> 2) * 16 + ((gw >> 1) & 1) * 8 + (gw & 1) * 2 : gw;
     const int lane = threadIdx.x;
@@ -636,14 +659,19 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
     const int i0 = cell_start[gc];
     const int n0 = cell_start[gc + (kGroup ? 2 : 1)] - i0;
     const int i1 = kGroup ? cell_start[gc + 4] : 0;
-    const int n = n0 + (kGroup ? cell_start[gc + 6] - i1 : 0);
-    if (n == 0) return;
-    const SimConst<T> S = sims[s];
-    const int sw1 = 2 * S.sub + 1 + kExt;
+    const int nall = n0 + (kGroup ? cell_start[gc + 6] - i1 : 0);
+    // this wavefront's share of them, [qa, qb)
+    const int qa = (int)((int64_t)nall * part / split), qb = (int)((int64_t)nall * (part + 1) / split);
+    if (qa == qb) return;
+    const SimConst<T>& S = sims[s];
+    const T SL = S.L, SH = S.H;
+    const int sub = S.sub, nc = S.nc;
+    const int sw1 = 2 * sub + 1 + kExt;
     const int ncu = kGroup ? sw1 * sw1 : S.ncu;
     const T R2 = exact ? S.H2 : S.HL2;  // list radius: the support, or the support plus the skin
     // the cell's coordinates from its block and its place inside the block
     int cc[3];
+    bool inside = true;   // no stencil cell is a periodic image: every shift is zero
     {
         constexpr unsigned B = kBlockSide<DIM>, Bd = DIM == 3 ? B * B * B : B * B;
         const unsigned local = (unsigned)(gc - S.cell0);
@@ -653,6 +681,8 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
         cc[0] = (coord & 1023) * (int)B + (int)(w % B);
         cc[1] = ((coord >> 10) & 1023) * (int)B + (int)((w / B) % B);
         cc[2] = (DIM == 3) ? ((coord >> 20) & 1023) * (int)B + (int)(w / (B * B)) : 0;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) inside = inside && cc[k] >= sub && cc[k] + sub + kExt < nc;
     }
 
     // stencil cells: particle range and periodic image code, two per lane at most
@@ -676,9 +706,9 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
         }
         const int end = (beg + count < kCandTable) ? beg + count : kCandTable;
         for (int m = beg; m < end; ++m) uc_of[m] = uint8_t(u);
-        carry += __shfl(inc, 63, 64);
+        carry += __builtin_amdgcn_readlane(inc, 63);
     }
-    const int M = carry;
+    const int M = __builtin_amdgcn_readfirstlane(carry);
     if (lane == 0) uc_pref[ncu] = M;
     __syncthreads();
 
@@ -701,75 +731,126 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
         u = rec[j];
     };
 
-    // sorted index of the wavefront's particle q (the two ranges in order)
+    // sorted index of the unit's particle q (the two ranges in order)
     auto pidx = [&](int q) { return q < n0 ? i0 + q : i1 + (q - n0); };
     int pairs_acc = 0;
-    for (int pb = 0; pb < n; pb += 64) {
-        const int nb = __builtin_amdgcn_readfirstlane((n - pb < 64) ? n - pb : 64);
-        // batch positions [0, split) are in the first range, [split, nb) in the second
-        const int split = __builtin_amdgcn_readfirstlane(n0 - pb < 0 ? 0 : (n0 - pb < nb ? n0 - pb : nb));
+    for (int pb = qa; pb < qb; pb += 64) {
+        const int nb = __builtin_amdgcn_readfirstlane((qb - pb < 64) ? qb - pb : 64);
+        // batch positions [0, split0) are in the first range, [split0, nb) in the second
+        const int split0 = __builtin_amdgcn_readfirstlane(n0 - pb < 0 ? 0 : (n0 - pb < nb ? n0 - pb : nb));
         __syncthreads();
         if (lane < nb) pu[lane] = rec[pidx(pb + lane)];
         __syncthreads();
         int cnt = 0;  // lane p: entries of the batch's particle p so far
-        int jn = 0, coden = 0;
-        vec4_t<T> un;
-        un.x = un.y = un.z = un.w = T(0);
-        if (lane < M) fetch(lane, jn, un, coden);
-        for (int c0 = 0; c0 < M; c0 += 64) {
-            const bool valid = c0 + lane < M;
-            const int jc = jn;
-            T uj[3] = {T(0), T(0), T(0)}, sh[3];
-            unpack_u<T, DIM>(un, uj);
-            sh[0] = T(((coden >> kStencilIdBits) & 3) - 1) * S.L;
-            sh[1] = T(((coden >> (kStencilIdBits + 2)) & 3) - 1) * S.L;
-            sh[2] = T(((coden >> (kStencilIdBits + 4)) & 3) - 1) * S.L;
-            const T Aj = S.H + un.w;   // PERPAIR: H + h_j
-            // PERPAIR lists only need to hold a superset of the pairs within H (the sweeps test
-            // those exactly), so their distance takes the candidate's image once per chunk and
-            // contracted products; exact lists keep the predicate's own arithmetic
-            T ujs[3];
+        for (int c0 = 0; c0 < M; c0 += 64 * NC) {
+            int jc[NC], code[NC];
+            T uj[NC][3], Aj[NC];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) ujs[k] = uj[k] + sh[k];
-            if (c0 + 64 + lane < M) fetch(c0 + 64 + lane, jn, un, coden);  // next chunk in flight
-            const unsigned long long vmask = __ballot(valid);
-            // the rounds of batch positions [p0, p1), whose rows follow each other from row
-            auto rounds = [&](int p0, int p1, int32_t* row) {
-            for (int p = p0; p < p1; ++p, row += width) {
-                T ui[3] = {T(0), T(0), T(0)};
-                const vec4_t<T> rp = pu[p];
-                unpack_u<T, DIM>(rp, ui);
-                bool inr;
-                if (PERPAIR) {
-                    const T Rp = Aj + rp.w;
-                    const T d0 = ui[0] - ujs[0];
-                    T r2 = d0 * d0;
-#pragma unroll
-                    for (int k = 1; k < DIM; ++k) {
-                        const T d = ui[k] - ujs[k];
-                        r2 = fma(d, d, r2);
-                    }
-                    inr = r2 < Rp * Rp;
-                } else {
-                    inr = dist2_exact<T, DIM>(ui, uj, sh) < R2;
-                }
-                const unsigned long long mask = __ballot(inr) & vmask;
-                const bool ok = valid & inr;
-                const int base = __builtin_amdgcn_readlane(cnt, p);
-                const int total = base + __popcll(mask);
-                // base plus the accepted lanes below this one
-                const unsigned pos = __builtin_amdgcn_mbcnt_hi(
-                    unsigned(mask >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(mask), unsigned(base)));
-                if (total <= width) {           // wave-uniform: the whole run fits the row
-                    if (ok) row[pos] = jc;
-                } else if (ok && pos < unsigned(width)) {
-                    row[pos] = jc;
-                }
-                cnt = (lane == p) ? total : cnt;  // lane p keeps p's count
+            for (int k = 0; k < NC; ++k) {
+                // past the stream: out of every particle's reach (the squared distance overflows)
+                vec4_t<T> un;
+                un.x = un.y = un.z = T(1e38);
+                un.w = T(0);
+                jc[k] = 0;
+                code[k] = 1 | (1 << 2) | (1 << 4);
+                code[k] <<= kStencilIdBits;
+                const int m = c0 + 64 * k + lane;
+                if (m < M) fetch(m, jc[k], un, code[k]);
+                uj[k][2] = T(0);
+                unpack_u<T, DIM>(un, uj[k]);
+                Aj[k] = SH + un.w;   // PERPAIR: H + h_j
             }
+            auto shift_of = [&](int k, int d) {
+                return T(((code[k] >> (kStencilIdBits + 2 * d)) & 3) - 1) * SL;
             };
-            rounds(0, split, nbr + (int64_t)(i0 + pb) * width);
-            if (kGroup) rounds(split, nb, nbr + (int64_t)pidx(pb + split) * width);
+            if (PERPAIR && !inside) {
+                // PERPAIR lists only need to hold a superset of the pairs within H (the sweeps test
+                // those exactly), so their distance takes the candidate's image once per tile and
+                // contracted products; exact lists keep the predicate's own arithmetic
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+#pragma unroll
+                    for (int d = 0; d < DIM; ++d) uj[k][d] = uj[k][d] + shift_of(k, d);
+            }
+            // The batch positions [p0, p1), whose rows follow each other from row, against the tile's
+            // first NA chunks.  Straight-line code for a run that fits the row: the scalar unit issues
+            // as many instructions per test as the vector unit, so every branch here counts.
+            auto rounds = [&](auto images, auto chunks, int p0, int p1, int32_t* row) {
+                constexpr int NA = decltype(chunks)::value;
+                vec4_t<T> rn = pu[p0];
+                for (int p = p0; p < p1; ++p, row += width) {
+                    const vec4_t<T> rp = rn;
+                    rn = pu[p + 1];
+                    T ui[3] = {T(0), T(0), T(0)};
+                    unpack_u<T, DIM>(rp, ui);
+                    unsigned long long mask[NA];
+                    bool in[NA];
+#pragma unroll
+                    for (int k = 0; k < NA; ++k) {
+                        if (PERPAIR) {
+                            const T Rp = Aj[k] + rp.w;
+                            const T d0 = ui[0] - uj[k][0];
+                            T r2 = d0 * d0;
+#pragma unroll
+                            for (int d = 1; d < DIM; ++d) {
+                                const T dd = ui[d] - uj[k][d];
+                                r2 = fma(dd, dd, r2);
+                            }
+                            in[k] = r2 < Rp * Rp;
+                        } else if (decltype(images)::value) {
+                            const T sh[3] = {shift_of(k, 0), shift_of(k, 1), shift_of(k, 2)};
+                            in[k] = dist2_exact<T, DIM>(ui, uj[k], sh) < R2;
+                        } else {
+                            const T sh[3] = {T(0), T(0), T(0)};   // d - 0 is d
+                            in[k] = dist2_exact<T, DIM>(ui, uj[k], sh) < R2;
+                        }
+                        mask[k] = __ballot(in[k]);
+                    }
+                    const int base = __builtin_amdgcn_readlane(cnt, p);
+                    int c[NA], total = base;
+#pragma unroll
+                    for (int k = 0; k < NA; ++k) {
+                        c[k] = __popcll(mask[k]);
+                        total += c[k];
+                    }
+                    // an accepted lane's place: after the accepted lanes below it and the earlier chunks
+                    if (total <= width) {   // wave-uniform: the whole run fits the row
+                        char* at = reinterpret_cast<char*>(row) + 4 * (int64_t)base;
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) {
+                            const unsigned below = __builtin_amdgcn_mbcnt_hi(
+                                unsigned(mask[k] >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(mask[k]), 0u));
+                            if (in[k]) *reinterpret_cast<int32_t*>(at + (below << 2)) = jc[k];
+                            at += 4 * c[k];
+                        }
+                    } else {
+                        int first = base;
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) {
+                            const unsigned pos = __builtin_amdgcn_mbcnt_hi(
+                                unsigned(mask[k] >> 32),
+                                __builtin_amdgcn_mbcnt_lo(unsigned(mask[k]), unsigned(first)));
+                            if (in[k] && pos < unsigned(width)) row[pos] = jc[k];
+                            first += c[k];
+                        }
+                    }
+                    cnt = (lane == p) ? total : cnt;   // lane p keeps p's count
+                }
+            };
+            auto tile = [&](auto images, auto chunks) {
+                rounds(images, chunks, 0, split0, nbr + (int64_t)(i0 + pb) * width);
+                if (kGroup) rounds(images, chunks, split0, nb, nbr + (int64_t)pidx(pb + split0) * width);
+            };
+            auto sized = [&](auto images) {
+                const int left = M - c0;   // wave-uniform
+                if (left > 192) tile(images, std::integral_constant<int, 4>{});
+                else if (left > 128) tile(images, std::integral_constant<int, 3>{});
+                else if (left > 64) tile(images, std::integral_constant<int, 2>{});
+                else tile(images, std::integral_constant<int, 1>{});
+            };
+            static_assert(NC == 4, "a tile has four chunks");
+            if (PERPAIR || inside) sized(std::false_type{});
+            else sized(std::true_type{});
         }
         if (lane < nb) {
             const int i = pidx(pb + lane);
