@@ -114,7 +114,7 @@ struct sph_plan {
     // workspace layout (byte offsets)
     size_t o_simc = 0, o_psim = 0, o_cell_sim = 0, o_blk_coord = 0, o_blk_rank = 0;
     size_t o_cell_count = 0, o_cell_start = 0, o_part = 0, o_cell_of = 0, o_slot_of = 0, o_tmp = 0;
-    size_t o_SB = 0, o_jdA = 0, o_jdB = 0, o_status = 0, o_part64 = 0, o_pairs = 0, o_ticket = 0, o_uref = 0;
+    size_t o_SB = 0, o_jdA = 0, o_status = 0, o_part64 = 0, o_pairs = 0, o_ticket = 0, o_uref = 0;
     // status words of the neighbour export's own list build, kept apart from the plan's status
     // words (an overflow there is returned by sph_neighbors, not left for sph_poll)
     size_t o_status_x = 0;
@@ -122,7 +122,8 @@ struct sph_plan {
     size_t o_poll = 0;
     // two buffers of adjoint prologue records; adj_buf is the one in use, and adj_ready the tape
     // slot whose records an adjoint sweep has already written there (-1: none)
-    size_t o_jdA2 = 0, o_jdB2 = 0;
+    size_t o_jdA2 = 0;
+    size_t o_cots = 0;   // cotangents in sorted order, between the adjoint sweeps of a reuse interval
     int adj_buf = 0, adj_ready = -1;
     std::vector<SlotLayout> slot;
     // Every write of a slot's sorted state or lists gives the slot a new generation number; the
@@ -211,6 +212,9 @@ namespace {
 
 template <typename T>
 T* wsp(const sph_plan* p, size_t off) { return reinterpret_cast<T*>(p->ws + off); }
+
+// The particle -> simulation table, null for a plan of one simulation.
+const int32_t* sim_table(const sph_plan* P) { return P->nsims == 1 ? nullptr : wsp<int32_t>(P, P->o_psim); }
 
 size_t tsize(const sph_plan* p) { return p->dtype == SPH_F64 ? 8 : 4; }
 
@@ -474,6 +478,16 @@ sph_status build_lists(sph_plan* P, int slot, hipStream_t st, bool exact = false
     return SPH_OK;
 }
 
+// Lanes per particle that a sweep runs with.  Eight lanes fill the GPU with a small plan; from two
+// wavefronts per SIMD on, four are faster in FP32 2D, where a row is two turns of eight lanes' 32
+// positions and the second is mostly empty (24 uneven simulations, 110 000 particles: forward 25.1 us
+// against 28.2, adjoint 32.8 against 36.5).  Results do not depend on it.
+template <typename T, int D>
+int sweep_lanes(const sph_plan* P, int set)
+{
+    return sizeof(T) == 4 && D == 2 && set == 8 && P->N * 4 >= 64 * 2048 ? 4 : set;
+}
+
 // Renormalised density gradient of the state sorted into L, with the lists of LL (and L_i
 // when `with_l`, for the adjoint).
 template <typename T, int D, int LPP>
@@ -484,7 +498,7 @@ void launch_renorm(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, hipSt
     k_renorm<T, D, LPP><<<grid_for(lanes, 256), 256, 0, st>>>(
         P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
         wsp<vec4_t<T>>(P, L.jd1), ws_state<T, D>(P, L.SA).rho, wsp<int32_t>(P, P->o_psim),
-        wsp<SimConst<T>>(P, P->o_simc), P->filter ? 1 : 0, wsp<vec4_t<T>>(P, P->o_jdG),
+        wsp<SimConst<T>>(P, P->o_simc), wsp<vec4_t<T>>(P, P->o_jdG),
         with_l ? wsp<vec4_t<T>>(P, P->o_jdL) : nullptr);
 }
 
@@ -493,20 +507,21 @@ void launch_sweep(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, StateP
                   T* rhosum, NextCells next, NextSlot<T> ns, hipStream_t st, ProfScope* prof)
 {
     const int64_t lanes = P->N * LPP;
+    constexpr int threads = kSweepThreads<T, D, LPP>;
     if (P->renorm) {
-        launch_k(prof, k_sweep<T, D, MODE, LPP, true>, dim3(grid_for(lanes, 256)), dim3(256), st,
+        launch_k(prof, k_sweep<T, D, MODE, LPP, true>, dim3(grid_for(lanes, threads)), dim3(threads), st,
             P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
             wsp<vec4_t<T>>(P, L.jd1), ws_state<T, D>(P, L.SA), dst, wsp<int32_t>(P, L.orig), drho, acc, rhosum,
-            wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), next, ns,
-            P->filter ? 1 : 0, P->filter ? wsp<unsigned long long>(P, P->o_pairs) : nullptr,
+            sim_table(P), wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), next, ns,
+            P->filter ? wsp<unsigned long long>(P, P->o_pairs) : nullptr,
             (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_jdG));
         return;
     }
-    launch_k(prof, k_sweep<T, D, MODE, LPP, false>, dim3(grid_for(lanes, 256)), dim3(256), st,
+    launch_k(prof, k_sweep<T, D, MODE, LPP, false>, dim3(grid_for(lanes, threads)), dim3(threads), st,
         P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
         wsp<vec4_t<T>>(P, L.jd1), ws_state<T, D>(P, L.SA), dst, wsp<int32_t>(P, L.orig), drho, acc, rhosum,
-        wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), next, ns,
-        P->filter ? 1 : 0, P->filter ? wsp<unsigned long long>(P, P->o_pairs) : nullptr,
+        sim_table(P), wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), next, ns,
+        P->filter ? wsp<unsigned long long>(P, P->o_pairs) : nullptr,
         (const vec4_t<T>*)nullptr);
 }
 
@@ -543,7 +558,7 @@ sph_status sweep(sph_plan* P, int slot, T* drho, T* acc, T* rhosum, hipStream_t 
         LAUNCH_CHECK("renorm");
     }
     ProfScope prof(P, st, SPH_KERN_SWEEP, true);
-    switch (P->lpp_fwd) {
+    switch (sweep_lanes<T, D>(P, P->lpp_fwd)) {
     case 2: launch_sweep<T, D, MODE, 2>(P, L, LL, dst, drho, acc, rhosum, next, ns, st, &prof); break;
     case 8: launch_sweep<T, D, MODE, 8>(P, L, LL, dst, drho, acc, rhosum, next, ns, st, &prof); break;
     default: launch_sweep<T, D, MODE, 4>(P, L, LL, dst, drho, acc, rhosum, next, ns, st, &prof); break;
@@ -564,28 +579,28 @@ sph_status unsort_from(sph_plan* P, StatePtrs<T, D> src, int slot, StatePtrs<T, 
 }
 
 size_t jdA_off(const sph_plan* P, int buf) { return buf ? P->o_jdA2 : P->o_jdA; }
-size_t jdB_off(const sph_plan* P, int buf) { return buf ? P->o_jdB2 : P->o_jdB; }
 
 template <typename T, int D, int LPP>
-void launch_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, StatePtrs<T, D> cot, hipStream_t st,
-                bool vjp, ProfScope* prof, NextAdj<T> na)
+void launch_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, StatePtrs<T, D> cin, bool cin_sorted,
+                StatePtrs<T, D> cout, bool cout_sorted, hipStream_t st, bool vjp, ProfScope* prof, NextAdj<T> na)
 {
     const int64_t lanes = P->N * LPP;
+    constexpr int threads = kSweepThreads<T, D, LPP>;
     if (P->renorm) {
-        launch_k(prof, k_adj_sweep<T, D, LPP, true>, dim3(grid_for(lanes, 256)), dim3(256), st,
+        launch_k(prof, k_adj_sweep<T, D, LPP, true>, dim3(grid_for(lanes, threads)), dim3(threads), st,
             P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
-            wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)),
-            wsp<vec4_t<T>>(P, jdB_off(P, P->adj_buf)), wsp<int32_t>(P, L.orig), cot, wsp<int32_t>(P, P->o_psim),
-            wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), P->filter ? 1 : 0, vjp ? 1 : 0,
+            wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)), wsp<int32_t>(P, L.orig), cin,
+            cin_sorted ? 1 : 0, cout, cout_sorted ? 1 : 0, sim_table(P), wsp<SimConst<T>>(P, P->o_simc),
+            wsp<int32_t>(P, P->o_status), vjp ? 1 : 0,
             (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_jdG), (const vec4_t<T>*)wsp<vec4_t<T>>(P, P->o_jdL),
             wsp<vec4_t<T>>(P, P->o_gbar), na);
         return;
     }
-    launch_k(prof, k_adj_sweep<T, D, LPP, false>, dim3(grid_for(lanes, 256)), dim3(256), st,
+    launch_k(prof, k_adj_sweep<T, D, LPP, false>, dim3(grid_for(lanes, threads)), dim3(threads), st,
         P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
-        wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)),
-        wsp<vec4_t<T>>(P, jdB_off(P, P->adj_buf)), wsp<int32_t>(P, L.orig), cot, wsp<int32_t>(P, P->o_psim),
-        wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status), P->filter ? 1 : 0, vjp ? 1 : 0,
+        wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)), wsp<int32_t>(P, L.orig), cin,
+        cin_sorted ? 1 : 0, cout, cout_sorted ? 1 : 0, sim_table(P), wsp<SimConst<T>>(P, P->o_simc),
+        wsp<int32_t>(P, P->o_status), vjp ? 1 : 0,
         (const vec4_t<T>*)nullptr, (const vec4_t<T>*)nullptr, (vec4_t<T>*)nullptr, na);
 }
 
@@ -597,37 +612,36 @@ void launch_renorm_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, S
     const int64_t lanes = P->N * LPP;
     k_renorm_adj<T, D, LPP><<<grid_for(lanes, 256), 256, 0, st>>>(
         P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
-        wsp<vec4_t<T>>(P, jdB_off(P, P->adj_buf)), wsp<vec4_t<T>>(P, P->o_jdG), wsp<vec4_t<T>>(P, P->o_gbar),
-        wsp<int32_t>(P, L.orig), cot, wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc),
-        P->filter ? 1 : 0);
+        wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, P->o_jdG), wsp<vec4_t<T>>(P, P->o_gbar),
+        wsp<int32_t>(P, L.orig), cot, wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc));
 }
 
 // Adjoint of the step that starts from the state in `slot` (sorted with its lists built).
 // With vjp, the update function's VJP instead: cot holds the cotangents (kx, ka, krho) of
 // (v, a, drho/dt) on entry and (xbar, vbar, rhobar) on exit.
 // With next_slot >= 0 (a tape slot sharing this slot's particle order, whose adjoint runs next),
-// the sweep also writes that step's prologue records into the other buffer, and the next call
-// skips its prologue.
+// the sweep also writes that step's prologue records into the other buffer and the cotangents in
+// sorted order, and the next call skips its prologue and reads those; the last sweep of such a
+// chain writes cot.
 template <typename T, int D>
 sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, bool vjp = false,
                    int next_slot = -1)
 {
     if (P->N == 0) return SPH_OK;
     const SlotLayout& L = P->slot[slot];
-    if (P->adj_ready != slot) {
+    const bool ready = P->adj_ready == slot;   // the sweep before left this slot's records and cotangents
+    if (!ready) {
         ProfScope prof(P, st, SPH_KERN_OTHER);
         k_adj_prologue<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(
             P->N, wsp<int32_t>(P, L.orig), cot, ws_state<T, D>(P, L.SA), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)),
-            wsp<vec4_t<T>>(P, jdB_off(P, P->adj_buf)), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc),
-            vjp ? 1 : 0);
+            wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), vjp ? 1 : 0);
         LAUNCH_CHECK("adj_prologue");
     }
     P->adj_ready = -1;
     const bool fuse = next_slot >= 0 && !vjp && !P->renorm;
-    NextAdj<T> na{nullptr, nullptr, nullptr};
+    NextAdj<T> na{nullptr, nullptr};
     if (fuse)
-        na = NextAdj<T>{wsp<vec4_t<T>>(P, jdA_off(P, 1 - P->adj_buf)), wsp<vec4_t<T>>(P, jdB_off(P, 1 - P->adj_buf)),
-                        ws_state<T, D>(P, P->slot[next_slot].SA).rho};
+        na = NextAdj<T>{wsp<vec4_t<T>>(P, jdA_off(P, 1 - P->adj_buf)), ws_state<T, D>(P, P->slot[next_slot].SA).rho};
     const SlotLayout& LL = P->slot[P->list_of[slot]];
     if (P->renorm) {
         // the step's renormalised gradients and L_i, recomputed from its sorted state
@@ -639,11 +653,13 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
         LAUNCH_CHECK("renorm");
     }
     {
+        const StatePtrs<T, D> sorted = ws_state<T, D>(P, P->o_cots);
+        const StatePtrs<T, D> cin = ready ? sorted : cot, cout = fuse ? sorted : cot;
         ProfScope prof(P, st, SPH_KERN_ADJOINT, true);
-        switch (P->lpp_adj) {
-        case 2: launch_adj<T, D, 2>(P, L, LL, cot, st, vjp, &prof, na); break;
-        case 8: launch_adj<T, D, 8>(P, L, LL, cot, st, vjp, &prof, na); break;
-        default: launch_adj<T, D, 4>(P, L, LL, cot, st, vjp, &prof, na); break;
+        switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
+        case 2: launch_adj<T, D, 2>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
+        case 8: launch_adj<T, D, 8>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
+        default: launch_adj<T, D, 4>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
         }
         LAUNCH_CHECK("adj_sweep");
     }
@@ -733,7 +749,7 @@ void launch_shift(sph_plan* P, StatePtrs<T, D> st_user, T beta, hipStream_t st)
     const SlotLayout& L = P->slot[0];
     k_shift<T, D, LPP><<<grid_for(P->N * LPP, 256), 256, 0, st>>>(
         P->N, P->width, wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), wsp<vec4_t<T>>(P, L.jd0),
-        wsp<int32_t>(P, L.orig), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), P->filter ? 1 : 0, beta,
+        wsp<int32_t>(P, L.orig), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), beta,
         st_user);
 }
 
@@ -744,7 +760,7 @@ void launch_shift_adj(sph_plan* P, StatePtrs<T, D> cot, T beta, hipStream_t st)
     k_shift_adj<T, D, LPP><<<grid_for(P->N * LPP, 256), 256, 0, st>>>(
         P->N, P->width, wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), wsp<vec4_t<T>>(P, L.jd0),
         wsp<vec4_t<T>>(P, P->o_jdA), ws_state<T, D>(P, L.SA).rho, wsp<int32_t>(P, L.orig), wsp<int32_t>(P, P->o_psim),
-        wsp<SimConst<T>>(P, P->o_simc), P->filter ? 1 : 0, beta, cot);
+        wsp<SimConst<T>>(P, P->o_simc), beta, cot);
 }
 
 template <typename T, int D>
@@ -1295,8 +1311,7 @@ void launch_density_adj(sph_plan* P, const SlotLayout& L, const T* gs, T* xbar, 
     const int64_t lanes = P->N * LPP;
     k_density_adj<T, D, LPP><<<grid_for(lanes, 256), 256, 0, st>>>(
         P->N, P->width, wsp<int32_t>(P, L.nbr), wsp<int32_t>(P, L.cnt), wsp<vec4_t<T>>(P, L.jd0), gs,
-        wsp<int32_t>(P, L.orig), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), xbar,
-        P->filter ? 1 : 0);
+        wsp<int32_t>(P, L.orig), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc), xbar);
 }
 
 // Summation-density VJP of the state s: sort, lists, the cotangent gathered into sorted
@@ -1584,9 +1599,8 @@ sph_status sph_plan_create(const sph_params* sims, int32_t nsims, const int64_t*
     P->o_tmp = take(4 * N);
     P->o_SB = take(T * N * (2 * d + 1));
     P->o_jdA = take(V4 * N);
-    P->o_jdB = take(V4 * N);
     P->o_jdA2 = take(V4 * N);
-    P->o_jdB2 = take(V4 * N);
+    P->o_cots = take(T * N * (2 * d + 1));
     P->o_status = take(4 * (size_t)nsims);
     P->o_status_x = take(4 * (size_t)nsims);
     P->o_part64 = take(8 * ((size_t)P->nparts64 + 1) + 8 * (N + 1));

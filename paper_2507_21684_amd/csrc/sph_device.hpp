@@ -563,6 +563,23 @@ __device__ __forceinline__ void unpack_u(const vec4_t<T>& a, T* u)
     if (DIM == 3) u[2] = a.z;
 }
 
+// ---------------------------------------------------------------- list rows
+//
+// A row holds list position k (canonical order) at offset list_offset(k).  Inside every group of 16
+// positions the two low and the two high bits of the position change places, so that four consecutive
+// offsets hold positions p, p + 4, p + 8, p + 12: with four lanes per particle one 16-byte load is a
+// lane's share of the group (positions congruent to the lane modulo 4), and the four lanes still gather
+// four consecutive positions at a time, which are mostly consecutive particles of one cell, i.e. one or
+// two cache lines.  (Rows in canonical order took a load per entry, or a 4 x 4 transpose by DPP: 18
+// vector instructions per lane and group, about a tenth of the pair work.)  The width is a multiple of
+// 8; where it is not one of 16, the last 8 positions stay in order.  The build fills a row up to the
+// next multiple of 16 positions with the particle itself, whose pair adds exactly zero to every sum,
+// so the sweeps test no position against the count.
+__device__ __forceinline__ int list_offset(int k, int width)
+{
+    return k < (width & ~15) ? (k & ~15) | ((k & 3) << 2) | ((k >> 2) & 3) : k;
+}
+
 // ---------------------------------------------------------------- neighbour lists
 
 // The pair counter is spread over kPairSlots words, one per 128-byte line, so that the
@@ -608,8 +625,8 @@ constexpr int kCandTable = 2048;
 // wavefront's particles, staged in LDS, are taken one after the other with the same address in
 // every lane.  For a particle the tile's chunks are independent tests of 64 candidates each; the
 // ballot of the accepted ones gives each its rank, so a chunk appends a contiguous run to the
-// particle's row, in candidate order.  Lane p keeps p's running count.  Lists are row-major: entry k
-// of particle i is nbr[i * width + k].
+// particle's row, in candidate order.  Lane p keeps p's running count.  Lists are row-major: list
+// position k of particle i is nbr[i * width + list_offset(k, width)].
 // Bound: instruction issue (the tests; the matrix cores cannot evaluate the predicate's rounding),
 // and in plans of few cells the wavefront's serial chain.  Taking a tile of chunks per particle
 // instead of one reads the particle's position and count once per tile and leaves the chunks' tests
@@ -665,6 +682,7 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
     if (qa == qb) return;
     const SimConst<T>& S = sims[s];
     const T SL = S.L, SH = S.H;
+    const int width16 = width & ~15;
     const int sub = S.sub, nc = S.nc;
     const int sw1 = 2 * sub + 1 + kExt;
     const int ncu = kGroup ? sw1 * sw1 : S.ncu;
@@ -814,23 +832,26 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
                         total += c[k];
                     }
                     // an accepted lane's place: after the accepted lanes below it and the earlier chunks
-                    if (total <= width) {   // wave-uniform: the whole run fits the row
-                        char* at = reinterpret_cast<char*>(row) + 4 * (int64_t)base;
-#pragma unroll
-                        for (int k = 0; k < NA; ++k) {
-                            const unsigned below = __builtin_amdgcn_mbcnt_hi(
-                                unsigned(mask[k] >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(mask[k]), 0u));
-                            if (in[k]) *reinterpret_cast<int32_t*>(at + (below << 2)) = jc[k];
-                            at += 4 * c[k];
-                        }
-                    } else {
-                        int first = base;
+                    int first = base;
+                    if (total <= width16) {   // wave-uniform: the whole run fits the row's full groups
 #pragma unroll
                         for (int k = 0; k < NA; ++k) {
                             const unsigned pos = __builtin_amdgcn_mbcnt_hi(
                                 unsigned(mask[k] >> 32),
                                 __builtin_amdgcn_mbcnt_lo(unsigned(mask[k]), unsigned(first)));
-                            if (in[k] && pos < unsigned(width)) row[pos] = jc[k];
+                            // 4 list_offset(pos, width), as two bit-field inserts
+                            const unsigned mid = ((pos << 4) & 48u) | (pos & ~48u);
+                            const unsigned off = (mid & 60u) | ((pos << 2) & ~60u);
+                            if (in[k]) *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(row) + off) = jc[k];
+                            first += c[k];
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) {
+                            const unsigned pos = __builtin_amdgcn_mbcnt_hi(
+                                unsigned(mask[k] >> 32),
+                                __builtin_amdgcn_mbcnt_lo(unsigned(mask[k]), unsigned(first)));
+                            if (in[k] && pos < unsigned(width)) row[list_offset((int)pos, width)] = jc[k];
                             first += c[k];
                         }
                     }
@@ -851,6 +872,14 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
             static_assert(NC == 4, "a tile has four chunks");
             if (PERPAIR || inside) sized(std::false_type{});
             else sized(std::true_type{});
+        }
+        // each row filled up to a whole group of 16 positions with the particle itself: 16 lanes a row
+        for (int p0 = 0; p0 < nb; p0 += 4) {
+            const int p = p0 + (lane >> 4), i = pidx(pb + p);
+            const int have = __shfl(cnt, p & 63, 64);
+            const int pos = have + (lane & 15);
+            if (p < nb && pos < ((have + 15) & ~15) && pos < width)
+                nbr[(int64_t)i * width + list_offset(pos, width)] = i;
         }
         if (lane < nb) {
             const int i = pidx(pb + lane);
@@ -900,77 +929,196 @@ __device__ __forceinline__ V ldo(const V* __restrict__ base, uint32_t idx)
     return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + idx * (uint32_t)sizeof(V));
 }
 
-// List entries of lane r at its positions m0 .. m0 + U - 1 (position k = r + LPP m of the row);
-// positions past the lane's count read as the particle itself, a valid index whose pair is
-// skipped.  The sweeps load the next group's entries before computing the current one, so
-// that only the record gathers stand between consecutive groups.
-template <int LPP, int U>
-__device__ __forceinline__ void load_entries(const int32_t* __restrict__ row, int r, int m0, int mcount, int self,
-                                             int* jj)
+// ---------------------------------------------------------------- traversal of a list row
+
+// One lane's list entries of a group of 16 positions: with 4 lanes a = positions r, r + 4, r + 8,
+// r + 12; with 8 lanes the same of r mod 4 (half of it is the lane's); with 2 lanes also b, those
+// of r + 2.
+struct ListGroup {
+    int4 a, b;
+};
+
+template <int LPP>
+__device__ __forceinline__ ListGroup load_group(const int32_t* __restrict__ row, int g, int r)
 {
-#pragma unroll
-    for (int u = 0; u < U; ++u) jj[u] = (m0 + u < mcount) ? row[r + LPP * (m0 + u)] : self;
+    ListGroup c;
+    const int32_t* p = row + 16 * g;
+    c.a = *reinterpret_cast<const int4*>(p + 4 * (r & 3));
+    c.b = LPP == 2 ? *reinterpret_cast<const int4*>(p + 4 * (r + 2)) : c.a;
+    return c;
 }
 
-// The same entries with every load issued unconditionally: the position is clamped to the row
-// (width entries), so the load needs no branch, and past the lane's count the entry read is
-// replaced by the particle itself.
-template <int LPP, int U>
-__device__ __forceinline__ void load_entries_clamped(const int32_t* __restrict__ row, int width, int r, int m0,
-                                                     int mcount, int self, int* jj)
+// Entry u (0 or 1) of the lane's half step e in a group: its list positions r + LPP (2 e + u).
+// (The selections are of values: a conditional of lvalues becomes an indexed array in LDS.)
+template <int LPP>
+__device__ __forceinline__ int group_entry(const ListGroup& c, int e, int u, int r)
 {
+    const int x = c.a.x, y = c.a.y, z = c.a.z, w = c.a.w;
+    if (LPP == 8) {
+        const bool odd = (r & 4) != 0;
+        return u ? (odd ? +w : +z) : (odd ? +y : +x);
+    }
+    if (LPP == 4) return e ? (u ? w : z) : (u ? y : x);
+    if (u) return e == 0 ? c.b.x : e == 1 ? c.b.y : e == 2 ? c.b.z : c.b.w;
+    return e == 0 ? x : e == 1 ? y : e == 2 ? z : w;
+}
+
+// Keeps the loads of a record where they were issued: without it the compiler sinks them past the
+// exit test that follows, to their first use, and every pair waits for its own gather.
+template <int N = 4, typename V>
+__device__ __forceinline__ void pin(V& v)
+{
+    if (N == 4) asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    else asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z));
+}
+
+// The pairs of lane r of the LPP lanes that share a particle, over the n positions of its row, four at
+// a time: gather(j, rec) loads the records of neighbour j, pair(q, rec) adds its terms to the lane's
+// partial sum q.  Position k = r + LPP m belongs to partial sum m mod (8 / LPP), in increasing m.
+// The four neighbours' records are gathered together, with the next list entries behind them, and
+// computed without a branch in between: the more gathers in flight the better where gathers bound the
+// sweep (FP32: with two pairs at a time, the next two gathered meanwhile, the 512-simulation batch took
+// 375 us a forward sweep against 335).  This part covers the full groups of 16 positions of the row;
+// list_tail the last half group.
+template <int LPP, typename REC, typename GATHER, typename PAIR>
+__device__ __forceinline__ void sweep_burst(const int32_t* __restrict__ row, int width, int n, int r, int self,
+                                           GATHER&& gather, PAIR&& pair)
+{
+    const int groups = width >> 4;
+    n = n < 16 * groups ? n : 16 * groups;
+    if (n <= 0) return;
+    if (LPP == 2) {
+        // a group is two turns of 8 positions
+        ListGroup c = load_group<LPP>(row, 0, r);
+        for (int g = 0;; ++g) {
+            const ListGroup nx = load_group<LPP>(row, g + 1 < groups ? g + 1 : g, r);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int pos = r + LPP * (m0 + u);
-        const int e = row[pos < width ? pos : width - 1];
-        jj[u] = (m0 + u < mcount) ? e : self;
+            for (int h = 0; h < 2; ++h) {
+                REC rec[4];
+                gather(group_entry<LPP>(c, 2 * h, 0, r), rec[0]);
+                gather(group_entry<LPP>(c, 2 * h, 1, r), rec[1]);
+                gather(group_entry<LPP>(c, 2 * h + 1, 0, r), rec[2]);
+                gather(group_entry<LPP>(c, 2 * h + 1, 1, r), rec[3]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pair(u, rec[u]);
+                if (16 * g + 8 * (h + 1) >= n) return;
+            }
+            c = nx;
+        }
+    } else {
+        constexpr int GI = LPP == 8 ? 2 : 1;   // groups per turn
+        ListGroup c0 = load_group<LPP>(row, 0, r);
+        ListGroup c1 = load_group<LPP>(row, GI == 2 && groups > 1 ? 1 : 0, r);
+        for (int g = 0;; g += GI) {
+            REC rec[4];
+            gather(group_entry<LPP>(c0, 0, 0, r), rec[0]);
+            gather(group_entry<LPP>(c0, 0, 1, r), rec[1]);
+            if (LPP == 8) {
+                // past the row's filled groups the entries are not list entries
+                const bool more = 16 * (g + 1) < n;
+                gather(more ? group_entry<LPP>(c1, 0, 0, r) : self, rec[2]);
+                gather(more ? group_entry<LPP>(c1, 0, 1, r) : self, rec[3]);
+            } else {
+                gather(group_entry<LPP>(c0, 1, 0, r), rec[2]);
+                gather(group_entry<LPP>(c0, 1, 1, r), rec[3]);
+            }
+            c0 = load_group<LPP>(row, g + GI < groups ? g + GI : 0, r);
+            if (GI == 2) c1 = load_group<LPP>(row, g + GI + 1 < groups ? g + GI + 1 : 0, r);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pair(LPP == 4 ? u & 1 : 0, rec[u]);
+            if (16 * (g + GI) >= n) return;
+        }
     }
 }
 
-
-
-// Four lanes per particle (adjoint sweep): each group of 16 list positions (16 g .. 16 g + 15,
-// four per lane) is read as four 16-byte chunks, lane r reading positions 16 g + 4 r .. + 3, and
-// a 4 x 4 transpose inside the lane quad gives lane r its positions r + 4 c (c = 0..3), the ones
-// the canonical assignment gives it: one load instead of four.
-// The chunk start is clamped to the row (width is a multiple of 8), so a chunk past the row end
-// rereads its last chunk, whose positions the caller discards.  A lane leaves the loop after its
-// own last position; the values it would pass to the lanes still looping are positions at or
-// past the row's count (lane c stops once 4 c + 16 g >= count), which those lanes discard too.
-__device__ __forceinline__ int4 load_chunk4(const int32_t* __restrict__ row, int width, int pos)
+// The same pairs two at a time, the records of the next two gathered while these are computed, the
+// list entries two groups ahead: for FP64, whose pair terms take several times as long as FP32's, so
+// that a wavefront hides its own gathers (2D 32^2, 64 wavefronts: 13.5 us a sweep with four at a time,
+// 8.8 with two ahead; 3D 20^3 27.3 and 20.9).
+template <int LPP, typename REC, typename GATHER, typename PAIR>
+__device__ __forceinline__ void sweep_piped(const int32_t* __restrict__ row, int width, int n, int r, int self,
+                                           GATHER&& gather, PAIR&& pair)
 {
-    pos = pos < width - 4 ? pos : width - 4;
-    return *reinterpret_cast<const int4*>(row + pos);
+    constexpr int HS = 8 / LPP;           // half steps of a group
+    constexpr int UN = HS == 1 ? 2 : 1;   // groups per turn (an even number of half steps)
+    const int groups = width >> 4;
+    n = n < 16 * groups ? n : 16 * groups;
+    if (n <= 0) return;
+    ListGroup c = load_group<LPP>(row, 0, r);
+    ListGroup nx = load_group<LPP>(row, groups > 1 ? 1 : 0, r);
+    REC rec[2][2];
+    gather(group_entry<LPP>(c, 0, 0, r), rec[0][0]);
+    gather(group_entry<LPP>(c, 0, 1, r), rec[0][1]);
+    for (int g0 = 0;; g0 += UN) {
+#pragma unroll
+        for (int s = 0; s < HS * UN; ++s) {
+            const int g = g0 + s / HS, e = s % HS;
+            const bool last = e + 1 == HS;
+            int j0, j1;
+            if (!last) {
+                j0 = group_entry<LPP>(c, e + 1, 0, r);
+                j1 = group_entry<LPP>(c, e + 1, 1, r);
+            } else {
+                // past the row's filled groups the entries are not list entries
+                const bool more = 16 * (g + 1) < n;
+                j0 = more ? group_entry<LPP>(nx, 0, 0, r) : self;
+                j1 = more ? group_entry<LPP>(nx, 0, 1, r) : self;
+            }
+            gather(j0, rec[(s + 1) & 1][0]);
+            gather(j1, rec[(s + 1) & 1][1]);
+            if (last) {
+                c = nx;
+                nx = load_group<LPP>(row, g + 2 < groups ? g + 2 : 0, r);
+            }
+            pair(LPP == 2 ? (2 * e) % 4 : 0, rec[s & 1][0]);
+            pair(LPP == 2 ? (2 * e + 1) % 4 : LPP == 4 ? 1 : 0, rec[s & 1][1]);
+            rec[(s + 1) & 1][0].keep();
+            rec[(s + 1) & 1][1].keep();
+            if (16 * g + 2 * LPP * (e + 1) >= n) return;
+        }
+    }
 }
 
-template <int CTRL>
-__device__ __forceinline__ int quad_perm(int v)
+template <bool PIPED, int LPP, typename REC, typename GATHER, typename PAIR>
+__device__ __forceinline__ void sweep_list(const int32_t* __restrict__ row, int width, int n, int r, int self,
+                                           GATHER&& gather, PAIR&& pair)
 {
-    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+    if (PIPED) sweep_piped<LPP, REC>(row, width, n, r, self, gather, pair);
+    else sweep_burst<LPP, REC>(row, width, n, r, self, gather, pair);
 }
 
-__device__ __forceinline__ void quad_transpose(int r, const int4& m, int* out)
+// The last 8 positions (in order) of a row whose width is 8 modulo 16, for the rare particle that
+// has so many neighbours.
+template <int LPP, typename REC, typename GATHER, typename PAIR>
+__device__ __forceinline__ void list_tail(const int32_t* __restrict__ row, int width, int n, int r, int self,
+                                          GATHER&& gather, PAIR&& pair)
 {
-    const bool hi = (r & 2) != 0, odd = (r & 1) != 0;
-    // exchange 2 x 2 blocks with lane r ^ 2 (quad permutation 2, 3, 0, 1)
-    const int y0 = quad_perm<0x4E>(hi ? m.x : m.z);
-    const int y1 = quad_perm<0x4E>(hi ? m.y : m.w);
-    const int n0 = hi ? y0 : m.x, n1 = hi ? y1 : m.y, n2 = hi ? m.z : y0, n3 = hi ? m.w : y1;
-    // exchange single elements with lane r ^ 1 (quad permutation 1, 0, 3, 2)
-    const int z0 = quad_perm<0xB1>(odd ? n0 : n1);
-    const int z1 = quad_perm<0xB1>(odd ? n2 : n3);
-    out[0] = odd ? z0 : n0;
-    out[1] = odd ? n1 : z0;
-    out[2] = odd ? z1 : n2;
-    out[3] = odd ? n3 : z1;
+    const int first = width & ~15;
+    if (n <= first) return;
+#pragma unroll
+    for (int m = 0; m < 8 / LPP; ++m) {
+        const int k = first + r + LPP * m;
+        REC rec;
+        gather(k < n ? row[k] : self, rec);
+        pair(m, rec);
+    }
+}
+
+// Positions the lanes of a particle visit for a row of n entries.
+template <typename T, int LPP>
+__device__ __forceinline__ int positions_visited(int n, int width)
+{
+    constexpr int kTurn = (sizeof(T) == 8 ? 2 : 4) * LPP;   // positions of one turn
+    const int first = width & ~15, m = n < first ? n : first;
+    return (m + kTurn - 1) / kTurn * kTurn + (n > first ? 8 : 0);
 }
 
 // Per-simulation constants the pair loops use, held in registers.
 template <typename T>
 struct PairConst {
-    T L, invL, invH, kG, kH, epsH2, cA, cD, H2;
-    T kGF;  // kG (-56/3): grad W = kGF t^5 (1 + 5 q) x_ij
-    T m;    // particle mass
+    T L, invL, H, invH, epsH2, cA, cD, H2, m;
+    T kGF;  // kG (-56/3): grad W = kGF t^5 (1 + 5 q) x_ij = kGF t^5 (6 - 5 t) x_ij
+    T hc;   // kH / kGF = -30 / H^2: the kernel Hessian is kGF (t^5 (6 - 5 t) I + hc t^4 x x^T)
 };
 
 // Squared distance of a listed pair with the arithmetic of the neighbour predicate (per
@@ -996,6 +1144,58 @@ __device__ __forceinline__ T r2_exact(const T* ui, const vec4_t<T>& a, T L, T in
     return r2;
 }
 
+// The pair vector and its square without the periodic image, with the same roundings: equal to
+// r2_exact for every pair within the support of a particle that lies more than the support inside the
+// box (the image term is zero there); any other pair comes out at its distance across the box, which is
+// past the support too.
+template <typename T, int DIM>
+__device__ __forceinline__ T r2_inner(const T* ui, const vec4_t<T>& a, T* d)
+{
+#pragma clang fp contract(off)
+    const T uj[3] = {a.x, a.y, a.z};
+    T r2 = T(0);
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        const T dk = ui[k] - uj[k];
+        d[k] = dk;
+        const T dd = dk * dk;
+        r2 = r2 + dd;
+    }
+    return r2;
+}
+
+template <typename T, int DIM, bool IMAGE>
+__device__ __forceinline__ T pair_vector(const T* ui, const vec4_t<T>& a, T L, T invL, T* d)
+{
+    if (IMAGE) return r2_exact<T, DIM>(ui, a, L, invL, d);
+    return r2_inner<T, DIM>(ui, a, d);
+}
+
+// Whether every lane's particle lies more than the support (and a margin for rounding) inside the box.
+template <typename T, int DIM>
+__device__ __forceinline__ bool wave_inside(const T* ui, T H, T L)
+{
+    const T lo = H * T(1.001), hi = L - lo;
+    bool in = true;
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) in = in && ui[k] > lo && ui[k] < hi;
+    return __all(in) != 0;
+}
+
+// x where it is positive, else zero; x <= 1 (FP32: the clamp of the instruction that makes x).
+template <typename T>
+__device__ __forceinline__ T positive_part(T x) { return x > T(0) ? x : T(0); }
+template <>
+__device__ __forceinline__ float positive_part<float>(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
+
+// t = 1 - r / H, zero from the support on: every pair term carries a power of t, so a listed pair past
+// the support (lists with a skin) adds exactly zero without a test.
+template <typename T>
+__device__ __forceinline__ T kernel_t(T r2, T invH)
+{
+    return positive_part(fma(-invH, fast_sqrt(r2), T(1)));
+}
+
 // What the sweep that finishes a step does for the next step when that step reuses the lists
 // (null jd0: the next step sorts and rebuilds): the next state goes straight into the next
 // tape slot in the same particle order, with its packed records and original indices, and each
@@ -1008,29 +1208,58 @@ struct NextSlot {
     const vec4_t<T>* uref;
 };
 
+// The simulation of sorted particle i; a plan of one simulation passes no table (psim null).
+__device__ __forceinline__ int sim_of(const int32_t* __restrict__ psim, int64_t i) { return psim ? psim[i] : 0; }
+
+template <typename T>
+__device__ __forceinline__ PairConst<T> pair_const(const SimConst<T>& S);
+
+// The constants of simulation s: by scalar loads where the wavefront holds one simulation (vector
+// loads of one address still cost the vector L1 an access per four lanes).
+template <typename T>
+__device__ __forceinline__ PairConst<T> pair_const_of(const SimConst<T>* __restrict__ sims, int s)
+{
+    const int s0 = __builtin_amdgcn_readfirstlane(s);
+    if (__all(s == s0)) return pair_const(sims[s0]);
+    return pair_const(sims[s]);
+}
+
 template <typename T>
 __device__ __forceinline__ PairConst<T> pair_const(const SimConst<T>& S)
 {
     PairConst<T> c;
     c.L = S.L;
     c.invL = S.invL;
+    c.H = S.H;
     c.invH = S.invH;
-    c.kG = S.kG;
-    c.kH = S.kH;
     c.epsH2 = S.epsH2;
     c.cA = S.cA;
     c.cD = S.cD;
     c.H2 = S.H2;
-    c.kGF = S.kG * T(-56.0 / 3.0);
     c.m = S.m;
+    c.kGF = S.kG * T(-56.0 / 3.0);
+    c.hc = T(-30) * (S.invH * S.invH);
     return c;
 }
 
 // ---------------------------------------------------------------- forward sweep
 
+// Workgroup of the forward and adjoint sweeps.  In FP32 3D with eight lanes 512, i.e. 64 particles, whose
+// neighbourhoods overlap in the vector L1 (3D 64^3: 213 and 317 us against 229 and 326 with 256; with
+// four lanes, where 256 lanes are 64 particles, 512 is no faster, and neither is it in 2D).
+template <typename T, int DIM, int LPP>
+constexpr int kSweepThreads = sizeof(T) == 4 && DIM == 3 && LPP == 8 ? 512 : 256;
+
 constexpr int kModeStep = 0;  // integrate into dst (sorted order)
 constexpr int kModeRhs = 1;   // write drho, a, rho_sum to caller arrays (original order)
-constexpr int kPairsInFlight = 4;  // list positions each lane loads before computing them
+
+// Weight of a neighbour in the pair sums: its volume in 2D (in its record), 1 / rho in 3D, where
+// the sums are multiplied by the particle mass at the end instead.
+template <typename T, int DIM>
+__device__ __forceinline__ T pair_weight(const vec4_t<T>& a)
+{
+    return DIM == 3 ? fast_rcp(a.w) : a.z;
+}
 
 // ---------------------------------------------------------------- renormalised density gradient
 //
@@ -1047,6 +1276,16 @@ template <typename T, int DIM>
 struct RenormAcc {
     T M[6];   // 2D: M00, M01, M11; 3D: M00, M01, M02, M11, M12, M22
     T g[3];
+};
+
+template <typename T, int DIM>
+struct RenormNbr {
+    vec4_t<T> a, b;
+    __device__ __forceinline__ void keep()
+    {
+        pin<DIM == 3 ? 4 : 3>(a);
+        if (DIM == 2) pin<3>(b);
+    }
 };
 
 template <typename T, int DIM>
@@ -1095,11 +1334,10 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
                                                 const int32_t* __restrict__ nbr_count,
                                                 const vec4_t<T>* __restrict__ jd0, const vec4_t<T>* __restrict__ jd1,
                                                 const T* __restrict__ rho3, const int32_t* __restrict__ psim,
-                                                const SimConst<T>* __restrict__ sims, int filter,
+                                                const SimConst<T>* __restrict__ sims,
                                                 vec4_t<T>* __restrict__ G_out, vec4_t<T>* __restrict__ L_out)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
     constexpr int NM = DIM == 2 ? 3 : 6;
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t i = t / LPP;
@@ -1112,7 +1350,6 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
     const T rhoi = (DIM == 3) ? rho3[i] : jd1[i].z;
     int n = nbr_count[i];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + i * (int64_t)width;
     RenormAcc<T, DIM> acc[NQ];
 #pragma unroll
@@ -1121,59 +1358,57 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
         for (int a = 0; a < 6; ++a) acc[q].M[a] = T(0);
         acc[q].g[0] = acc[q].g[1] = acc[q].g[2] = T(0);
     }
-    int jn[U];
-    load_entries<LPP, U>(row, r, 0, mcount, (int)i, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        vec4_t<T> a[U];
-        T rj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = ldo(jd0, (uint32_t)jn[u]);
-            rj[u] = (DIM == 3) ? a[u].w : ldo(jd1, (uint32_t)jn[u]).z;
-        }
-        load_entries<LPP, U>(row, r, m0 + U, mcount, (int)i, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (m0 + u >= mcount) continue;
+    auto gather = [&](int j, RenormNbr<T, DIM>& nb) {
+        nb.a = ldo(jd0, (uint32_t)j);
+        if (DIM == 2) nb.b = ldo(jd1, (uint32_t)j);
+    };
+    auto pairs = [&](auto image, auto walk) {
+        walk([&](int q, RenormNbr<T, DIM>& nb) {
             T d[3] = {0, 0, 0};
-            const T r2 = r2_exact<T, DIM>(ui, a[u], c.L, c.invL, d);
-            if (filter && !(r2 < c.H2)) continue;
-            const T q = fast_sqrt(r2) * c.invH;
-            const T tt = T(1) - q;
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
+            const T tt = kernel_t(r2, c.invH);
             const T t2 = tt * tt;
-            const T gF = c.kG * (T(-56.0 / 3.0) * (t2 * t2 * tt) * (T(1) + T(5) * q));
-            const T Vj = rec_volume<T, DIM>(a[u], S.m);
-            const T f = Vj * gF;
-            RenormAcc<T, DIM>& A = acc[u % NQ];
-            if (DIM == 2) {
-                A.M[0] -= f * d[0] * d[0];
-                A.M[1] -= f * d[0] * d[1];
-                A.M[2] -= f * d[1] * d[1];
-            } else {
-                A.M[0] -= f * d[0] * d[0];
-                A.M[1] -= f * d[0] * d[1];
-                A.M[2] -= f * d[0] * d[2];
-                A.M[3] -= f * d[1] * d[1];
-                A.M[4] -= f * d[1] * d[2];
-                A.M[5] -= f * d[2] * d[2];
-            }
-            const T fr = f * (rj[u] - rhoi);
+            const T rj = (DIM == 3) ? nb.a.w : nb.b.z;
+            const T f = pair_weight<T, DIM>(nb.a) * (t2 * t2) * (tt * fma(T(-5), tt, T(6)));
+            RenormAcc<T, DIM>& A = acc[q];
+            T fd[3];
 #pragma unroll
-            for (int k = 0; k < DIM; ++k) A.g[k] += fr * d[k];
-        }
-    }
+            for (int k = 0; k < DIM; ++k) fd[k] = f * d[k];
+            if (DIM == 2) {
+                A.M[0] = fma(-fd[0], d[0], A.M[0]);
+                A.M[1] = fma(-fd[0], d[1], A.M[1]);
+                A.M[2] = fma(-fd[1], d[1], A.M[2]);
+            } else {
+                A.M[0] = fma(-fd[0], d[0], A.M[0]);
+                A.M[1] = fma(-fd[0], d[1], A.M[1]);
+                A.M[2] = fma(-fd[0], d[2], A.M[2]);
+                A.M[3] = fma(-fd[1], d[1], A.M[3]);
+                A.M[4] = fma(-fd[1], d[2], A.M[4]);
+                A.M[5] = fma(-fd[2], d[2], A.M[5]);
+            }
+            const T dr = rj - rhoi;
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) A.g[k] = fma(dr, fd[k], A.g[k]);
+        });
+    };
+    auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, RenormNbr<T, DIM>>(row, width, n, r, (int)i, gather, pair); };
+    auto tail = [&](auto&& pair) { list_tail<LPP, RenormNbr<T, DIM>>(row, width, n, r, (int)i, gather, pair); };
+    if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, groups);
+    else pairs(std::true_type{}, groups);
+    pairs(std::true_type{}, tail);
+    const T scale = (DIM == 3) ? c.kGF * S.m : c.kGF;
     T M[6], g[3] = {0, 0, 0}, tmp[NQ];
 #pragma unroll
     for (int e = 0; e < NM; ++e) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].M[e];
-        M[e] = combine_leaves<LPP>(tmp);
+        M[e] = scale * combine_leaves<LPP>(tmp);
     }
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].g[k];
-        g[k] = combine_leaves<LPP>(tmp);
+        g[k] = scale * combine_leaves<LPP>(tmp);
     }
     if (r != 0) return;
     T L[6] = {0, 0, 0, 0, 0, 0}, G[3] = {0, 0, 0};
@@ -1205,34 +1440,44 @@ struct FwdAcc {
 };
 
 // Per-particle sweep record of a neighbour (jd0, jd1; G with the renormalised diffusion).
-template <typename T, int DIM>
+template <typename T, int DIM, bool RENORM>
 struct FwdNbr {
     vec4_t<T> a, b, G;
+    int j;
+    __device__ __forceinline__ void keep()
+    {
+        pin(a);
+        if (DIM == 3) pin(b);
+        else pin<3>(b);
+        if (RENORM) pin<3>(G);
+    }
 };
 
 // Forward pair terms of (i, j), added to acc:
 //   a_i    += ((alpha H c0 rho0 pi_ij - p_i) V_j - p_j V_j) gW
 //   drho_i += V_j (v_i - v_j).gW     (times rho_i later)   and   V_j (rho_i - rho_j) x_ij.gW / (r^2 + eps H^2)
 //   rho_i  += W shape (times m C_d / H^d later)
-// In 3D jd0 = (u, rho) and jd1 = (v, p), with V = m / rho recomputed as the writer computed it;
-// in 2D jd0 = (u, V, p V) and jd1 = (v, rho, p).  Two records per neighbour either way, since
-// the sweeps are bound by the vector L1's line rate, which counts gathers, not arithmetic.
-// d and r2 are the pair vector x_ij and its square.  With keep false the pair leaves acc
-// unchanged: MASK = false selects the old sums, MASK = true zeroes the kernel factors (every
-// term carries gF or W) and adds, so the neighbour's records are consumed unconditionally and
-// their loads stay ahead of the pair terms.  No implicit contraction: the products that are fused
-// are written as fma, so a pair rounds the same whichever list position and lane count it has.
-template <typename T, int DIM, bool RHOSUM, bool RENORM, bool MASK = false>
-__device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T rhoi, T pi, const FwdNbr<T, DIM>& nb,
-                                         const T* Gi, const T* d, T r2, bool keep, FwdAcc<T, DIM>& acc)
+// In 3D jd0 = (u, rho) and jd1 = (v, p): the pair weight is 1 / rho_j, and the constants m and
+// -56/3 kG of V_j gW are left to the end of the sum, which saves registers and with
+// them a wavefront in flight (262,144 particles, 8 lanes: 212 us, against 231 with V_j gW formed per
+// pair).  In 2D jd0 = (u, V, p V) and jd1 = (v, rho, p), and V_j gW is formed per pair.  Two records
+// per neighbour either way: the sweep is bound by its gathers, not by arithmetic.  d and r2 are the
+// pair vector x_ij and its square.  The particle itself (also in the places past its count) has d = 0,
+// equal velocities and densities, and adds exactly zero; a neighbour past the support has t = 0.  No
+// implicit contraction: the products that are fused are written as fma, so a pair rounds the same in
+// every copy of the loop.
+template <typename T, int DIM, bool RHOSUM, bool RENORM>
+__device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T rhoi, T pi,
+                                         const FwdNbr<T, DIM, RENORM>& nb, const T* Gi, const T* d, T r2,
+                                         int self, FwdAcc<T, DIM>& acc)
 {
 #pragma clang fp contract(off)
     T vj[3];
     T Vj, pVj, rhoj;
     if (DIM == 3) {
         rhoj = nb.a.w;
-        Vj = c.m * fast_rcp(rhoj);
-        vj[0] = nb.b.x; vj[1] = nb.b.y; vj[2] = nb.b.z; pVj = nb.b.w * Vj;
+        Vj = fast_rcp(rhoj);
+        vj[0] = nb.b.x; vj[1] = nb.b.y; vj[2] = nb.b.z; pVj = nb.b.w;
     } else {
         Vj = nb.a.z; pVj = nb.a.w;
         vj[0] = nb.b.x; vj[1] = nb.b.y; rhoj = nb.b.z;
@@ -1241,38 +1486,39 @@ __device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T r
 #pragma unroll
     for (int k = 1; k < DIM; ++k) ue = fma(vi[k] - vj[k], d[k], ue);
     const T q = fast_sqrt(r2) * c.invH;
-    const T t = T(1) - q;
+    const T t = positive_part(T(1) - q);
     const T t2 = t * t;
     const T t4 = t2 * t2;
-    const T t5 = t4 * t;
-    T gF = c.kGF * (t5 * fma(T(5), q, T(1)));  // grad W = gF x_ij
-    T wq = t4 * t2 * fma(q, fma(q, T(35.0 / 3.0), T(6)), T(1));   // W shape
-    if (MASK) {
-        const T kf = keep ? T(1) : T(0);
-        gF = gF * kf;
-        wq = wq * kf;
-    }
     const T inv = fast_rcp(r2 + c.epsH2);
     const T pij = ue * inv;
-    const T cg = fma(fma(c.cA, pij, -pi), Vj, -pVj) * gF;
-    const T rdv = fma(Vj, gF * ue, acc.rdv);
-    const T rdd = fma(Vj * (rhoi - rhoj), gF * r2 * inv, acc.rdd);
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-        const T ax = fma(cg, d[k], acc.ax[k]);
-        acc.ax[k] = (MASK || keep) ? ax : acc.ax[k];
-    }
-    acc.rdv = (MASK || keep) ? rdv : acc.rdv;
-    acc.rdd = (MASK || keep) ? rdd : acc.rdd;
-    if (RHOSUM) acc.rs = (MASK || keep) ? acc.rs + wq : acc.rs;
+    T sg = T(0);
     if (RENORM) {
         // V_j (G_i + G_j) . grad_i W_ij of the renormalised diffusion
         const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z};
-        T sg = (Gi[0] + Gj[0]) * d[0];
+        sg = (Gi[0] + Gj[0]) * d[0];
 #pragma unroll
         for (int k = 1; k < DIM; ++k) sg = fma(Gi[k] + Gj[k], d[k], sg);
-        const T rdg = fma(Vj, gF * sg, acc.rdg);
-        acc.rdg = (MASK || keep) ? rdg : acc.rdg;
+    }
+    if (DIM == 3) {
+        const T g = (Vj * t4) * (t * fma(T(-5), t, T(6)));   // 5 q + 1 = 6 - 5 t
+        const T cg = fma(c.cA, pij, -(pi + pVj)) * g;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) acc.ax[k] = fma(cg, d[k], acc.ax[k]);
+        acc.rdv = fma(g, ue, acc.rdv);
+        acc.rdd = fma((rhoi - rhoj) * (r2 * inv), g, acc.rdd);
+        if (RENORM) acc.rdg = fma(g, sg, acc.rdg);
+    } else {
+        const T gF = c.kGF * (t4 * t * fma(T(5), q, T(1)));  // grad W = gF x_ij
+        const T cg = fma(fma(c.cA, pij, -pi), Vj, -pVj) * gF;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) acc.ax[k] = fma(cg, d[k], acc.ax[k]);
+        acc.rdv = fma(Vj, gF * ue, acc.rdv);
+        acc.rdd = fma(Vj * (rhoi - rhoj), gF * r2 * inv, acc.rdd);
+        if (RENORM) acc.rdg = fma(Vj, gF * sg, acc.rdg);
+    }
+    if (RHOSUM) {
+        const T w6 = nb.j != self ? t4 * t2 : T(0);   // its own W(0) = 1 is in the sum from the start
+        acc.rs = fma(w6, fma(q, fma(q, T(35.0 / 3.0), T(6)), T(1)), acc.rs);
     }
 }
 
@@ -1285,25 +1531,21 @@ struct NextCells {
     int32_t* slot_of;
 };
 
-// The neighbour list positions of lane r among the LPP lanes of a particle are
-// k = r + LPP m (m = 0, 1, ...); position k belongs to partial sum k mod 8, which is
-// accumulator m mod (8 / LPP) of the lane.  Lanes gather the records of kPairsInFlight
-// positions before computing them, in increasing m, with the list entries of the following
-// group already in flight.
-//
-// In 3D the pairs of a group are computed without branches: a position past the lane's
-// count or rejected by the filter is computed and dropped from the sums by a select (the
-// accumulators start at +0 and never become -0, so adding nothing and skipping agree
-// bitwise), which lets the compiler interleave the independent pairs of the group.  A 3D
-// sweep keeps every SIMD busy with many wavefronts, and this takes the per-pair exec-mask
-// branches out of its instruction stream.  In 2D with 2 or 8 lanes per particle the per-pair
-// branches, which skip the tail positions that no lane of the wavefront holds, measured faster.
-// In 2D with 4 lanes the list entries are read as quad chunks (a quarter of the entry loads, the
-// vector L1's line rate being the bound) and the pairs again go without branches, dropped ones
-// masked inside fwd_pair: with a branch per pair the compiler sinks a neighbour's gathers into
-// it behind a full wait for the loads in flight.
+// LPP lanes share a particle and walk its row with sweep_list; wavefronts whose particles all lie more
+// than the support inside the box run a copy of the pair loop without the periodic image (the same
+// roundings), 6 of 45 (2D) instructions per pair less.
+// Bound: the gathers.  The texture path returns 64 bytes a clock, so a wavefront's 16-byte gather takes 16
+// clocks at the least (17.9 where quads of lanes read consecutive records, as list positions mostly
+// do); its data return is busy 93 to 100 % of a large launch, and a quarter fewer vector instructions
+// changed little by themselves.  Small launches are bound by a wavefront's own chain.  Measured, before
+// (a load per list entry, a test of every position against the count and of every pair against the
+// support) and now: 2D 32^2 FP64 13.5 and 9.0 us, 2D 101^2 8.2 and 7.4, 2D 256^2 15.0 and 13.9, 3D 47^3
+// 86.5 and 83.0, 3D 64^3 222 and 214, 3D 20^3 FP64 27.3 and 21, 512-simulation batch 335 and 325.
+// Copying a workgroup's reach to LDS first (10 to 12 clocks a gather) took twice as long: the copy's 39 to 58
+// KB leave too few wavefronts per CU.
 template <typename T, int DIM, int MODE, int LPP, bool RENORM>
-__global__ __launch_bounds__(256) void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
+__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>))
+void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                const int32_t* __restrict__ nbr_count,
                                                const vec4_t<T>* __restrict__ jd0, const vec4_t<T>* __restrict__ jd1,
                                                StatePtrs<T, DIM> cur, StatePtrs<T, DIM> dst,
@@ -1311,27 +1553,31 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t N, int32_t width, const i
                                                T* __restrict__ acc_out, T* __restrict__ rhosum_out,
                                                const int32_t* __restrict__ psim,
                                                const SimConst<T>* __restrict__ sims, int32_t* __restrict__ status,
-                                               NextCells next, NextSlot<T> ns, int filter,
+                                               NextCells next, NextSlot<T> ns,
                                                unsigned long long* __restrict__ pair_counter,
                                                const vec4_t<T>* __restrict__ jdG)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
-    static_assert(LPP >= 2 && LPP <= 8 && U % NQ == 0, "lanes per particle must be 2, 4 or 8");
+    static_assert(LPP == 2 || LPP == 4 || LPP == 8, "lanes per particle must be 2, 4 or 8");
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t i = t / LPP;
     const int r = (int)(t - i * LPP);
-    int accepted = 0;  // entries kept by the filter (lists with a skin), less the self entry
+    int accepted = 0;  // listed pairs with r < H (lists with a skin)
     if (i < N) {
-    const int s = psim[i];
-    const SimConst<T>& S = sims[s];
-    const PairConst<T> c = pair_const(S);
-    T ui[3] = {0, 0, 0}, vi[3] = {0, 0, 0};
-    unpack_u<T, DIM>(jd0[i], ui);
+    const int s = sim_of(psim, i);
+    FwdAcc<T, DIM> acc[NQ];
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) vi[k] = cur.v[k][i];
-    const T rhoi = cur.rho[i];
-    const T pi = tait(S, rhoi);
+    for (int q = 0; q < NQ; ++q) {
+        acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
+        acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
+    }
+    const PairConst<T> c = pair_const_of(sims, s);
+    const vec4_t<T> ra = jd0[i], rb = jd1[i];
+    T ui[3] = {0, 0, 0};
+    unpack_u<T, DIM>(ra, ui);
+    const T vi[3] = {rb.x, rb.y, (DIM == 3) ? rb.z : T(0)};
+    const T rhoi = (DIM == 3) ? ra.w : rb.z;
+    const T pi = rb.w;
     T Gi[3] = {0, 0, 0};
     if (RENORM) {
         const vec4_t<T> g = jdG[i];
@@ -1341,63 +1587,32 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t N, int32_t width, const i
     }
     int n = nbr_count[i];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + i * (int64_t)width;
-    // every list holds its particle once, at r2 = 0, which the filter keeps
-    if (r == 0 && n > 0) accepted = -1;
-    FwdAcc<T, DIM> acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
-        acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
-    }
-    constexpr bool kSelect = DIM == 3;
-    // four lanes per particle: list entries as 16-byte chunks and a quad transpose (one load
-    // per lane and group of four positions instead of four), and no branch per position (the
-    // positions past the count read the particle itself and are masked like dropped pairs), so
-    // that no neighbour's gathers are sunk behind the pair terms of an earlier one
-    constexpr bool kQuad = LPP == 4 && U == 4 && !kSelect;
-    int jn[U];
-    int4 chunk = make_int4(0, 0, 0, 0);
-    if (kQuad) chunk = load_chunk4(row, width, 4 * r);
-    else if (kSelect) load_entries_clamped<LPP, U>(row, width, r, 0, mcount, (int)i, jn);
-    else load_entries<LPP, U>(row, r, 0, mcount, (int)i, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        if (kQuad) {
-            int t4[4];
-            quad_transpose(r, chunk, t4);
-#pragma unroll
-            for (int u = 0; u < U; ++u) jn[u] = (m0 + u < mcount) ? t4[u] : (int)i;
-        }
-        int jj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) jj[u] = jn[u];
-        FwdNbr<T, DIM> nb[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t j = (uint32_t)jj[u];
-            nb[u].a = ldo(jd0, j);
-            nb[u].b = ldo(jd1, j);
-            if (RENORM) nb[u].G = ldo(jdG, j);
-        }
-        if (kQuad) chunk = load_chunk4(row, width, 4 * (m0 + U) + 4 * r);
-        else if (kSelect) load_entries_clamped<LPP, U>(row, width, r, m0 + U, mcount, (int)i, jn);
-        else load_entries<LPP, U>(row, r, m0 + U, mcount, (int)i, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!kQuad && !kSelect && m0 + u >= mcount) continue;
+    // the particle's own entry and the places past the count, at r2 = 0, are counted by the loop
+    if (r == 0 && n > 0) accepted = n - positions_visited<T, LPP>(n, width) - 1;
+    // W(0) = 1 of the particle itself
+    if (MODE == kModeRhs && r == 0 && n > 0) acc[0].rs = T(1);
+    using Nbr = FwdNbr<T, DIM, RENORM>;
+    auto gather = [&](int j, Nbr& nb) {
+        nb.j = j;
+        nb.a = ldo(jd0, (uint32_t)j);
+        nb.b = ldo(jd1, (uint32_t)j);
+        if (RENORM) nb.G = ldo(jdG, (uint32_t)j);
+    };
+    auto pairs = [&](auto image, auto walk) {
+        walk([&](int q, Nbr& nb) {
             T d[3];
-            const T r2 = r2_exact<T, DIM>(ui, nb[u].a, c.L, c.invL, d);
-            const bool keep = (m0 + u < mcount) && (!filter || r2 < c.H2);
-            if (!kQuad && !kSelect && !keep) continue;
-            accepted += keep ? 1 : 0;
-            if (kQuad)
-                fwd_pair<T, DIM, MODE == kModeRhs, RENORM, true>(c, vi, rhoi, pi, nb[u], Gi, d, r2, keep, acc[u % NQ]);
-            else
-                fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, vi, rhoi, pi, nb[u], Gi, d, r2, keep, acc[u % NQ]);
-        }
-    }
-    T ax[3] = {0, 0, 0};
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
+            accepted += r2 < c.H2 ? 1 : 0;
+            fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, vi, rhoi, pi, nb, Gi, d, r2, (int)i, acc[q]);
+        });
+    };
+    auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
+    auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
+    if (wave_inside<T, DIM>(ui, c.H, c.L)) pairs(std::false_type{}, groups);
+    else pairs(std::true_type{}, groups);
+    pairs(std::true_type{}, tail);
+    T ax[3] = {0, 0, 0}, rs = 0, rdg = 0;
     T tmp[NQ];
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
@@ -1407,23 +1622,31 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t N, int32_t width, const i
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdv;
-    const T rdv = combine_leaves<LPP>(tmp);
+    T rdv = combine_leaves<LPP>(tmp);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdd;
-    const T rdd = combine_leaves<LPP>(tmp);
-    T rs = 0;
+    T rdd = combine_leaves<LPP>(tmp);
     if (MODE == kModeRhs) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rs;
         rs = combine_leaves<LPP>(tmp);
     }
-    T rdg = 0;
     if (RENORM) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdg;
         rdg = combine_leaves<LPP>(tmp);
     }
     if (r == 0) {
+    const SimConst<T>& S = sims[s];
+    if (DIM == 3) {
+        // the constants that the 3D pair terms leave out (V_j gW = scale g)
+        const T scale = S.kG * T(-56.0 / 3.0) * S.m;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) ax[k] = scale * ax[k];
+        rdv = scale * rdv;
+        rdd = scale * rdd;
+        rdg = scale * rdg;
+    }
     const T invrho = fast_rcp(rhoi);
     T a[3];
 #pragma unroll
@@ -1518,18 +1741,27 @@ __global__ __launch_bounds__(256) void k_gather_sorted(int64_t N, const T* __res
     if (q < N) out[q] = in[orig[q]];
 }
 
+template <typename T>
+struct DensNbr {
+    vec4_t<T> a;
+    T g;
+    __device__ __forceinline__ void keep()
+    {
+        pin(a);
+        asm volatile("" : "+v"(g));
+    }
+};
+
 template <typename T, int DIM, int LPP>
 __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                      const int32_t* __restrict__ nbr_count,
                                                      const vec4_t<T>* __restrict__ jd0, const T* __restrict__ gs,
                                                      const int32_t* __restrict__ orig,
                                                      const int32_t* __restrict__ psim,
-                                                     const SimConst<T>* __restrict__ sims, T* __restrict__ xbar,
-                                                     int filter)
+                                                     const SimConst<T>* __restrict__ sims, T* __restrict__ xbar)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
-    static_assert(LPP >= 2 && LPP <= 8 && U % NQ == 0, "lanes per particle must be 2, 4 or 8");
+    static_assert(LPP == 2 || LPP == 4 || LPP == 8, "lanes per particle must be 2, 4 or 8");
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t i = t / LPP;
     const int r = (int)(t - i * LPP);
@@ -1541,38 +1773,30 @@ __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, c
     const T gi = gs[i];
     int n = nbr_count[i];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + i * (int64_t)width;
     T acc[NQ][3];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
-    int jn[U];
-    load_entries<LPP, U>(row, r, 0, mcount, (int)i, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        vec4_t<T> a[U];
-        T gj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = ldo(jd0, (uint32_t)jn[u]);
-            gj[u] = ldo(gs, (uint32_t)jn[u]);
-        }
-        load_entries<LPP, U>(row, r, m0 + U, mcount, (int)i, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (m0 + u >= mcount) continue;
+    auto gather = [&](int j, DensNbr<T>& nb) {
+        nb.a = ldo(jd0, (uint32_t)j);
+        nb.g = ldo(gs, (uint32_t)j);
+    };
+    auto pairs = [&](auto image, auto walk) {
+        walk([&](int q, DensNbr<T>& nb) {
             T d[3] = {0, 0, 0};
-            const T r2 = r2_exact<T, DIM>(ui, a[u], c.L, c.invL, d);
-            if (filter && !(r2 < c.H2)) continue;
-            const T q = fast_sqrt(r2) * c.invH;
-            const T tt = T(1) - q;
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
+            const T tt = kernel_t(r2, c.invH);
             const T t2 = tt * tt;
-            const T t5 = t2 * t2 * tt;
-            const T gF = c.kGF * (t5 * (T(1) + T(5) * q));
-            const T w = (gi + gj[u]) * gF;
+            const T w = (gi + nb.g) * ((t2 * t2) * (tt * fma(T(-5), tt, T(6))));
 #pragma unroll
-            for (int k = 0; k < DIM; ++k) acc[u % NQ][k] += w * d[k];
-        }
-    }
+            for (int k = 0; k < DIM; ++k) acc[q][k] = fma(w, d[k], acc[q][k]);
+        });
+    };
+    auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, DensNbr<T>>(row, width, n, r, (int)i, gather, pair); };
+    auto tail = [&](auto&& pair) { list_tail<LPP, DensNbr<T>>(row, width, n, r, (int)i, gather, pair); };
+    if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, groups);
+    else pairs(std::true_type{}, groups);
+    pairs(std::true_type{}, tail);
     T out[3] = {0, 0, 0};
     T tmp[NQ];
 #pragma unroll
@@ -1584,7 +1808,7 @@ __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, c
     if (r != 0) return;
     const int o = orig[i];
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) xbar[(int64_t)k * N + o] = S.m * out[k];
+    for (int k = 0; k < DIM; ++k) xbar[(int64_t)k * N + o] = (S.m * c.kGF) * out[k];
 }
 
 // ---------------------------------------------------------------- explicit Runge-Kutta stages
@@ -1742,14 +1966,24 @@ __global__ __launch_bounds__(256) void k_unsort(int64_t N, StatePtrs<T, DIM> src
 
 // ---------------------------------------------------------------- adjoint
 
-// Gathers the output cotangents into sorted order: jdA = (abar / rho, rbar) with
-// vt = v'_bar + dt x'_bar, abar = dt vt, rbar = dt rho'_bar; jdB = (rho, p, rbar rho, dp/drho).
-// The acceleration cotangent enters every pair term divided by its particle's density, so the
-// record holds it divided once.
+// Gathers the output cotangents into sorted order, with vt = v'_bar + dt x'_bar, abar = dt vt,
+// rbar = dt rho'_bar: (abar, rbar rho) in 3D, (abar, rbar rho, rbar rho^2) in 2D.
+template <typename T, int DIM>
+__device__ __forceinline__ vec4_t<T> adjoint_record(const T* ab, T rb, T rho)
+{
+    const T rbr = rb * rho;
+    vec4_t<T> a;
+    a.x = ab[0];
+    a.y = ab[1];
+    a.z = (DIM == 3) ? ab[2] : rbr;
+    a.w = (DIM == 3) ? rbr : rbr * rho;
+    return a;
+}
+
 template <typename T, int DIM>
 __global__ __launch_bounds__(256) void k_adj_prologue(int64_t N, const int32_t* __restrict__ orig,
                                                       StatePtrs<T, DIM> cot, StatePtrs<T, DIM> cur,
-                                                      vec4_t<T>* __restrict__ jdA, vec4_t<T>* __restrict__ jdB,
+                                                      vec4_t<T>* __restrict__ jdA,
                                                       const int32_t* __restrict__ psim,
                                                       const SimConst<T>* __restrict__ sims, int vjp)
 {
@@ -1770,204 +2004,185 @@ __global__ __launch_bounds__(256) void k_adj_prologue(int64_t N, const int32_t* 
         for (int k = 0; k < DIM; ++k) ab[k] = S.dt * (cot.v[k][o] + S.dt * cot.x[k][o]);
         rb = S.dt * cot.rho[o];
     }
-    const T rho = cur.rho[q];
-    const T ir = fast_rcp(rho);
-    vec4_t<T> a;
-    if (DIM == 3) {
-        a.x = ab[0] * ir; a.y = ab[1] * ir; a.z = ab[2] * ir; a.w = rb;
-    } else {
-        a.x = ab[0] * ir; a.y = ab[1] * ir; a.z = rb; a.w = rb * rho;
-    }
-    jdA[q] = a;
-    vec4_t<T> b;
-    b.x = rho;
-    b.y = tait(S, rho);
-    b.z = rb * rho;
-    b.w = tait_slope(S, rho);
-    jdB[q] = b;
+    jdA[q] = adjoint_record<T, DIM>(ab, rb, cur.rho[q]);
 }
 
+// Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
+// (cin_sorted, cout_sorted): contiguous accesses, where the caller's order scatters them.
 // What the adjoint sweep of step t prepares for the adjoint of step t - 1 when both states share
 // the particle order (a step within one list-reuse interval): the prologue records of step t - 1
 // at the same sorted index, from the cotangents the sweep has just formed (null jdA: none).
 template <typename T>
 struct NextAdj {
     vec4_t<T>* jdA;
-    vec4_t<T>* jdB;
     const T* rho;   // densities of state t - 1, sorted order
 };
 
 template <typename T, int DIM>
 struct AdjAcc {
     T gx[3], gv[3];
-    T gr;
+    T s1, s2;  // the density cotangent is -dp/drho s1 - s2 / rho
     T Gb[3];   // cotangent of the renormalised density gradient
 };
 
-// Per-particle adjoint record of a neighbour: jd0 = (u, rho), jd1 = (v, p), jdA = (abar / rho, rbar)
-// in 3D; jd0 = (u, V, p V), jd1 = (v, rho, p), jdA = (abar / rho, rbar, rbar rho) in 2D.  They
-// hold everything a neighbour contributes (3D: V = m / rho and rbar rho recomputed), so the
-// sweep gathers three records per neighbour; jdB = (rho, p, rbar rho, dp/drho) is read for the
-// particle itself only.
-template <typename T>
+// Per-particle adjoint record of a neighbour: jd0 = (u, rho), jd1 = (v, p), jdA = (abar, rbar rho) in
+// 3D; jd0 = (u, V, p V), jd1 = (v, rho, p), jdA = (abar, rbar rho, rbar rho^2) in 2D.  They hold
+// everything a neighbour contributes: three records per neighbour, and no others for the particle.
+template <typename T, int DIM, bool RENORM>
 struct AdjNbr {
     vec4_t<T> a, b, A, G;
+    __device__ __forceinline__ void keep()
+    {
+        pin<DIM == 3 ? 4 : 3>(a);
+        pin(b);
+        pin(A);
+        if (RENORM) pin<3>(G);
+    }
 };
 
 // Adjoint pair terms, gather form.  For particle k and a neighbour j != k: the partial
 // derivatives, with respect to k's position, velocity and density, of the two directed pair
 // terms (k,j) and (j,k) contracted with their particles' cotangents (abar, rbar).  With
-// e = x_kj, G = gF e, the kernel Hessian Jg = gF I + hF e e^T, pi = (v_k - v_j).e / (r^2+eps H^2),
-// s = e.G / (r^2+eps H^2), these partials reduce to the closed forms below.  The self pair
-// contributes exactly zero.  The momentum term's factor 1/rho_k and 1/rho_j always multiplies
-// the acceleration cotangent of the same particle, so both sides take abar / rho from their
-// records (ak, aj here), and X = cA pi - p_k - p_j is the pressure-and-viscosity factor that
-// Q_k = X / rho_k and Q_j = X / rho_j share.
+// e = x_kj, u = v_kj, the kernel gradient gF e and Hessian Jg = gF I + hF e e^T, inv = 1/(r^2+eps H^2),
+// pi = (u.e) inv, s = gF r^2 inv, sigma = inv (2 gF + hF r^2 - 2 s), X = cA pi - p_k - p_j, and the
+// symmetric weight Phi = V_k V_j / m = m / (rho_k rho_j), every partial has the factor Phi, because
+// V_j / rho_k = V_k / rho_j = Phi.  With da = abar_k - abar_j, Q = rbar rho, R = rbar rho^2:
+//   B    = cA inv gF (da.e)
+//   xbar = Phi [ (B + gF (R_k + R_j)) u + gF X da
+//                + (hF (X (da.e) + (R_k + R_j)(u.e)) - 2 pi B + cD sigma (rho_k - rho_j)(Q_k - Q_j)) e ]
+//   vbar = Phi (B + gF (R_k + R_j)) e
+//   rbar = Phi [ -gF (da.e) (p'_k + X / rho_k) + (gF u.e + cD s)(R_k - R_j) / rho_k ]
+// The differences da, u, e, R_k - R_j vanish exactly for the particle itself, whose pair (also in
+// the places past its count) therefore adds exactly zero.  V_j is a factor of gF and hF here (1 / rho_j
+// in 3D); the particle's own factor of Phi and the constant kGF are applied at the end.
 //
 // With RENORM, the renormalised diffusion T_i = c sum_j V_j (G_i + G_j) . grad_i W_ij
-// (c = -delta H c0) adds, for q = rbar_k V_j - rbar_j V_k and s = G_k + G_j with the
-// gradients held fixed: gx += c q Jg s, Gbar += c q gF e, gr += (V_k / rho_k) c rbar_j gF s.e.
+// (c = -delta H c0) adds, with the gradients held fixed and s = G_k + G_j: xbar += Phi c (Q_k - Q_j) Jg s,
+// Gbar += Phi c (Q_k - Q_j) gF e, rbar += Phi c Q_j gF s.e / rho_k.
+//
+// Bound: the gathers, as in k_sweep, three records per neighbour.  Dropping the second adjoint record
+// (u and the density are in jd0 and jd1), the common factor Phi (62 vector instructions per pair, 80 before) and
+// the walk of the rows: 2D 101^2 9.4 and 9.0 us, 2D 256^2 18.4 and 17.3, 3D 47^3 140 and 125, 3D 64^3 318 and
+// 317, 3D 20^3 FP64 25.9 and 22.3, 512-simulation batch 439 and 406; with renormalisation, the second pass
+// (k_renorm_adj, 3D 32^3) 42.8 and 25.1.
 template <typename T>
 struct AdjSelf {
-    T v[3], a[3];   // velocity, abar / rho
-    T rb, V, rho, p, ir, dp;
-    T rbr;          // rbar rho
-    T Vir;          // V / rho
+    T v[3], a[3];   // velocity, abar
+    T rho, p, Q, R;
     T G[3];
 };
 
 template <typename T, int DIM, bool RENORM>
-__device__ __forceinline__ void adj_pair(const PairConst<T>& c, const AdjSelf<T>& K, const AdjNbr<T>& nb,
-                                         const T* e, T r2, bool keep, AdjAcc<T, DIM>& acc)
+__device__ __forceinline__ void adj_pair(const PairConst<T>& c, const AdjSelf<T>& K, const AdjNbr<T, DIM, RENORM>& nb,
+                                         const T* e, T r2, AdjAcc<T, DIM>& acc)
 {
-    T vj[3], aj[3];
-    T Vj, rbj;
-    if (DIM == 3) {
-        Vj = c.m * fast_rcp(nb.a.w);
-        vj[0] = nb.b.x; vj[1] = nb.b.y; vj[2] = nb.b.z;
-        aj[0] = nb.A.x; aj[1] = nb.A.y; aj[2] = nb.A.z; rbj = nb.A.w;
-    } else {
-        Vj = nb.a.z;
-        vj[0] = nb.b.x; vj[1] = nb.b.y;
-        aj[0] = nb.A.x; aj[1] = nb.A.y; rbj = nb.A.z;
-    }
+#pragma clang fp contract(off)
+    const T Vj = pair_weight<T, DIM>(nb.a);
     const T rhoj = (DIM == 3) ? nb.a.w : nb.b.z;
     const T pj = nb.b.w;
-    const T rbrj = (DIM == 3) ? rbj * rhoj : nb.A.w;
-    const T cA = c.cA, cD = c.cD;
-    const T Vk = K.V, rbk = K.rb, rhok = K.rho;
-    T u[3];
-    T ue = 0, ake = 0, aje = 0;
+    const T Qj = (DIM == 3) ? nb.A.w : nb.A.z;
+    const T Rj = (DIM == 3) ? Qj * rhoj : nb.A.w;
+    const T vj[3] = {nb.b.x, nb.b.y, nb.b.z}, aj[3] = {nb.A.x, nb.A.y, nb.A.z};
+    T u[3], da[3];
+    u[0] = K.v[0] - vj[0];
+    da[0] = K.a[0] - aj[0];
+    T ue = u[0] * e[0], de = da[0] * e[0];
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
+    for (int k = 1; k < DIM; ++k) {
         u[k] = K.v[k] - vj[k];
-        ue += u[k] * e[k];
-        ake += K.a[k] * e[k];
-        aje += aj[k] * e[k];
+        da[k] = K.a[k] - aj[k];
+        ue = fma(u[k], e[k], ue);
+        de = fma(da[k], e[k], de);
     }
-    const T q = fast_sqrt(r2) * c.invH;
-    const T t = T(1) - q;
+    const T t = kernel_t(r2, c.invH);
     const T t2 = t * t;
-    const T t4 = t2 * t2;
-    const T gF = c.kGF * (t4 * t * (T(1) + T(5) * q));  // grad W = gF e
-    const T hF = c.kH * t4;                                              // Hessian: gF I + hF e e^T
+    const T vt4 = Vj * (t2 * t2);
+    const T g = vt4 * (t * fma(T(-5), t, T(6)));
+    const T h = c.hc * vt4;
     const T inv = fast_rcp(r2 + c.epsH2);
     const T pij = ue * inv;
-    const T sij = gF * r2 * inv;
-    const T sig = inv * (T(2) * gF + hF * r2 - T(2) * sij);              // d s / d e = sig e
-    const T aGk = gF * ake, aGj = gF * aje, uG = gF * ue;
-    const T X = cA * pij - (K.p + pj);
-    const T beta = cA * inv * (Vj * aGk - Vk * aGj);
-    const T gam = Vj * K.rbr + Vk * rbrj;
-    const T drho = rhok - rhoj;
-    const T cdr = cD * sig * drho * (Vj * rbk - Vk * rbj);
-    T w[3];
-    T ew = 0;
+    const T s = g * (r2 * inv);
+    const T sig = inv * fma(T(2), g - s, h * r2);   // d s / d e = sig e
+    const T X = fma(c.cA, pij, -(K.p + pj));
+    const T Rs = K.R + Rj, Rd = K.R - Rj, Qd = K.Q - Qj;
+    const T gde = g * de;
+    const T B = (c.cA * inv) * gde;
+    const T cu = fma(g, Rs, B);
+    const T gX = g * X;
+    const T ew = fma(X, de, Rs * ue);
+    const T ce = fma(h, ew, fma(T(-2) * B, pij, sig * ((c.cD * (K.rho - rhoj)) * Qd)));
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
-        w[k] = X * (Vj * K.a[k] - Vk * aj[k]) + gam * u[k];
-        ew += e[k] * w[k];
+        acc.gx[k] = fma(cu, u[k], fma(gX, da[k], fma(ce, e[k], acc.gx[k])));
+        acc.gv[k] = fma(cu, e[k], acc.gv[k]);
     }
-    const T ce = cdr - T(2) * beta * pij + hF * ew;  // coefficient of e in the position cotangent
-    const T bg = beta + gam * gF;
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-        acc.gx[k] = keep ? fma(gF, w[k], fma(ce, e[k], fma(beta, u[k], acc.gx[k]))) : acc.gx[k];
-        acc.gv[k] = keep ? fma(bg, e[k], acc.gv[k]) : acc.gv[k];
-    }
-    // density cotangent: the (k,j) and (j,k) terms' density partials; the (j,k) momentum term
-    // enters through 1/rho_k as -(V_k / rho_k) P
-    const T cds = cD * sij;
-    const T rbjc = rbj * cds;
-    const T P = rbrj * uG - X * aGj - drho * rbjc;
-    const T dgr = Vj * (aGk * -(K.dp + X * K.ir) + rbk * (uG + cds)) - K.Vir * P + Vk * (aGj * K.dp - rbjc);
-    acc.gr = keep ? acc.gr + dgr : acc.gr;
+    acc.s1 = acc.s1 + gde;
+    acc.s2 = fma(gde, X, fma(-fma(c.cD, s, g * ue), Rd, acc.s2));
     if (RENORM) {
-        const T cr = T(-0.5) * cD;
+        const T cr = T(-0.5) * c.cD;
         const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z};
         T sv[3], es = T(0);
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
             sv[k] = K.G[k] + Gj[k];
-            es += e[k] * sv[k];
+            es = fma(e[k], sv[k], es);
         }
-        const T qq = cr * (rbk * Vj - rbj * Vk);
+        const T qq = cr * Qd, gq = g * qq, hq = (h * qq) * es;
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
-            acc.gx[k] = keep ? acc.gx[k] + qq * (gF * sv[k] + hF * es * e[k]) : acc.gx[k];
-            acc.Gb[k] = keep ? acc.Gb[k] + qq * gF * e[k] : acc.Gb[k];
+            acc.gx[k] = fma(gq, sv[k], fma(hq, e[k], acc.gx[k]));
+            acc.Gb[k] = fma(gq, e[k], acc.Gb[k]);
         }
-        acc.gr = keep ? acc.gr + Vk * K.ir * cr * rbj * gF * es : acc.gr;
+        acc.s2 = fma(-(cr * Qj), g * es, acc.s2);
     }
 }
 
+// Wavefronts per SIMD the adjoint sweep's registers are held to: in FP32 2D five (96 registers instead of
+// 113: the 512-simulation batch 399 us a launch against 463).  In 3D the same limit spills.
+template <typename T, int DIM>
+constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 ? 5 : 1;
+
 template <typename T, int DIM, int LPP, bool RENORM>
-__global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
+__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM>))
+void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                    const int32_t* __restrict__ nbr_count,
                                                    const vec4_t<T>* __restrict__ jd0,
                                                    const vec4_t<T>* __restrict__ jd1,
                                                    const vec4_t<T>* __restrict__ jdA,
-                                                   const vec4_t<T>* __restrict__ jdB,
-                                                   const int32_t* __restrict__ orig, StatePtrs<T, DIM> cot,
+                                                   const int32_t* __restrict__ orig, StatePtrs<T, DIM> cin,
+                                                   int cin_sorted, StatePtrs<T, DIM> cout, int cout_sorted,
                                                    const int32_t* __restrict__ psim,
                                                    const SimConst<T>* __restrict__ sims, int32_t* __restrict__ status,
-                                                   int filter, int vjp, const vec4_t<T>* __restrict__ jdG,
+                                                   int vjp, const vec4_t<T>* __restrict__ jdG,
                                                    const vec4_t<T>* __restrict__ jdL, vec4_t<T>* __restrict__ gbar,
                                                    NextAdj<T> na)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
-    static_assert(LPP >= 2 && LPP <= 8 && U % NQ == 0, "lanes per particle must be 2, 4 or 8");
+    static_assert(LPP == 2 || LPP == 4 || LPP == 8, "lanes per particle must be 2, 4 or 8");
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t k = t / LPP;
     const int r = (int)(t - k * LPP);
     if (k >= N) return;
-    const int s = psim[k];
-    const SimConst<T>& S = sims[s];
-    const PairConst<T> c = pair_const(S);
+    const int s = sim_of(psim, k);
+    AdjAcc<T, DIM> acc[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) acc[q].gx[d] = acc[q].gv[d] = acc[q].Gb[d] = T(0);
+        acc[q].s1 = acc[q].s2 = T(0);
+    }
+    const PairConst<T> c = pair_const_of(sims, s);
     T uk[3] = {0, 0, 0};
     AdjSelf<T> K;
     {
         const vec4_t<T> a = jd0[k], b = jd1[k], A = jdA[k];
-        K.v[2] = K.a[2] = T(0);
-        if (DIM == 3) {
-            uk[0] = a.x; uk[1] = a.y; uk[2] = a.z; K.V = S.m * fast_rcp(a.w);
-            K.v[0] = b.x; K.v[1] = b.y; K.v[2] = b.z;
-            K.a[0] = A.x; K.a[1] = A.y; K.a[2] = A.z; K.rb = A.w;
-        } else {
-            uk[0] = a.x; uk[1] = a.y; K.V = a.z;
-            K.v[0] = b.x; K.v[1] = b.y;
-            K.a[0] = A.x; K.a[1] = A.y; K.rb = A.z;
-        }
-    }
-    {
-        const vec4_t<T> Bk = jdB[k];
-        K.rho = Bk.x;
-        K.p = Bk.y;
-        K.rbr = Bk.z;
-        K.dp = Bk.w;
-        K.ir = fast_rcp(K.rho);
-        K.Vir = K.V * K.ir;
+        unpack_u<T, DIM>(a, uk);
+        K.v[0] = b.x; K.v[1] = b.y; K.v[2] = (DIM == 3) ? b.z : T(0);
+        K.a[0] = A.x; K.a[1] = A.y; K.a[2] = (DIM == 3) ? A.z : T(0);
+        K.rho = (DIM == 3) ? a.w : b.z;
+        K.p = b.w;
+        K.Q = (DIM == 3) ? A.w : A.z;
+        K.R = (DIM == 3) ? A.w * a.w : A.w;
     }
     K.G[0] = K.G[1] = K.G[2] = T(0);
     if (RENORM) {
@@ -1978,51 +2193,30 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
     }
     int n = nbr_count[k];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + k * (int64_t)width;
-    AdjAcc<T, DIM> acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) acc[q].gx[d] = acc[q].gv[d] = acc[q].Gb[d] = T(0);
-        acc[q].gr = T(0);
-    }
-    int jn[U];
-    int4 chunk = make_int4(0, 0, 0, 0);
-    constexpr bool kQuad = LPP == 4 && U == 4;
-    if (kQuad) chunk = load_chunk4(row, width, 4 * r);
-    else load_entries<LPP, U>(row, r, 0, mcount, (int)k, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        if (kQuad) {
-            int t4[4];
-            quad_transpose(r, chunk, t4);
-#pragma unroll
-            for (int u = 0; u < U; ++u) jn[u] = (m0 + u < mcount) ? t4[u] : (int)k;
-        }
-        AdjNbr<T> nb[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t j = (uint32_t)jn[u];
-            nb[u].a = ldo(jd0, j);
-            nb[u].b = ldo(jd1, j);
-            nb[u].A = ldo(jdA, j);
-            if (RENORM) nb[u].G = ldo(jdG, j);
-        }
-        if (kQuad) chunk = load_chunk4(row, width, 4 * (m0 + U) + 4 * r);
-        else load_entries<LPP, U>(row, r, m0 + U, mcount, (int)k, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // position m0 is below the count inside the loop; its pair is dropped by a select
-            // rather than a branch, which keeps its gathers ahead of the pair terms
-            if (u > 0 && m0 + u >= mcount) continue;
+    using Nbr = AdjNbr<T, DIM, RENORM>;
+    auto gather = [&](int j, Nbr& nb) {
+        nb.a = ldo(jd0, (uint32_t)j);
+        nb.b = ldo(jd1, (uint32_t)j);
+        nb.A = ldo(jdA, (uint32_t)j);
+        if (RENORM) nb.G = ldo(jdG, (uint32_t)j);
+    };
+    auto pairs = [&](auto image, auto walk) {
+        walk([&](int q, Nbr& nb) {
             T e[3];
-            const T r2 = r2_exact<T, DIM>(uk, nb[u].a, c.L, c.invL, e);
-            const bool keep = !filter || r2 < c.H2;
-            if (u > 0 && !keep) continue;
-            adj_pair<T, DIM, RENORM>(c, K, nb[u], e, r2, keep, acc[u % NQ]);
-        }
-    }
-    T gx[3] = {0, 0, 0}, gv[3] = {0, 0, 0};
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(uk, nb.a, c.L, c.invL, e);
+            adj_pair<T, DIM, RENORM>(c, K, nb, e, r2, acc[q]);
+        });
+    };
+    // four records per neighbour with RENORM: two pairs at a time, or the registers leave too few wavefronts
+    auto groups = [&](auto&& pair) {
+        sweep_list<(sizeof(T) == 8 || RENORM), LPP, Nbr>(row, width, n, r, (int)k, gather, pair);
+    };
+    auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
+    if (wave_inside<T, DIM>(uk, c.H, c.L)) pairs(std::false_type{}, groups);
+    else pairs(std::true_type{}, groups);
+    pairs(std::true_type{}, tail);
+    T gx[3] = {0, 0, 0}, gv[3] = {0, 0, 0}, Gb[3] = {0, 0, 0};
     T tmp[NQ];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
@@ -2032,20 +2226,33 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gv[d];
         gv[d] = combine_leaves<LPP>(tmp);
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gr;
-    const T gr = combine_leaves<LPP>(tmp);
-    T Gb[3] = {0, 0, 0};
-    if (RENORM) {
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
+        if (RENORM) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].Gb[d];
             Gb[d] = combine_leaves<LPP>(tmp);
         }
     }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s1;
+    const T s1 = combine_leaves<LPP>(tmp);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s2;
+    const T s2 = combine_leaves<LPP>(tmp);
     if (r != 0) return;
+    const SimConst<T>& S = sims[s];
+    // the particle's factor of Phi = m / (rho_k rho_j) and the kernel constant (the neighbour's factor
+    // is V_j in 2D, 1 / rho_j in 3D)
+    const T rhok = K.rho;
+    const T ir = fast_rcp(rhok);
+    const T kGF = S.kG * T(-56.0 / 3.0);
+    const T scale = (DIM == 3) ? kGF * (S.m * ir) : kGF * ir;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        gx[d] = scale * gx[d];
+        gv[d] = scale * gv[d];
+        Gb[d] = scale * Gb[d];
+    }
+    const T gr = -scale * fma(tait_slope(S, rhok), s1, ir * s2);
     if (RENORM) {
         // gbar_k = L_k^T Gbar_k (L symmetric), for the second renormalisation pass
         T L[6] = {0, 0, 0, 0, 0, 0};
@@ -2065,14 +2272,15 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
         o4.w = T(0);
         gbar[k] = o4;
     }
-    const int o = orig[k];
     const T dt = S.dt;
+    const int64_t o = (cin_sorted && cout_sorted) ? k : (int64_t)orig[k];
+    const int64_t ci = cin_sorted ? k : o, co = cout_sorted ? k : o;
     bool bad = !isfinite(gr);
     T xn[3] = {0, 0, 0}, vn[3] = {0, 0, 0};
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-        const T xb = cot.x[d][o];
-        const T vb = cot.v[d][o];
+        const T xb = cin.x[d][ci];
+        const T vb = cin.v[d][ci];
         if (vjp) {
             // (xbar, vbar, rhobar) = (J_x^T, kx + J_v^T, J_rho^T): dx/dt = v adds kx to vbar
             xn[d] = gx[d];
@@ -2081,12 +2289,12 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
             xn[d] = xb + gx[d];
             vn[d] = vb + dt * xb + gv[d];
         }
-        cot.x[d][o] = xn[d];
-        cot.v[d][o] = vn[d];
+        cout.x[d][co] = xn[d];
+        cout.v[d][co] = vn[d];
         bad = bad || !isfinite(gx[d]) || !isfinite(gv[d]);
     }
-    const T rn = vjp ? gr : cot.rho[o] + gr;
-    cot.rho[o] = rn;
+    const T rn = vjp ? gr : cin.rho[ci] + gr;
+    cout.rho[co] = rn;
     if (bad) atomicOr(&status[s], kFlagNonfinite);
     if (na.jdA) {
         // the prologue of the previous step's adjoint (same arithmetic as k_adj_prologue)
@@ -2094,21 +2302,7 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
 #pragma unroll
         for (int d = 0; d < DIM; ++d) ab[d] = dt * (vn[d] + dt * xn[d]);
         const T rb = dt * rn;
-        const T rho = na.rho[k];
-        const T ir = fast_rcp(rho);
-        vec4_t<T> a;
-        if (DIM == 3) {
-            a.x = ab[0] * ir; a.y = ab[1] * ir; a.z = ab[2] * ir; a.w = rb;
-        } else {
-            a.x = ab[0] * ir; a.y = ab[1] * ir; a.z = rb; a.w = rb * rho;
-        }
-        na.jdA[k] = a;
-        vec4_t<T> b;
-        b.x = rho;
-        b.y = tait(S, rho);
-        b.z = rb * rho;
-        b.w = tait_slope(S, rho);
-        na.jdB[k] = b;
+        na.jdA[k] = adjoint_record<T, DIM>(ab, rb, na.rho[k]);
     }
 }
 
@@ -2122,18 +2316,29 @@ __global__ __launch_bounds__(256) void k_adj_sweep(int64_t N, int32_t width, con
 //     xbar_k += V_k [gbar_j (G_j.w) + Jg G_j (gbar_j.e)] - V_k (rho_k - rho_j) Jg gbar_j
 //     rbar_k += -V_k (gbar_j.w) + (V_k / rho_k) [(rho_k - rho_j)(gbar_j.w) - (e.gbar_j)(G_j.w)]
 // added to the cotangents (original order).  Same list traversal and partial sums.
+template <typename T, int DIM>
+struct RenormAdjNbr {
+    vec4_t<T> a, b, G, gb;
+    __device__ __forceinline__ void keep()
+    {
+        pin<DIM == 3 ? 4 : 3>(a);
+        if (DIM == 2) pin<3>(b);
+        pin<3>(G);
+        pin<3>(gb);
+    }
+};
+
 template <typename T, int DIM, int LPP>
 __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                     const int32_t* __restrict__ nbr_count,
-                                                    const vec4_t<T>* __restrict__ jd0, const vec4_t<T>* __restrict__ jdB,
+                                                    const vec4_t<T>* __restrict__ jd0, const vec4_t<T>* __restrict__ jd1,
                                                     const vec4_t<T>* __restrict__ jdG,
                                                     const vec4_t<T>* __restrict__ gbar,
                                                     const int32_t* __restrict__ orig, StatePtrs<T, DIM> cot,
                                                     const int32_t* __restrict__ psim,
-                                                    const SimConst<T>* __restrict__ sims, int filter)
+                                                    const SimConst<T>* __restrict__ sims)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t k = t / LPP;
     const int r = (int)(t - k * LPP);
@@ -2144,77 +2349,71 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
     T uk[3] = {0, 0, 0};
     unpack_u<T, DIM>(a0, uk);
     const T Vk = rec_volume<T, DIM>(a0, S.m);
-    const T rhok = jdB[k].x;
+    const T rhok = (DIM == 3) ? a0.w : jd1[k].z;
+    const T irk = T(1) / rhok;
     const vec4_t<T> g4 = jdG[k], b4 = gbar[k];
     const T Gk[3] = {g4.x, g4.y, g4.z}, bk[3] = {b4.x, b4.y, b4.z};
     int n = nbr_count[k];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + k * (int64_t)width;
     T ax[NQ][3], ar[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
-    int jn[U];
-    load_entries<LPP, U>(row, r, 0, mcount, (int)k, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        vec4_t<T> na[U], nB[U], nG[U], nb[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t j = (uint32_t)jn[u];
-            na[u] = ldo(jd0, j);
-            nB[u] = ldo(jdB, j);
-            nG[u] = ldo(jdG, j);
-            nb[u] = ldo(gbar, j);
-        }
-        load_entries<LPP, U>(row, r, m0 + U, mcount, (int)k, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (m0 + u >= mcount) continue;
+    using Nbr = RenormAdjNbr<T, DIM>;
+    auto gather = [&](int j, Nbr& nb) {
+        nb.a = ldo(jd0, (uint32_t)j);
+        if (DIM == 2) nb.b = ldo(jd1, (uint32_t)j);
+        nb.G = ldo(jdG, (uint32_t)j);
+        nb.gb = ldo(gbar, (uint32_t)j);
+    };
+    auto pairs = [&](auto image, auto walk) {
+        walk([&](int q, Nbr& nb) {
             T e[3] = {0, 0, 0};
-            const T r2 = r2_exact<T, DIM>(uk, na[u], c.L, c.invL, e);
-            if (filter && !(r2 < c.H2)) continue;
-            const T q = fast_sqrt(r2) * c.invH;
-            const T tt = T(1) - q;
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(uk, nb.a, c.L, c.invL, e);
+            const T tt = kernel_t(r2, c.invH);
             const T t2 = tt * tt;
             const T t4 = t2 * t2;
-            const T gF = c.kG * (T(-56.0 / 3.0) * t4 * tt * (T(1) + T(5) * q));
-            const T hF = c.kH * t4;
-            const T Vj = rec_volume<T, DIM>(na[u], S.m);
-            const T rhoj = nB[u].x;
-            const T Gj[3] = {nG[u].x, nG[u].y, nG[u].z}, bj[3] = {nb[u].x, nb[u].y, nb[u].z};
-            T bke = 0, bje = 0, Gke = 0, Gje = 0;
+            const T g = t4 * (tt * fma(T(-5), tt, T(6)));   // Jg v = kGF (g v + h (e.v) e)
+            const T h = c.hc * t4;
+            const T Vj = rec_volume<T, DIM>(nb.a, S.m);
+            const T rhoj = (DIM == 3) ? nb.a.w : nb.b.z;
+            const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z}, bj[3] = {nb.gb.x, nb.gb.y, nb.gb.z};
+            T bke = bk[0] * e[0], bje = bj[0] * e[0], Gke = Gk[0] * e[0], Gje = Gj[0] * e[0];
 #pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                Gke += Gk[d] * e[d];
-                bke += bk[d] * e[d];
-                Gje += Gj[d] * e[d];
-                bje += bj[d] * e[d];
+            for (int d = 1; d < DIM; ++d) {
+                Gke = fma(Gk[d], e[d], Gke);
+                bke = fma(bk[d], e[d], bke);
+                Gje = fma(Gj[d], e[d], Gje);
+                bje = fma(bj[d], e[d], bje);
             }
-            const T Gkw = gF * Gke, Gjw = gF * Gje, bkw = gF * bke, bjw = gF * bje;
+            // own terms carry G_k.e + (rho_j - rho_k), the neighbour's G_j.e + (rho_j - rho_k)
             const T drk = rhoj - rhok;
+            const T P = Gke + drk, Q = Gje + drk;
+            const T vP = Vj * P, vb = Vj * bke, wQ = Vk * Q, wb = Vk * bje;
+            const T he = h * fma(vb, P, wb * Q);
 #pragma unroll
             for (int d = 0; d < DIM; ++d) {
-                // Jg v = gF v + hF (e.v) e
-                const T JGk = gF * Gk[d] + hF * Gke * e[d];
-                const T Jbk = gF * bk[d] + hF * bke * e[d];
-                const T JGj = gF * Gj[d] + hF * Gje * e[d];
-                const T Jbj = gF * bj[d] + hF * bje * e[d];
-                ax[u % NQ][d] += Vj * (bk[d] * Gkw + JGk * bke) + Vj * drk * Jbk +
-                                 Vk * (bj[d] * Gjw + JGj * bje) + Vk * drk * Jbj;
+                const T z = fma(bk[d], vP, fma(Gk[d], vb, fma(bj[d], wQ, Gj[d] * wb)));
+                ax[q][d] = fma(g, z, fma(he, e[d], ax[q][d]));
             }
-            ar[u % NQ] += -Vj * bkw - Vk * bjw + (Vk / rhok) * (-drk * bjw - bje * Gjw);
-        }
-    }
+            ar[q] = fma(-g, vb + wb * fma(irk, Q, T(1)), ar[q]);
+        });
+    };
+    auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
+    auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
+    if (wave_inside<T, DIM>(uk, S.H, S.L)) pairs(std::false_type{}, groups);
+    else pairs(std::true_type{}, groups);
+    pairs(std::true_type{}, tail);
     T gx[3] = {0, 0, 0}, tmp[NQ];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
-        gx[d] = combine_leaves<LPP>(tmp);
+        gx[d] = c.kGF * combine_leaves<LPP>(tmp);
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
-    const T gr = combine_leaves<LPP>(tmp);
+    const T gr = c.kGF * combine_leaves<LPP>(tmp);
     if (r != 0) return;
     const int o = orig[k];
 #pragma unroll
@@ -2229,16 +2428,21 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
 // partial sums as the sweeps; x is updated in original order.
 constexpr double kShiftR = 0.2;
 
+template <typename T>
+struct ShiftNbr {
+    vec4_t<T> a, b;
+    __device__ __forceinline__ void keep() { pin(a); }
+};
+
 template <typename T, int DIM, int LPP>
 __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                const int32_t* __restrict__ nbr_count,
                                                const vec4_t<T>* __restrict__ jd0, const int32_t* __restrict__ orig,
                                                const int32_t* __restrict__ psim,
-                                               const SimConst<T>* __restrict__ sims, int filter, T beta,
+                                               const SimConst<T>* __restrict__ sims, T beta,
                                                StatePtrs<T, DIM> state)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t i = t / LPP;
     const int r = (int)(t - i * LPP);
@@ -2249,37 +2453,27 @@ __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const i
     unpack_u<T, DIM>(jd0[i], ui);
     int n = nbr_count[i];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + i * (int64_t)width;
     T acc[NQ][3];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
-    int jn[U];
-    load_entries<LPP, U>(row, r, 0, mcount, (int)i, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        vec4_t<T> a[U];
+    auto gather = [&](int j, ShiftNbr<T>& nb) { nb.a = ldo(jd0, (uint32_t)j); };
+    auto pair = [&](int q, ShiftNbr<T>& nb) {
+        T d[3] = {0, 0, 0};
+        const T r2 = r2_exact<T, DIM>(ui, nb.a, c.L, c.invL, d);
+        const T tt = kernel_t(r2, c.invH);
+        const T qq = fast_sqrt(r2) * c.invH;
+        const T t2 = tt * tt;
+        const T t4 = t2 * t2;
+        const T wr = S.kW * t4 * t2 * (T(1) + qq * (T(6) + qq * T(35.0 / 3.0))) * S.invW0;   // W / W(dx)
+        const T w2 = wr * wr;
+        const T phi = T(1) + T(kShiftR) * w2 * w2;
+        const T f = phi * rec_volume<T, DIM>(nb.a, S.m) * (t4 * (tt * fma(T(-5), tt, T(6))));
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = ldo(jd0, (uint32_t)jn[u]);
-        load_entries<LPP, U>(row, r, m0 + U, mcount, (int)i, jn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (m0 + u >= mcount) continue;
-            T d[3] = {0, 0, 0};
-            const T r2 = r2_exact<T, DIM>(ui, a[u], c.L, c.invL, d);
-            if (filter && !(r2 < c.H2)) continue;
-            const T q = fast_sqrt(r2) * c.invH;
-            const T tt = T(1) - q;
-            const T t2 = tt * tt;
-            const T t4 = t2 * t2;
-            const T gF = c.kG * (T(-56.0 / 3.0) * t4 * tt * (T(1) + T(5) * q));
-            const T wr = S.kW * t4 * t2 * (T(1) + q * (T(6) + q * T(35.0 / 3.0))) * S.invW0;   // W / W(dx)
-            const T w2 = wr * wr;
-            const T phi = T(1) + T(kShiftR) * w2 * w2;
-            const T f = phi * rec_volume<T, DIM>(a[u], S.m) * gF;
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) acc[u % NQ][k] += f * d[k];
-        }
-    }
+        for (int k = 0; k < DIM; ++k) acc[q][k] = fma(f, d[k], acc[q][k]);
+    };
+    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, pair);
+    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, pair);
     T sum[3] = {0, 0, 0}, tmp[NQ];
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
@@ -2289,7 +2483,7 @@ __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const i
     }
     if (r != 0) return;
     const int o = orig[i];
-    const T cs = -beta * S.H2;
+    const T cs = -beta * S.H2 * c.kGF;
 #pragma unroll
     for (int k = 0; k < DIM; ++k) state.x[k][o] += cs * sum[k];
 }
@@ -2322,11 +2516,10 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
                                                    const vec4_t<T>* __restrict__ jd0,
                                                    const vec4_t<T>* __restrict__ xs, const T* __restrict__ rho_s,
                                                    const int32_t* __restrict__ orig, const int32_t* __restrict__ psim,
-                                                   const SimConst<T>* __restrict__ sims, int filter, T beta,
+                                                   const SimConst<T>* __restrict__ sims, T beta,
                                                    StatePtrs<T, DIM> cot)
 {
     constexpr int NQ = kLeaves / LPP;
-    constexpr int U = kPairsInFlight;
     const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t k = t / LPP;
     const int r = (int)(t - k * LPP);
@@ -2341,53 +2534,47 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
     const T xbk[3] = {xk4.x, xk4.y, xk4.z};
     int n = nbr_count[k];
     n = n < width ? n : width;
-    const int mcount = (n - r + LPP - 1) / LPP;
     const int32_t* row = nbr + k * (int64_t)width;
     T ax[NQ][3], ar[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
-    int jn[U];
-    load_entries<LPP, U>(row, r, 0, mcount, (int)k, jn);
-    for (int m0 = 0; m0 < mcount; m0 += U) {
-        vec4_t<T> a[U], b[U];
+    auto gather = [&](int j, ShiftNbr<T>& nb) {
+        nb.a = ldo(jd0, (uint32_t)j);
+        nb.b = ldo(xs, (uint32_t)j);
+    };
+    auto pair = [&](int q, ShiftNbr<T>& nb) {
+#pragma clang fp contract(off)
+        T e[3] = {0, 0, 0};
+        const T r2 = r2_exact<T, DIM>(uk, nb.a, c.L, c.invL, e);
+        const T tt = kernel_t(r2, c.invH);
+        const T qq = fast_sqrt(r2) * c.invH;
+        const T t2 = tt * tt;
+        const T t4 = t2 * t2;
+        const T gF = t4 * (tt * fma(T(-5), tt, T(6)));   // times kGF at the end
+        const T hF = c.hc * t4;
+        const T wr = S.kW * t4 * t2 * (T(1) + qq * (T(6) + qq * T(35.0 / 3.0))) * S.invW0;
+        const T w2 = wr * wr;
+        const T phi = T(1) + T(kShiftR) * w2 * w2;
+        const T dphi = T(4.0 * kShiftR) * w2 * wr * S.invW0;
+        const T Vj = rec_volume<T, DIM>(nb.a, S.m);
+        const T xbj[3] = {nb.b.x, nb.b.y, nb.b.z};
+        // z = V_j xb_k - V_k xb_j (zero for the particle itself: no contraction);
+        // D z = phi (gF z + hF (e.z) e) + dphi gF^2 (e.z) e
+        T z[3], ez = T(0), exj = T(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = ldo(jd0, (uint32_t)jn[u]);
-            b[u] = ldo(xs, (uint32_t)jn[u]);
+        for (int d = 0; d < DIM; ++d) {
+            z[d] = Vj * xbk[d] - Vk * xbj[d];
+            ez = fma(e[d], z[d], ez);
+            exj = fma(e[d], xbj[d], exj);
         }
-        load_entries<LPP, U>(row, r, m0 + U, mcount, (int)k, jn);
+        const T ce = ez * fma(phi, hF, dphi * (c.kGF * gF) * gF);
+        const T pg = phi * gF;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (m0 + u >= mcount) continue;
-            T e[3] = {0, 0, 0};
-            const T r2 = r2_exact<T, DIM>(uk, a[u], c.L, c.invL, e);
-            if (filter && !(r2 < c.H2)) continue;
-            const T q = fast_sqrt(r2) * c.invH;
-            const T tt = T(1) - q;
-            const T t2 = tt * tt;
-            const T t4 = t2 * t2;
-            const T gF = c.kG * (T(-56.0 / 3.0) * t4 * tt * (T(1) + T(5) * q));
-            const T hF = c.kH * t4;
-            const T wr = S.kW * t4 * t2 * (T(1) + q * (T(6) + q * T(35.0 / 3.0))) * S.invW0;
-            const T w2 = wr * wr;
-            const T phi = T(1) + T(kShiftR) * w2 * w2;
-            const T dphi = T(4.0 * kShiftR) * w2 * wr * S.invW0;
-            const T Vj = rec_volume<T, DIM>(a[u], S.m);
-            const T xbj[3] = {b[u].x, b[u].y, b[u].z};
-            // z = V_j xb_k - V_k xb_j;  D z = phi (gF z + hF (e.z) e) + dphi gF^2 (e.z) e
-            T z[3], ez = T(0), exj = T(0);
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                z[d] = Vj * xbk[d] - Vk * xbj[d];
-                ez += e[d] * z[d];
-                exj += e[d] * xbj[d];
-            }
-            const T ce = phi * hF * ez + dphi * gF * gF * ez;
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) ax[u % NQ][d] += phi * gF * z[d] + ce * e[d];
-            ar[u % NQ] += phi * gF * exj;
-        }
-    }
+        for (int d = 0; d < DIM; ++d) ax[q][d] = fma(pg, z[d], fma(ce, e[d], ax[q][d]));
+        ar[q] = fma(pg, exj, ar[q]);
+    };
+    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, pair);
+    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, pair);
     T gx[3] = {0, 0, 0}, tmp[NQ];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
@@ -2400,7 +2587,7 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
     const T gr = combine_leaves<LPP>(tmp);
     if (r != 0) return;
     const int o = orig[k];
-    const T cs = -beta * S.H2;
+    const T cs = -beta * S.H2 * c.kGF;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) cot.x[d][o] += cs * gx[d];
     cot.rho[o] += cs * (Vk / rho_s[k]) * gr;
@@ -2463,7 +2650,7 @@ __global__ __launch_bounds__(64 * kExportRows) void k_export_rows(int64_t N, int
     const int32_t* src = nbr + q * (int64_t)width;
     const int64_t base = offsets[orig[q]];
     if (c <= 64) {
-        const int v = lane < c ? orig[src[lane]] : 0;
+        const int v = lane < c ? orig[src[list_offset(lane, width)]] : 0;
         int rank = 0;
         for (int k = 0; k < c; ++k) rank += (__builtin_amdgcn_readlane(v, k) < v) ? 1 : 0;
         if (lane < c) out[base + rank] = v;
@@ -2474,7 +2661,7 @@ __global__ __launch_bounds__(64 * kExportRows) void k_export_rows(int64_t N, int
         for (int m0 = lane; m0 < c; m0 += 256) {   // four entries of a lane in flight; past the row, its last
             int v[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = src[m0 + 64 * j < c ? m0 + 64 * j : c - 1];
+            for (int j = 0; j < 4; ++j) v[j] = src[list_offset(m0 + 64 * j < c ? m0 + 64 * j : c - 1, width)];
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] = orig[v[j]];
 #pragma unroll
@@ -2560,10 +2747,10 @@ __global__ __launch_bounds__(64 * kExportRows) void k_export_rows(int64_t N, int
         return;
     }
     for (int m0 = 0; m0 < c; m0 += 64) {
-        const int v = m0 + lane < c ? orig[src[m0 + lane]] : 0;
+        const int v = m0 + lane < c ? orig[src[list_offset(m0 + lane, width)]] : 0;
         int rank = 0;
         for (int k0 = 0; k0 < c; k0 += 64) {
-            const int w = k0 + lane < c ? orig[src[k0 + lane]] : 0;
+            const int w = k0 + lane < c ? orig[src[list_offset(k0 + lane, width)]] : 0;
             const int kn = c - k0 < 64 ? c - k0 : 64;
             for (int k = 0; k < kn; ++k) rank += (__builtin_amdgcn_readlane(w, k) < v) ? 1 : 0;
         }
@@ -2714,7 +2901,7 @@ __global__ __launch_bounds__(256) void k_adapt_build(int64_t N, const vec4_t<T>*
         const T hm = hi > hj ? hi : hj;
         const T hm2 = hm * hm;
         if (r2 < hm2) {
-            if (c < width) row[c] = j;
+            if (c < width) row[list_offset(c, width)] = j;
             ++c;
         }
     });
