@@ -46,6 +46,8 @@ sph_status fail(sph_status code, const std::string& msg)
     } while (0)
 
 constexpr double kCellMargin = 1.0 + 1.0 / 1024.0;  // cell side exceeds H/sub by more than rounding
+constexpr size_t kMaxMembers = 64;                   // places per cell for its members, at most
+constexpr int64_t kMemberCells = 131072;              // plans with this many cells collect them in rows of places
 constexpr int64_t kGroupedBuildCells = 65536;         // 2D plans with this many cell slots build by 2 x 2 groups
 
 // 3D builds with fewer wavefronts than kBuildWaves (eight on every SIMD) let up to four share a cell's
@@ -113,7 +115,7 @@ struct sph_plan {
     std::vector<unsigned char> h_simc;
     // workspace layout (byte offsets)
     size_t o_simc = 0, o_psim = 0, o_cell_sim = 0, o_blk_coord = 0, o_blk_rank = 0;
-    size_t o_cell_count = 0, o_cell_start = 0, o_part = 0, o_cell_of = 0, o_slot_of = 0, o_tmp = 0;
+    size_t o_cell_count = 0, o_cell_start = 0, o_part = 0, o_cell_of = 0, o_link = 0;
     size_t o_SB = 0, o_jdA = 0, o_status = 0, o_part64 = 0, o_pairs = 0, o_ticket = 0, o_uref = 0;
     // status words of the neighbour export's own list build, kept apart from the plan's status
     // words (an overflow there is returned by sph_neighbors, not left for sph_poll)
@@ -123,7 +125,10 @@ struct sph_plan {
     // two buffers of adjoint prologue records; adj_buf is the one in use, and adj_ready the tape
     // slot whose records an adjoint sweep has already written there (-1: none)
     size_t o_jdA2 = 0;
-    size_t o_cots = 0;   // cotangents in sorted order, between the adjoint sweeps of a reuse interval
+    // cotangents in sorted order, between the adjoint sweeps of a reuse interval; or the cells' members
+    // (members_cap places each), between the counting and the gather of a sort
+    size_t o_cots = 0;
+    int32_t members_cap = 0;
     int adj_buf = 0, adj_ready = -1;
     std::vector<SlotLayout> slot;
     // Every write of a slot's sorted state or lists gives the slot a new generation number; the
@@ -215,6 +220,12 @@ T* wsp(const sph_plan* p, size_t off) { return reinterpret_cast<T*>(p->ws + off)
 
 // The particle -> simulation table, null for a plan of one simulation.
 const int32_t* sim_table(const sph_plan* P) { return P->nsims == 1 ? nullptr : wsp<int32_t>(P, P->o_psim); }
+
+// Where the cells' members are collected between the counting and the gather of a sort.
+CellMembers cell_members(const sph_plan* P)
+{
+    return CellMembers{wsp<int32_t>(P, P->o_cots), wsp<int32_t>(P, P->o_link), P->members_cap};
+}
 
 size_t tsize(const sph_plan* p) { return p->dtype == SPH_F64 ? 8 : 4; }
 
@@ -396,8 +407,6 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
     int32_t* cell_count = wsp<int32_t>(P, P->o_cell_count);
     int32_t* cell_start = wsp<int32_t>(P, P->o_cell_start);
     int32_t* cell_of = wsp<int32_t>(P, P->o_cell_of);
-    int32_t* slot_of = wsp<int32_t>(P, P->o_slot_of);
-    int32_t* tmp = wsp<int32_t>(P, P->o_tmp);
     const int32_t* psim = wsp<int32_t>(P, P->o_psim);
     const SimConst<T>* simc = wsp<SimConst<T>>(P, P->o_simc);
     const int32_t* blk_rank = wsp<int32_t>(P, P->o_blk_rank);
@@ -407,19 +416,25 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
     const unsigned g = grid_for(N, 256);
     ProfScope prof(P, st, SPH_KERN_SORT);
     if (!assigned) {
-        k_assign<T, D><<<g, 256, 0, st>>>(N, src, psim, simc, blk_rank, cell_count, cell_of, slot_of, status);
+        k_assign<T, D><<<g, 256, 0, st>>>(N, src, psim, simc, blk_rank, cell_count, cell_of, cell_members(P), orig_in,
+                                          status);
         LAUNCH_CHECK("assign");
     }
-    RC_TRY(scan_exclusive<int32_t>(cell_count, P->ncell, wsp<int32_t>(P, P->o_part),
-                                   wsp<unsigned int>(P, P->o_ticket), cell_start, true, st));
-    k_scatter<<<g, 256, 0, st>>>(N, cell_of, slot_of, cell_start, tmp);
-    LAUNCH_CHECK("scatter");
-    k_order_gather<T, D><<<g, 256, 0, st>>>(N, tmp, cell_of, cell_start, orig_in, src, ws_state<T, D>(P, L.SA),
-                                            orig_out, wsp<vec4_t<T>>(P, L.jd0), wsp<vec4_t<T>>(P, L.jd1), psim,
-                                            simc, P->filter ? wsp<vec4_t<T>>(P, P->o_uref) : nullptr,
-                                            (T)(P->speed_skins ? kSkinFloor : 1.0),
-                                            (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0));
-    LAUNCH_CHECK("order_gather");
+    unsigned int* ticket = wsp<unsigned int>(P, P->o_ticket);
+    const bool scan = P->ncell <= kSortScanCells;
+    if (!scan)
+        RC_TRY(scan_exclusive<int32_t>(cell_count, P->ncell, wsp<int32_t>(P, P->o_part), ticket, cell_start, true, st));
+    if (P->members_cap == 0) {
+        k_scatter<<<g, 256, 0, st>>>(N, cell_of, cell_start, orig_in, cell_members(P));
+        LAUNCH_CHECK("scatter");
+    }
+    auto kernel = scan ? k_sort_gather<T, D, true> : k_sort_gather<T, D, false>;
+    kernel<<<grid_for(N, kSortThreads), kSortThreads, 0, st>>>(
+        N, (int32_t)P->ncell, cell_count, cell_start, ticket, cell_of, cell_members(P), orig_in, src,
+        ws_state<T, D>(P, L.SA), orig_out, wsp<vec4_t<T>>(P, L.jd0), wsp<vec4_t<T>>(P, L.jd1), sim_table(P), simc,
+        P->filter ? wsp<vec4_t<T>>(P, P->o_uref) : nullptr, (T)(P->speed_skins ? kSkinFloor : 1.0),
+        (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0));
+    LAUNCH_CHECK("sort_gather");
     return SPH_OK;
 }
 
@@ -537,8 +552,7 @@ sph_status sweep(sph_plan* P, int slot, T* drho, T* acc, T* rhosum, hipStream_t 
     if (P->N == 0) return SPH_OK;
     const SlotLayout& L = P->slot[slot];
     const SlotLayout& LL = P->slot[P->list_of[slot]];
-    NextCells next{wsp<int32_t>(P, P->o_blk_rank), nullptr, wsp<int32_t>(P, P->o_cell_of),
-                   wsp<int32_t>(P, P->o_slot_of)};
+    NextCells next{wsp<int32_t>(P, P->o_blk_rank), nullptr, wsp<int32_t>(P, P->o_cell_of), cell_members(P)};
     if (assign_next) next.cell_count = wsp<int32_t>(P, P->o_cell_count);
     NextSlot<T> ns{nullptr, nullptr, nullptr, nullptr};
     StatePtrs<T, D> dst = ws_state<T, D>(P, P->o_SB);
@@ -1595,12 +1609,17 @@ sph_status sph_plan_create(const sph_params* sims, int32_t nsims, const int64_t*
     P->o_cell_start = take(4 * ((size_t)P->ncell + 1));
     P->o_part = take(4 * ((size_t)P->nparts + 1));
     P->o_cell_of = take(4 * N);
-    P->o_slot_of = take(4 * N);
-    P->o_tmp = take(4 * N);
+    P->o_link = take(4 * N);
     P->o_SB = take(T * N * (2 * d + 1));
     P->o_jdA = take(V4 * N);
     P->o_jdA2 = take(V4 * N);
-    P->o_cots = take(T * N * (2 * d + 1));
+    const size_t cots = T * N * (2 * d + 1);
+    const bool rows = P->ncell > 0 && P->ncell <= kMemberCells;
+    P->o_cots = take(rows ? std::max<size_t>(cots, 4 * (size_t)P->ncell) : cots);
+    if (rows) {
+        const size_t cap = std::min<size_t>(cots / (4 * (size_t)P->ncell), kMaxMembers) & ~(size_t)3;
+        P->members_cap = cap ? (int32_t)cap : 1;
+    }
     P->o_status = take(4 * (size_t)nsims);
     P->o_status_x = take(4 * (size_t)nsims);
     P->o_part64 = take(8 * ((size_t)P->nparts64 + 1) + 8 * (N + 1));

@@ -284,6 +284,9 @@ __device__ __forceinline__ int64_t wave_incl_scan(int64_t v)
     return v;
 }
 
+// The simulation of sorted particle i; a plan of one simulation passes no table (psim null).
+__device__ __forceinline__ int sim_of(const int32_t* __restrict__ psim, int64_t i) { return psim ? psim[i] : 0; }
+
 // ---------------------------------------------------------------- fill
 
 template <typename I>
@@ -295,12 +298,33 @@ __global__ void k_fill(I* __restrict__ p, int64_t n, I val)
 
 // ---------------------------------------------------------------- cell assignment
 
+// The members of the cells, collected while they are counted: cell c keeps the original indices of its
+// first cap - 1 arrivals in row c of `rows`; later ones (dense clusters) are chained, the chain's head in
+// the row's last place and the links, by position in the source order, in `link`.  A chain's length
+// follows from the cell's count, so neither rows nor links are ever cleared.  cap is 1 or a multiple of 4;
+// or 0 in plans of many cells, whose arrivals keep their place in the cell in `link` and are scattered into
+// contiguous `rows` once the cell starts are known (k_scatter): the scattered stores of a padded row cost
+// the 512-simulation batch, 3.1 million particles, more than that launch does.
+struct CellMembers {
+    int32_t* rows;
+    int32_t* link;
+    int32_t cap;
+};
+
+__device__ __forceinline__ void add_member(const CellMembers& m, int cell, int slot, int32_t p, int32_t orig)
+{
+    int32_t* row = m.rows + (int64_t)cell * m.cap;
+    if (m.cap == 0) m.link[p] = slot;
+    else if (slot < m.cap - 1) row[slot] = orig;
+    else m.link[p] = atomicExch(&row[m.cap - 1], p);
+}
+
 template <typename T, int DIM>
 __global__ __launch_bounds__(256) void k_assign(int64_t N, StatePtrs<T, DIM> st, const int32_t* __restrict__ psim,
                                                 const SimConst<T>* __restrict__ sims,
                                                 const int32_t* __restrict__ blk_rank, int32_t* __restrict__ cell_count,
-                                                int32_t* __restrict__ cell_of, int32_t* __restrict__ slot_of,
-                                                int32_t* __restrict__ status)
+                                                int32_t* __restrict__ cell_of, CellMembers members,
+                                                const int32_t* __restrict__ orig_in, int32_t* __restrict__ status)
 {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
@@ -321,7 +345,7 @@ __global__ __launch_bounds__(256) void k_assign(int64_t N, StatePtrs<T, DIM> st,
     if (bad) atomicOr(&status[s], kFlagNonfinite);
     int gc = global_cell<T, DIM>(S, blk_rank, c[0], c[1], c[2]);
     cell_of[p] = gc;
-    slot_of[p] = atomicAdd(&cell_count[gc], 1);
+    add_member(members, gc, atomicAdd(&cell_count[gc], 1), (int32_t)p, orig_in ? orig_in[p] : (int32_t)p);
 }
 
 // ---------------------------------------------------------------- exclusive scan (3 phases)
@@ -423,24 +447,39 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(I* __restrict__ in,
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = part[np];
 }
 
-// ---------------------------------------------------------------- scatter and within-cell order
+// ---------------------------------------------------------------- within-cell order and gather
 
 __global__ __launch_bounds__(256) void k_scatter(int64_t N, const int32_t* __restrict__ cell_of,
-                                                 const int32_t* __restrict__ slot_of,
-                                                 const int32_t* __restrict__ cell_start, int32_t* __restrict__ tmp)
+                                                 const int32_t* __restrict__ cell_start,
+                                                 const int32_t* __restrict__ orig_in, CellMembers members)
 {
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
-    tmp[cell_start[cell_of[p]] + slot_of[p]] = (int32_t)p;
+    members.rows[cell_start[cell_of[p]] + members.link[p]] = orig_in ? orig_in[p] : (int32_t)p;
 }
 
+// Threads of k_sort_gather, and the most cells whose counts each of its workgroups scans by itself.  Up to
+// there the sort is one launch behind the counting; past it the counts go through the two scan launches
+// first, as every workgroup reads them all (16 384 cells: 10.3 us against 16 and two launches more; the
+// reads grow with the square of the plan).
+constexpr int kSortThreads = 256;
+constexpr int kSortScanCells = 16384;
+
 // Final sorted position = cell start + rank of the particle's original index among its cell's
-// members; gathers the state into that position and packs the per-particle data that the
-// neighbour sweeps read (wrapped position, volume V = m / rho, p V, velocity).
-template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_order_gather(int64_t N, const int32_t* __restrict__ tmp,
-                                                      const int32_t* __restrict__ cell_of,
-                                                      const int32_t* __restrict__ cell_start,
+// members; moves the state there and packs the per-particle data that the neighbour sweeps read
+// (wrapped position, volume V = m / rho, p V, velocity).  One thread per particle in source order.
+// With SCAN the cell starts are formed here: a wavefront scans its share of the cells, four per lane and
+// turn, into LDS (a prefix per four cells), the workgroup's particles look their cell up there, and the
+// workgroups write cell_start between them; the last workgroup to have read the counts clears them for
+// the next sort.  Bound: launch and memory latency, a chain of a few dependent loads.  Measured behind
+// the counting, before (two scan launches, a scatter of the particle indices, a gather that ranked them
+// by three dependent loads each) and now, launch gaps not counted: 2D 101^2 17.3 and 5.5 us, 2D 32^2 FP64
+// 13.1 and 4.8, 2D 256^2 19.8 and 10.3, 3D 47^3 25.9 and 13.4, 3D 64^3 (scan launches) 34 and 21.
+template <typename T, int DIM, bool SCAN>
+__global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t ncell, int32_t* __restrict__ cell_count,
+                                                      int32_t* __restrict__ cell_start,
+                                                      unsigned int* __restrict__ ticket,
+                                                      const int32_t* __restrict__ cell_of, CellMembers members,
                                                       const int32_t* __restrict__ orig_in, StatePtrs<T, DIM> src,
                                                       StatePtrs<T, DIM> dst, int32_t* __restrict__ orig_out,
                                                       vec4_t<T>* __restrict__ jd0, vec4_t<T>* __restrict__ jd1,
@@ -449,20 +488,97 @@ __global__ __launch_bounds__(256) void k_order_gather(int64_t N, const int32_t* 
                                                       vec4_t<T>* __restrict__ uref, T skin_floor,
                                                       T skin_steps)
 {
-    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N) return;
-    const int p = tmp[q];
-    const int c = cell_of[p];
-    const int s0 = cell_start[c], s1 = cell_start[c + 1];
-    const int op = orig_in ? orig_in[p] : p;
+    constexpr int kWaves = kSortThreads / 64;
+    __shared__ int32_t quads[SCAN ? kSortScanCells / 4 : 1];
+    __shared__ int32_t wave_sum[kWaves];
+    __shared__ int is_last;
+    const int64_t p = (int64_t)blockIdx.x * kSortThreads + threadIdx.x;
+    const bool active = p < N;
+    const int c = active ? cell_of[p] : 0;
+    const int op = !active ? 0 : orig_in ? orig_in[p] : (int)p;
+    int s0 = 0, n = 0;
+    unsigned int done = 0;
+    const int nq = ncell >> 2;   // blocks hold 8 or 16 cells
+    if (SCAN) {
+        constexpr int U = 8;
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        const int seg = (nq + 64 * kWaves - 1) / (64 * kWaves) * 64;   // quads of a wavefront
+        const int4* counts = reinterpret_cast<const int4*>(cell_count);
+        const int end = (w + 1) * seg < nq ? (w + 1) * seg : nq;
+        int carry = 0;
+        for (int q0 = w * seg; q0 < end; q0 += 64 * U) {
+            int4 v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int q = q0 + 64 * k + lane;
+                v[k] = counts[q < end ? q : end - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int q = q0 + 64 * k + lane;
+                const int sum = q < end ? (v[k].x + v[k].y) + (v[k].z + v[k].w) : 0;
+                const int inc = wave_incl_scan(sum);
+                if (q < end) quads[q] = carry + inc - sum;
+                carry += __builtin_amdgcn_readlane(inc, 63);
+            }
+        }
+        if (lane == 0) wave_sum[w] = carry;
+        __syncthreads();
+        auto quad_start = [&](int q) {
+            int s = quads[q];
+#pragma unroll
+            for (int k = 0; k + 1 < kWaves; ++k) s += q >= (k + 1) * seg ? wave_sum[k] : 0;
+            return s;
+        };
+        const int4 v = counts[c >> 2];
+        s0 = quad_start(c >> 2);
+        if ((c & 3) > 0) s0 += v.x;
+        if ((c & 3) > 1) s0 += v.y;
+        if ((c & 3) > 2) s0 += v.z;
+        n = (c & 2) ? ((c & 1) ? +v.w : +v.z) : ((c & 1) ? +v.y : +v.x);
+        for (int64_t q = p; q < nq; q += (int64_t)gridDim.x * kSortThreads) {
+            const int4 u = counts[q];
+            int4 o;
+            o.x = quad_start((int)q);
+            o.y = o.x + u.x;
+            o.z = o.y + u.y;
+            o.w = o.z + u.z;
+            reinterpret_cast<int4*>(cell_start)[q] = o;
+        }
+        if (p == 0) cell_start[ncell] = (int32_t)N;
+        // every count this workgroup reads has arrived before it takes its ticket
+        asm volatile("" : "+v"(n), "+v"(s0));
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) done = atomicAdd(ticket, 1u);
+    } else if (active) {
+        s0 = cell_start[c];
+        n = cell_start[c + 1] - s0;
+    }
+    if (active) {
     int rank = 0;
-    for (int r = s0; r < s1; ++r) {
-        int pr = tmp[r];
-        int o = orig_in ? orig_in[pr] : pr;
-        rank += (o < op) ? 1 : 0;
+    if (!SCAN && members.cap == 0) {
+        const int32_t* row = members.rows + s0;
+#pragma unroll 4
+        for (int e = 0; e < n; ++e) rank += row[e] < op ? 1 : 0;
+    } else {
+        const int32_t* row = members.rows + (int64_t)c * members.cap;
+        const int listed = n < members.cap - 1 ? n : members.cap - 1;
+        for (int e = 0; e < listed; e += 4) {
+            const int4 o = *reinterpret_cast<const int4*>(row + e);
+            rank += (o.x < op) + (e + 1 < listed && o.y < op) + (e + 2 < listed && o.z < op) +
+                    (e + 3 < listed && o.w < op);
+        }
+        if (n > listed) {
+            int j = row[members.cap - 1];
+            for (int k = listed; k < n; ++k) {
+                rank += (orig_in ? orig_in[j] : j) < op ? 1 : 0;
+                if (k + 1 < n) j = members.link[j];
+            }
+        }
     }
     const int d = s0 + rank;
-    const SimConst<T>& S = sims[psim[d]];
+    const SimConst<T>& S = sims[sim_of(psim, p)];
     T x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, u[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
@@ -500,6 +616,16 @@ __global__ __launch_bounds__(256) void k_order_gather(int64_t N, const int32_t* 
         vec4_t<T> r;
         r.x = u[0]; r.y = u[1]; r.z = u[2]; r.w = h;
         uref[d] = r;
+    }
+    }
+    if (SCAN) {
+        if (threadIdx.x == 0) is_last = done == gridDim.x - 1;
+        __syncthreads();
+        if (is_last) {
+            for (int q = threadIdx.x; q < nq; q += kSortThreads)
+                reinterpret_cast<int4*>(cell_count)[q] = make_int4(0, 0, 0, 0);
+            if (threadIdx.x == 0) *ticket = 0u;
+        }
     }
 }
 
@@ -1208,9 +1334,6 @@ struct NextSlot {
     const vec4_t<T>* uref;
 };
 
-// The simulation of sorted particle i; a plan of one simulation passes no table (psim null).
-__device__ __forceinline__ int sim_of(const int32_t* __restrict__ psim, int64_t i) { return psim ? psim[i] : 0; }
-
 template <typename T>
 __device__ __forceinline__ PairConst<T> pair_const(const SimConst<T>& S);
 
@@ -1528,7 +1651,7 @@ struct NextCells {
     const int32_t* blk_rank;
     int32_t* cell_count;
     int32_t* cell_of;
-    int32_t* slot_of;
+    CellMembers members;
 };
 
 // LPP lanes share a particle and walk its row with sweep_list; wavefronts whose particles all lie more
@@ -1559,9 +1682,9 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
 {
     constexpr int NQ = kLeaves / LPP;
     static_assert(LPP == 2 || LPP == 4 || LPP == 8, "lanes per particle must be 2, 4 or 8");
-    const int64_t t = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    const int64_t i = t / LPP;
-    const int r = (int)(t - i * LPP);
+    const uint32_t t = (uint32_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    const uint32_t i = t / LPP;   // N records fit 32-bit offsets
+    const int r = (int)(t % LPP);
     int accepted = 0;  // listed pairs with r < H (lists with a skin)
     if (i < N) {
     const int s = sim_of(psim, i);
@@ -1587,7 +1710,7 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     }
     int n = nbr_count[i];
     n = n < width ? n : width;
-    const int32_t* row = nbr + i * (int64_t)width;
+    const int32_t* row = nbr + (int64_t)i * width;
     // the particle's own entry and the places past the count, at r2 = 0, are counted by the loop
     if (r == 0 && n > 0) accepted = n - positions_visited<T, LPP>(n, width) - 1;
     // W(0) = 1 of the particle itself
@@ -1673,7 +1796,7 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
         if (next.cell_count) {
             const int gcell = global_cell<T, DIM>(S, next.blk_rank, cc[0], cc[1], cc[2]);
             next.cell_of[i] = gcell;
-            next.slot_of[i] = atomicAdd(&next.cell_count[gcell], 1);
+            add_member(next.members, gcell, atomicAdd(&next.cell_count[gcell], 1), (int32_t)i, orig[i]);
         }
         if (ns.jd0) {
             // packed records of the next step, as the sort would write them
