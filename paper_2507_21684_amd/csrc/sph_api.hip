@@ -633,18 +633,19 @@ void launch_renorm_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, S
 // Adjoint of the step that starts from the state in `slot` (sorted with its lists built).
 // With vjp, the update function's VJP instead: cot holds the cotangents (kx, ka, krho) of
 // (v, a, drho/dt) on entry and (xbar, vbar, rhobar) on exit.
+// With has_records the caller has written the slot's adjoint records.
 // With next_slot >= 0 (a tape slot sharing this slot's particle order, whose adjoint runs next),
 // the sweep also writes that step's prologue records into the other buffer and the cotangents in
 // sorted order, and the next call skips its prologue and reads those; the last sweep of such a
 // chain writes cot.
 template <typename T, int D>
 sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, bool vjp = false,
-                   int next_slot = -1)
+                   int next_slot = -1, bool has_records = false)
 {
     if (P->N == 0) return SPH_OK;
     const SlotLayout& L = P->slot[slot];
     const bool ready = P->adj_ready == slot;   // the sweep before left this slot's records and cotangents
-    if (!ready) {
+    if (!ready && !has_records) {
         ProfScope prof(P, st, SPH_KERN_OTHER);
         k_adj_prologue<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(
             P->N, wsp<int32_t>(P, L.orig), cot, ws_state<T, D>(P, L.SA), wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)),
@@ -696,13 +697,9 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
 template <typename T, int D>
 sph_status copy_state(sph_plan* P, StatePtrs<T, D> dst, StatePtrs<T, D> src, hipStream_t st)
 {
-    const size_t b = sizeof(T) * (size_t)P->N;
-    if (b == 0) return SPH_OK;
-    for (int k = 0; k < D; ++k) {
-        HIP_TRY(hipMemcpyAsync(dst.x[k], src.x[k], b, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(dst.v[k], src.v[k], b, hipMemcpyDeviceToDevice, st));
-    }
-    HIP_TRY(hipMemcpyAsync(dst.rho, src.rho, b, hipMemcpyDeviceToDevice, st));
+    if (P->N == 0) return SPH_OK;
+    k_copy_state<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, src, dst);
+    LAUNCH_CHECK("copy_state");
     return SPH_OK;
 }
 
@@ -886,10 +883,9 @@ StatePtrs<T, D> rk_block(const sph_plan* P, size_t base, int i)
 }
 
 template <typename T, int D>
-sph_status lincomb(sph_plan* P, StatePtrs<T, D> out, StatePtrs<T, D> base, double s0, bool s0_dt, int n,
-                   const double* c, const StatePtrs<T, D>* K, bool c_dt, hipStream_t st)
+LinComb<T, D> make_lincomb(StatePtrs<T, D> out, StatePtrs<T, D> base, double s0, bool s0_dt, int n, const double* c,
+                           const StatePtrs<T, D>* K, bool c_dt)
 {
-    if (P->N == 0) return SPH_OK;
     LinComb<T, D> L{};
     L.out = out;
     L.base = base;
@@ -901,11 +897,29 @@ sph_status lincomb(sph_plan* P, StatePtrs<T, D> out, StatePtrs<T, D> base, doubl
         L.c[j] = (T)c[j];
         L.K[j] = K[j];
     }
+    return L;
+}
+
+template <typename T, int D>
+sph_status lincomb(sph_plan* P, StatePtrs<T, D> out, StatePtrs<T, D> base, double s0, bool s0_dt, int n,
+                   const double* c, const StatePtrs<T, D>* K, bool c_dt, hipStream_t st)
+{
+    if (P->N == 0) return SPH_OK;
+    const LinComb<T, D> L = make_lincomb<T, D>(out, base, s0, s0_dt, n, c, K, c_dt);
     ProfScope prof(P, st, SPH_KERN_OTHER);
-    k_lincomb<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, L, wsp<int32_t>(P, P->o_psim),
-                                                         wsp<SimConst<T>>(P, P->o_simc));
+    k_lincomb<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, L, sim_table(P), wsp<SimConst<T>>(P, P->o_simc));
     LAUNCH_CHECK("lincomb");
     return SPH_OK;
+}
+
+// The stage slot: slot 0, sorted and with lists; without `state` it holds the stage's state already.
+template <typename T, int D>
+StageSlot<T, D> stage_slot(sph_plan* P, bool state)
+{
+    const SlotLayout& L = P->slot[0];
+    if (state) P->touch(0);
+    return StageSlot<T, D>{wsp<int32_t>(P, L.orig), ws_state<T, D>(P, L.SA), state ? wsp<vec4_t<T>>(P, L.jd0) : nullptr,
+                           wsp<vec4_t<T>>(P, L.jd1), wsp<vec4_t<T>>(P, P->o_uref)};
 }
 
 // Puts a stage state w (original order) into slot 0 with neighbour lists for its sweeps.  The
@@ -919,15 +933,32 @@ sph_status stage_into_slot0(sph_plan* P, StatePtrs<T, D> w, bool first, hipStrea
         RC_TRY((sort_into<T, D>(P, w, nullptr, 0, st)));
         return build_lists<T, D>(P, 0, st);
     }
-    P->touch(0);
+    const StageSlot<T, D> slot = stage_slot<T, D>(P, true);
     if (P->N == 0) return SPH_OK;
-    const SlotLayout& L = P->slot[0];
     ProfScope prof(P, st, SPH_KERN_SORT);
-    k_repack<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(
-        P->N, wsp<int32_t>(P, L.orig), w, ws_state<T, D>(P, L.SA), wsp<vec4_t<T>>(P, L.jd0), wsp<vec4_t<T>>(P, L.jd1),
-        wsp<vec4_t<T>>(P, P->o_uref), wsp<int32_t>(P, P->o_psim), wsp<SimConst<T>>(P, P->o_simc),
-        wsp<int32_t>(P, P->o_status));
+    k_repack<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, w, slot, sim_table(P), wsp<SimConst<T>>(P, P->o_simc),
+                                                        wsp<int32_t>(P, P->o_status));
     LAUNCH_CHECK("repack");
+    return SPH_OK;
+}
+
+// A later stage's state out = base + dt sum_j c[j] K[j], put into slot 0 with lists: with a skin in one
+// pass into the particle order and with the lists of the step's first stage.
+template <typename T, int D>
+sph_status later_stage(sph_plan* P, StatePtrs<T, D> out, StatePtrs<T, D> base, int n, const double* c,
+                       const StatePtrs<T, D>* K, bool keep_lists, hipStream_t st)
+{
+    if (!keep_lists || !P->filter) {
+        RC_TRY((lincomb<T, D>(P, out, base, 1.0, false, n, c, K, true, st)));
+        return stage_into_slot0<T, D>(P, out, true, st);
+    }
+    const StageSlot<T, D> slot = stage_slot<T, D>(P, true);
+    if (P->N == 0) return SPH_OK;
+    ProfScope prof(P, st, SPH_KERN_SORT);
+    k_stage_state<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(
+        P->N, make_lincomb<T, D>(out, base, 1.0, false, n, c, K, true), slot, sim_table(P),
+        wsp<SimConst<T>>(P, P->o_simc), wsp<int32_t>(P, P->o_status));
+    LAUNCH_CHECK("stage_state");
     return SPH_OK;
 }
 
@@ -941,7 +972,10 @@ sph_status rk_stages(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D>* U, StatePt
     const int s = P->rk_stages;
     for (int i = 0; i < s; ++i) {
         U[i] = (i == 0) ? u : rk_block<T, D>(P, P->o_rkU, i);
-        if (i > 0) {
+        K[i] = rk_block<T, D>(P, P->o_rkK, i);
+        if (i == 0) {
+            RC_TRY((stage_into_slot0<T, D>(P, u, true, st)));
+        } else {
             double c[kMaxStages];
             StatePtrs<T, D> Ks[kMaxStages];
             int n = 0;
@@ -950,19 +984,17 @@ sph_status rk_stages(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D>* U, StatePt
                     c[n] = P->rk_A[i * kMaxStages + j];
                     Ks[n++] = K[j];
                 }
-            RC_TRY((lincomb<T, D>(P, U[i], u, 1.0, false, n, c, Ks, true, st)));
+            RC_TRY((later_stage<T, D>(P, U[i], u, n, c, Ks, true, st)));
         }
-        K[i] = rk_block<T, D>(P, P->o_rkK, i);
-        RC_TRY((stage_into_slot0<T, D>(P, U[i], i == 0, st)));
         RC_TRY((sweep<T, D, kModeRhs>(P, 0, K[i].rho, K[i].v[0], nullptr, st)));
         for (int k = 0; k < 3; ++k) K[i].x[k] = U[i].v[k];
     }
     return SPH_OK;
 }
 
-// One Runge-Kutta step of u in place: u <- u + dt sum_i b_i k_i.
+// One Runge-Kutta step: out = u + dt sum_i b_i k_i (out may be u).
 template <typename T, int D>
-sph_status rk_step(sph_plan* P, StatePtrs<T, D> u, hipStream_t st)
+sph_status rk_step(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D> out, hipStream_t st)
 {
     StatePtrs<T, D> U[kMaxStages], K[kMaxStages];
     RC_TRY((rk_stages<T, D>(P, u, U, K, st)));
@@ -974,7 +1006,7 @@ sph_status rk_step(sph_plan* P, StatePtrs<T, D> u, hipStream_t st)
             c[n] = P->rk_b[i];
             Ks[n++] = K[i];
         }
-    return lincomb<T, D>(P, u, u, 1.0, false, n, c, Ks, true, st);
+    return lincomb<T, D>(P, out, u, 1.0, false, n, c, Ks, true, st);
 }
 
 // Vector-Jacobian product of one Runge-Kutta step started at u, cot in place (output
@@ -987,8 +1019,6 @@ sph_status rk_step_adjoint(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D> cot, 
     const int s = P->rk_stages;
     StatePtrs<T, D> U[kMaxStages], K[kMaxStages], Ub[kMaxStages];
     RC_TRY((rk_stages<T, D>(P, u, U, K, st)));
-    const StatePtrs<T, D> B0 = rk_block<T, D>(P, P->o_rkB0, 0);
-    RC_TRY((lincomb<T, D>(P, B0, cot, 1.0, false, 0, nullptr, nullptr, false, st)));
     for (int i = s - 1; i >= 0; --i) {
         Ub[i] = rk_block<T, D>(P, P->o_rkUb, i);
         double c[kMaxStages];
@@ -999,24 +1029,27 @@ sph_status rk_step_adjoint(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D> cot, 
                 c[n] = P->rk_A[l * kMaxStages + i];
                 Ks[n++] = Ub[l];
             }
-        RC_TRY((lincomb<T, D>(P, Ub[i], B0, P->rk_b[i], true, n, c, Ks, true, st)));
-        // the stages' lists are those rk_stages left in slot 0 (the first stage's, with a skin)
-        RC_TRY((stage_into_slot0<T, D>(P, U[i], !P->filter, st)));
-        RC_TRY((adjoint<T, D>(P, 0, Ub[i], st, true)));
+        // the stages' lists are those rk_stages left in slot 0 (the first stage's, with a skin), and its
+        // state is the last stage's
+        if (P->filter && P->N > 0) {
+            const StageSlot<T, D> slot = stage_slot<T, D>(P, i + 1 < s);
+            ProfScope prof(P, st, SPH_KERN_SORT);
+            k_stage_cot<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(
+                P->N, make_lincomb<T, D>(Ub[i], cot, P->rk_b[i], true, n, c, Ks, true), U[i], slot,
+                wsp<vec4_t<T>>(P, jdA_off(P, P->adj_buf)), sim_table(P), wsp<SimConst<T>>(P, P->o_simc),
+                wsp<int32_t>(P, P->o_status));
+            LAUNCH_CHECK("stage_cot");
+        } else {
+            RC_TRY((lincomb<T, D>(P, Ub[i], cot, P->rk_b[i], true, n, c, Ks, true, st)));
+            RC_TRY((stage_into_slot0<T, D>(P, U[i], true, st)));
+        }
+        RC_TRY((adjoint<T, D>(P, 0, Ub[i], st, true, -1, P->filter)));
     }
     double ones[kMaxStages] = {1.0, 1.0, 1.0, 1.0};
-    return lincomb<T, D>(P, cot, B0, 1.0, false, s, ones, Ub, false, st);
+    return lincomb<T, D>(P, cot, cot, 1.0, false, s, ones, Ub, false, st);
 }
 
 // ---------------------------------------------------------------- symplectic Euler steps
-
-// Rates (., a, D) = f(w) into r (original order) from a sort, a list build and a sweep of w.
-template <typename T, int D>
-sph_status rates_at(sph_plan* P, StatePtrs<T, D> w, StatePtrs<T, D> r, bool first, hipStream_t st)
-{
-    RC_TRY((stage_into_slot0<T, D>(P, w, first, st)));
-    return sweep<T, D, kModeRhs>(P, 0, r.rho, r.v[0], nullptr, st);
-}
 
 template <typename T, int D>
 sph_status symp_final(sph_plan* P, StatePtrs<T, D> u, StatePtrs<T, D> uh, StatePtrs<T, D> r2, hipStream_t st)
@@ -1039,13 +1072,16 @@ sph_status symp_stages(sph_plan* P, StatePtrs<T, D> u, bool fresh, StatePtrs<T, 
     r1 = rk_block<T, D>(P, P->o_rkK, 0);
     r2 = rk_block<T, D>(P, P->o_rkK, 1);
     uh = rk_block<T, D>(P, P->o_rkU, 1);
-    if (fresh) RC_TRY((rates_at<T, D>(P, u, r1, true, st)));
+    if (fresh) {
+        RC_TRY((stage_into_slot0<T, D>(P, u, true, st)));
+        RC_TRY((sweep<T, D, kModeRhs>(P, 0, r1.rho, r1.v[0], nullptr, st)));
+    }
     StatePtrs<T, D> k1 = r1;
     for (int k = 0; k < 3; ++k) k1.x[k] = u.v[k];  // the predictor's x-rate is v
     const double half = 0.5;
-    RC_TRY((lincomb<T, D>(P, uh, u, 1.0, false, 1, &half, &k1, true, st)));
     // with a fresh predictor the step's lists are u's, which the predictor state can keep
-    return rates_at<T, D>(P, uh, r2, !fresh, st);
+    RC_TRY((later_stage<T, D>(P, uh, u, 1, &half, &k1, fresh, st)));
+    return sweep<T, D, kModeRhs>(P, 0, r2.rho, r2.v[0], nullptr, st);
 }
 
 // One step of u in place.  With re-use the corrector's rates are copied to block 0 for the
@@ -1118,7 +1154,7 @@ sph_status do_step(sph_plan* P, sph_state* s, int32_t nsteps, const sph_state* c
     if (P->rk_stages > 0) {
         for (int32_t t = 0; t < nsteps; ++t) {
             if (ckpt && t % every == 0) RC_TRY((copy_state<T, D>(P, user_state<T, D>(&ckpt[t / every]), user, st)));
-            RC_TRY((rk_step<T, D>(P, user, st)));
+            RC_TRY((rk_step<T, D>(P, user, user, st)));
         }
         return SPH_OK;
     }
@@ -1195,11 +1231,8 @@ sph_status do_rollout_backward(sph_plan* P, const sph_state* ckpt, int32_t nstep
         for (int32_t seg = nseg - 1; seg >= 0; --seg) {
             const int32_t len = std::min(every, nsteps - seg * every);
             RC_TRY((copy_state<T, D>(P, rk_block<T, D>(P, P->o_rkTape, 0), user_state<T, D>(&ckpt[seg]), st)));
-            for (int32_t t = 0; t + 1 < len; ++t) {
-                RC_TRY((copy_state<T, D>(P, rk_block<T, D>(P, P->o_rkTape, t + 1), rk_block<T, D>(P, P->o_rkTape, t),
-                                         st)));
-                RC_TRY((rk_step<T, D>(P, rk_block<T, D>(P, P->o_rkTape, t + 1), st)));
-            }
+            for (int32_t t = 0; t + 1 < len; ++t)
+                RC_TRY((rk_step<T, D>(P, rk_block<T, D>(P, P->o_rkTape, t), rk_block<T, D>(P, P->o_rkTape, t + 1), st)));
             for (int32_t t = len - 1; t >= 0; --t)
                 RC_TRY((rk_step_adjoint<T, D>(P, rk_block<T, D>(P, P->o_rkTape, t), c, st)));
         }

@@ -629,33 +629,31 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
     }
 }
 
-// A state in original order gathered into the particle order of a slot that is already sorted
-// and has lists (a later stage of a multistage step, with the lists of the step's first stage):
-// the sorted state and the packed records as k_order_gather writes them, and the displacement
-// since the lists were built checked against its half skin.
+// A particle's state put at sorted index d of a slot that is already sorted and has lists (a later stage
+// of a multistage step, with the lists of the step's first stage): the sorted state and the packed records
+// as k_sort_gather writes them, and the displacement since the lists were built checked against its half
+// skin.
 template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_repack(int64_t N, const int32_t* __restrict__ orig, StatePtrs<T, DIM> src,
-                                                StatePtrs<T, DIM> dst, vec4_t<T>* __restrict__ jd0,
-                                                vec4_t<T>* __restrict__ jd1, const vec4_t<T>* __restrict__ uref,
-                                                const int32_t* __restrict__ psim,
-                                                const SimConst<T>* __restrict__ sims, int32_t* __restrict__ status)
+struct StageSlot {
+    const int32_t* orig;
+    StatePtrs<T, DIM> state;
+    vec4_t<T>* jd0;   // null: the slot holds the stage's state already
+    vec4_t<T>* jd1;
+    const vec4_t<T>* uref;
+};
+
+template <typename T, int DIM>
+__device__ __forceinline__ void put_stage(const StageSlot<T, DIM>& slot, int64_t d, const SimConst<T>& S, const T* x,
+                                          const T* v, T rho, int32_t* __restrict__ status)
 {
-    int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= N) return;
-    const int s = psim[d];
-    const SimConst<T>& S = sims[s];
-    const int p = orig[d];
-    T x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, u[3] = {0, 0, 0};
+    T u[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
-        x[k] = src.x[k][p];
-        v[k] = src.v[k][p];
-        dst.x[k][d] = x[k];
-        dst.v[k][d] = v[k];
+        slot.state.x[k][d] = x[k];
+        slot.state.v[k][d] = v[k];
         u[k] = wrap_pos(isfinite(x[k]) ? x[k] : T(0), S.L, S.invL);
     }
-    const T rho = src.rho[p];
-    dst.rho[d] = rho;
+    slot.state.rho[d] = rho;
     const T V = S.m * fast_rcp(rho);
     const T pr = tait(S, rho);
     const T pV = pr * V;
@@ -667,9 +665,9 @@ __global__ __launch_bounds__(256) void k_repack(int64_t N, const int32_t* __rest
         a.x = u[0]; a.y = u[1]; a.z = V; a.w = pV;
         b.x = v[0]; b.y = v[1]; b.z = rho; b.w = pr;
     }
-    jd0[d] = a;
-    jd1[d] = b;
-    const vec4_t<T> ref = uref[d];
+    slot.jd0[d] = a;
+    slot.jd1[d] = b;
+    const vec4_t<T> ref = slot.uref[d];
     const T rr[3] = {ref.x, ref.y, ref.z};
     T d2 = T(0);
 #pragma unroll
@@ -678,7 +676,26 @@ __global__ __launch_bounds__(256) void k_repack(int64_t N, const int32_t* __rest
         dk -= S.L * rint(dk * S.invL);
         d2 += dk * dk;
     }
-    if (!(d2 <= ref.w * ref.w)) atomicOr(&status[s], kFlagSkin);
+    if (!(d2 <= ref.w * ref.w)) atomicOr(status, kFlagSkin);
+}
+
+// The same for a state in original order.
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_repack(int64_t N, StatePtrs<T, DIM> src, StageSlot<T, DIM> slot,
+                                                const int32_t* __restrict__ psim,
+                                                const SimConst<T>* __restrict__ sims, int32_t* __restrict__ status)
+{
+    int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= N) return;
+    const int s = sim_of(psim, d);
+    const int p = slot.orig[d];
+    T x[3] = {0, 0, 0}, v[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        x[k] = src.x[k][p];
+        v[k] = src.v[k][p];
+    }
+    put_stage<T, DIM>(slot, d, sims[s], x, v, src.rho[p], &status[s]);
 }
 
 template <typename T, int DIM>
@@ -1953,14 +1970,9 @@ struct LinComb {
 };
 
 template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_lincomb(int64_t N, LinComb<T, DIM> L, const int32_t* __restrict__ psim,
-                                                 const SimConst<T>* __restrict__ sims)
+__device__ __forceinline__ void lincomb_at(const LinComb<T, DIM>& L, int64_t i, T dt, T* x, T* v, T& r)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const T dt = sims[psim[i]].dt;
     const T s0 = L.s0_dt ? L.s0 * dt : L.s0;
-    T x[3], v[3], r;
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
         x[k] = s0 * L.base.x[k][i];
@@ -1982,6 +1994,49 @@ __global__ __launch_bounds__(256) void k_lincomb(int64_t N, LinComb<T, DIM> L, c
         L.out.v[k][i] = v[k];
     }
     L.out.rho[i] = r;
+}
+
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_lincomb(int64_t N, LinComb<T, DIM> L, const int32_t* __restrict__ psim,
+                                                 const SimConst<T>* __restrict__ sims)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    T x[3], v[3], r;
+    lincomb_at<T, DIM>(L, i, sims[sim_of(psim, i)].dt, x, v, r);
+}
+
+// A stage state formed (in original order, for the later stages and the adjoint) and put into the slot
+// whose lists it keeps, in one pass.  Bound: launch and memory latency (2D 151^2: 3.9 us; as k_lincomb and
+// k_repack, two launches of 3.5).
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_stage_state(int64_t N, LinComb<T, DIM> L, StageSlot<T, DIM> slot,
+                                                     const int32_t* __restrict__ psim,
+                                                     const SimConst<T>* __restrict__ sims,
+                                                     int32_t* __restrict__ status)
+{
+    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= N) return;
+    const int s = sim_of(psim, d);
+    const SimConst<T>& S = sims[s];
+    T x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, r;
+    lincomb_at<T, DIM>(L, slot.orig[d], S.dt, x, v, r);
+    put_stage<T, DIM>(slot, d, S, x, v, r, &status[s]);
+}
+
+// dst = src, every field: one launch (2D 151^2: 3.6 us), where a copy per array took 2 D + 1 of 2.2 and the
+// gaps between them.
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_copy_state(int64_t N, StatePtrs<T, DIM> src, StatePtrs<T, DIM> dst)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        dst.x[k][i] = src.x[k][i];
+        dst.v[k][i] = src.v[k][i];
+    }
+    dst.rho[i] = src.rho[i];
 }
 
 // ---------------------------------------------------------------- symplectic Euler
@@ -2128,6 +2183,35 @@ __global__ __launch_bounds__(256) void k_adj_prologue(int64_t N, const int32_t* 
         rb = S.dt * cot.rho[o];
     }
     jdA[q] = adjoint_record<T, DIM>(ab, rb, cur.rho[q]);
+}
+
+// A stage's cotangent formed (in original order, for the sweep that follows and the earlier stages), its
+// adjoint record, and, unless the slot holds it already, the stage's state put into the slot, in one pass
+// (2D 151^2: 4.3 us; as k_lincomb, k_repack and k_adj_prologue, three launches of 3.5, 3.5 and 2.8).
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_stage_cot(int64_t N, LinComb<T, DIM> L, StatePtrs<T, DIM> src,
+                                                   StageSlot<T, DIM> slot, vec4_t<T>* __restrict__ jdA,
+                                                   const int32_t* __restrict__ psim,
+                                                   const SimConst<T>* __restrict__ sims, int32_t* __restrict__ status)
+{
+    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= N) return;
+    const int s = sim_of(psim, d);
+    const SimConst<T>& S = sims[s];
+    const int p = slot.orig[d];
+    T kx[3], kv[3] = {0, 0, 0}, kr;
+    lincomb_at<T, DIM>(L, p, S.dt, kx, kv, kr);
+    const T rho = src.rho[p];
+    if (slot.jd0) {
+        T x[3] = {0, 0, 0}, v[3] = {0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) {
+            x[k] = src.x[k][p];
+            v[k] = src.v[k][p];
+        }
+        put_stage<T, DIM>(slot, d, S, x, v, rho, &status[s]);
+    }
+    jdA[d] = adjoint_record<T, DIM>(kv, kr, rho);
 }
 
 // Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
