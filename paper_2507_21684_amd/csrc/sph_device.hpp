@@ -801,7 +801,7 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
     // (written by the sort), and the list radius of a pair is H + h_i + h_j
     const vec4_t<T>* __restrict__ rec = PERPAIR ? href : jd0;
     __shared__ vec4_t<T> pu[65];
-    __shared__ int32_t uc_first[128];
+    __shared__ int32_t uc_delta[128];   // candidate m of stencil cell u is particle uc_delta[u] + m
     __shared__ int32_t uc_pref[129];
     __shared__ int32_t uc_code[128];
     __shared__ uint8_t uc_of[kCandTable];  // stencil cell of each of the first kCandTable candidates
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
         const int inc = wave_incl_scan(count);
         const int beg = carry + inc - count;
         if (u < 128) {
-            uc_first[u] = first;
+            uc_delta[u] = first - beg;
             uc_pref[u] = beg;
             uc_code[u] = code;
         }
@@ -873,23 +873,16 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
     if (lane == 0) uc_pref[ncu] = M;
     __syncthreads();
 
-    // candidate m of the stream: sorted index, position and periodic shift
-    auto fetch = [&](int m, int& j, vec4_t<T>& u, int& code) {
-        int lo;  // the stencil cell holding candidate m: the last one whose prefix is <= m
-        if (m < kCandTable) {
-            lo = uc_of[m];
-        } else {
-            lo = 0;
-            int hi = ncu - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (uc_pref[mid] <= m) lo = mid;
-                else hi = mid - 1;
-            }
+    // the stencil cell holding candidate m: the last one whose prefix is <= m
+    auto cell_of_candidate = [&](int m) {
+        if (m < kCandTable) return (int)uc_of[m];
+        int lo = 0, hi = ncu - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (uc_pref[mid] <= m) lo = mid;
+            else hi = mid - 1;
         }
-        j = uc_first[lo] + (m - uc_pref[lo]);
-        code = uc_code[lo];
-        u = rec[j];
+        return lo;
     };
 
     // sorted index of the unit's particle q (the two ranges in order)
@@ -906,20 +899,56 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
         for (int c0 = 0; c0 < M; c0 += 64 * NC) {
             int jc[NC], code[NC];
             T uj[NC][3], Aj[NC];
+            // Candidates past the stream are put out of every particle's reach (the squared distance
+            // overflows).  In 3D, where a wavefront goes through several tiles for few particles, the
+            // chunks' lookups and loads go side by side, with the last candidate in place of those past
+            // the stream; in 2D that costs registers and gains nothing (3D 40^3 75.1 and 70.7 us, 3D 64^3
+            // 195 and 189; the 2D batch 245 and 252).
+            if (DIM == 3) {
+                int m[NC];
 #pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                // past the stream: out of every particle's reach (the squared distance overflows)
-                vec4_t<T> un;
-                un.x = un.y = un.z = T(1e38);
-                un.w = T(0);
-                jc[k] = 0;
-                code[k] = 1 | (1 << 2) | (1 << 4);
-                code[k] <<= kStencilIdBits;
-                const int m = c0 + 64 * k + lane;
-                if (m < M) fetch(m, jc[k], un, code[k]);
-                uj[k][2] = T(0);
-                unpack_u<T, DIM>(un, uj[k]);
-                Aj[k] = SH + un.w;   // PERPAIR: H + h_j
+                for (int k = 0; k < NC; ++k) m[k] = c0 + 64 * k + lane < M ? c0 + 64 * k + lane : M - 1;
+                if (M <= kCandTable) {
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) code[k] = uc_of[m[k]];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) code[k] = cell_of_candidate(m[k]);
+                }
+                vec4_t<T> un[NC];
+#pragma unroll
+                for (int k = 0; k < NC; ++k) jc[k] = uc_delta[code[k]] + m[k];
+#pragma unroll
+                for (int k = 0; k < NC; ++k) un[k] = rec[jc[k]];
+                if (!inside) {
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) code[k] = uc_code[code[k]];
+                }
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    unpack_u<T, DIM>(un[k], uj[k]);
+                    if (c0 + 64 * k + lane >= M) uj[k][0] = T(1e38);
+                    Aj[k] = SH + un[k].w;   // PERPAIR: H + h_j
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    vec4_t<T> un;
+                    un.x = un.y = un.z = T(1e38);
+                    un.w = T(0);
+                    jc[k] = 0;
+                    code[k] = (1 | (1 << 2) | (1 << 4)) << kStencilIdBits;
+                    const int m = c0 + 64 * k + lane;
+                    if (m < M) {
+                        const int u = cell_of_candidate(m);
+                        jc[k] = uc_delta[u] + m;
+                        code[k] = uc_code[u];
+                        un = rec[jc[k]];
+                    }
+                    uj[k][2] = T(0);
+                    unpack_u<T, DIM>(un, uj[k]);
+                    Aj[k] = SH + un.w;
+                }
             }
             auto shift_of = [&](int k, int d) {
                 return T(((code[k] >> (kStencilIdBits + 2 * d)) & 3) - 1) * SL;
