@@ -129,7 +129,9 @@ struct sph_plan {
     // (members_cap places each), between the counting and the gather of a sort
     size_t o_cots = 0;
     int32_t members_cap = 0;
+    int32_t order_slots = 0;   // tape slots with room for order_before
     int adj_buf = 0, adj_ready = -1;
+    bool adj_sorted = false;   // the cotangents that go with adj_ready are in o_cots
     std::vector<SlotLayout> slot;
     // Every write of a slot's sorted state or lists gives the slot a new generation number; the
     // last sph_rhs or sph_step call records the slot holding the sort and lists of its input
@@ -220,6 +222,16 @@ T* wsp(const sph_plan* p, size_t off) { return reinterpret_cast<T*>(p->ws + off)
 
 // The particle -> simulation table, null for a plan of one simulation.
 const int32_t* sim_table(const sph_plan* P) { return P->nsims == 1 ? nullptr : wsp<int32_t>(P, P->o_psim); }
+
+// Each particle's place in the order that the sort into `slot` started from, for the adjoint's hand-over to
+// the step before; null for a slot without room for it.  Plans with exact lists sort every step and have
+// no use for the references of list reuse (o_uref), whose room the first of them share.
+constexpr int kOrderSlots = 2;   // further ones
+int32_t* order_before(const sph_plan* P, int slot)
+{
+    if (P->filter || slot >= P->order_slots) return nullptr;
+    return wsp<int32_t>(P, P->o_uref) + (size_t)slot * P->N;
+}
 
 // Where the cells' members are collected between the counting and the gather of a sort.
 CellMembers cell_members(const sph_plan* P)
@@ -433,7 +445,7 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
         N, (int32_t)P->ncell, cell_count, cell_start, ticket, cell_of, cell_members(P), orig_in, src,
         ws_state<T, D>(P, L.SA), orig_out, wsp<vec4_t<T>>(P, L.jd0), wsp<vec4_t<T>>(P, L.jd1), sim_table(P), simc,
         P->filter ? wsp<vec4_t<T>>(P, P->o_uref) : nullptr, (T)(P->speed_skins ? kSkinFloor : 1.0),
-        (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0));
+        (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0), order_before(P, slot));
     LAUNCH_CHECK("sort_gather");
     return SPH_OK;
 }
@@ -634,10 +646,10 @@ void launch_renorm_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, S
 // With vjp, the update function's VJP instead: cot holds the cotangents (kx, ka, krho) of
 // (v, a, drho/dt) on entry and (xbar, vbar, rhobar) on exit.
 // With has_records the caller has written the slot's adjoint records.
-// With next_slot >= 0 (a tape slot sharing this slot's particle order, whose adjoint runs next),
-// the sweep also writes that step's prologue records into the other buffer and the cotangents in
-// sorted order, and the next call skips its prologue and reads those; the last sweep of such a
-// chain writes cot.
+// With next_slot >= 0 (a tape slot whose adjoint runs next, and whose particle order is this slot's or
+// known here),
+// the sweep also writes that step's prologue records into the other buffer, and the next call skips
+// its prologue.  Where the order is the same the cotangents go between the two in sorted order.
 template <typename T, int D>
 sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, bool vjp = false,
                    int next_slot = -1, bool has_records = false)
@@ -654,9 +666,11 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
     }
     P->adj_ready = -1;
     const bool fuse = next_slot >= 0 && !vjp && !P->renorm;
-    NextAdj<T> na{nullptr, nullptr};
+    const bool same_order = fuse && P->list_of[slot] == P->list_of[next_slot];
+    NextAdj<T> na{nullptr, nullptr, nullptr};
     if (fuse)
-        na = NextAdj<T>{wsp<vec4_t<T>>(P, jdA_off(P, 1 - P->adj_buf)), ws_state<T, D>(P, P->slot[next_slot].SA).rho};
+        na = NextAdj<T>{wsp<vec4_t<T>>(P, jdA_off(P, 1 - P->adj_buf)), ws_state<T, D>(P, P->slot[next_slot].SA).rho,
+                        same_order ? nullptr : order_before(P, slot)};
     const SlotLayout& LL = P->slot[P->list_of[slot]];
     if (P->renorm) {
         // the step's renormalised gradients and L_i, recomputed from its sorted state
@@ -669,12 +683,14 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
     }
     {
         const StatePtrs<T, D> sorted = ws_state<T, D>(P, P->o_cots);
-        const StatePtrs<T, D> cin = ready ? sorted : cot, cout = fuse ? sorted : cot;
+        const bool cin_sorted = ready && P->adj_sorted;
+        const StatePtrs<T, D> cin = cin_sorted ? sorted : cot, cout = same_order ? sorted : cot;
+        P->adj_sorted = same_order;
         ProfScope prof(P, st, SPH_KERN_ADJOINT, true);
         switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
-        case 2: launch_adj<T, D, 2>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
-        case 8: launch_adj<T, D, 8>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
-        default: launch_adj<T, D, 4>(P, L, LL, cin, ready, cout, fuse, st, vjp, &prof, na); break;
+        case 2: launch_adj<T, D, 2>(P, L, LL, cin, cin_sorted, cout, same_order, st, vjp, &prof, na); break;
+        case 8: launch_adj<T, D, 8>(P, L, LL, cin, cin_sorted, cout, same_order, st, vjp, &prof, na); break;
+        default: launch_adj<T, D, 4>(P, L, LL, cin, cin_sorted, cout, same_order, st, vjp, &prof, na); break;
         }
         LAUNCH_CHECK("adj_sweep");
     }
@@ -1187,6 +1203,13 @@ sph_status do_step_adjoint(sph_plan* P, const sph_state* sn, sph_state* cot, hip
     return adjoint<T, D>(P, 0, user_state<T, D>(cot), st);
 }
 
+// Whether the adjoint of step t (in tape slot t) can prepare that of step t - 1: no sort happened in
+// between, or it kept the order before it.
+bool hands_over(const sph_plan* P, int t)
+{
+    return t > 0 && (P->list_of[t] == P->list_of[t - 1] || order_before(P, t) != nullptr);
+}
+
 // Checkpointed backward pass: segments in reverse; each is recomputed from its checkpoint
 // with its sorted states and neighbour lists kept in the tape, then its adjoint steps run in
 // reverse on the taped data.
@@ -1243,7 +1266,7 @@ sph_status do_rollout_backward(sph_plan* P, const sph_state* ckpt, int32_t nstep
         P->adj_buf = 0;
         P->adj_ready = -1;
         for (int32_t t = nsteps - 1; t >= 0; --t) {
-            const int next = (t > 0 && P->list_of[t] == P->list_of[t - 1]) ? t - 1 : -1;
+            const int next = hands_over(P, t) ? t - 1 : -1;
             RC_TRY((adjoint<T, D>(P, t, c, st, false, next)));
         }
         return SPH_OK;
@@ -1255,8 +1278,7 @@ sph_status do_rollout_backward(sph_plan* P, const sph_state* ckpt, int32_t nstep
         P->adj_buf = 0;
         P->adj_ready = -1;
         for (int32_t t = len - 1; t >= 0; --t) {
-            // the step before shares this state's particle order when no sort happened in between
-            const int next = (t > 0 && P->list_of[t] == P->list_of[t - 1]) ? t - 1 : -1;
+            const int next = hands_over(P, t) ? t - 1 : -1;
             RC_TRY((adjoint<T, D>(P, t, c, st, false, next)));
         }
     }
@@ -1659,7 +1681,8 @@ sph_status sph_plan_create(const sph_params* sims, int32_t nsims, const int64_t*
     P->o_pairs = take(8 * (size_t)kPairSlots * kPairStride);
     P->o_ticket = take(4);
     P->o_poll = take(8 + 4 * (size_t)nsims);
-    P->o_uref = take(V4 * N);
+    P->order_slots = (int32_t)std::min<size_t>((size_t)P->nslots, V4 / 4 + kOrderSlots);
+    P->o_uref = take(P->filter ? V4 * N : std::max<size_t>(V4 * N, 4 * N * (size_t)P->order_slots));
     P->slot.resize((size_t)P->nslots);
     P->list_of.assign((size_t)P->nslots, 0);
     P->slot_gen.assign((size_t)P->nslots, 0);

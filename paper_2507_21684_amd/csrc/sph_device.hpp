@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
                                                       const int32_t* __restrict__ psim,
                                                       const SimConst<T>* __restrict__ sims,
                                                       vec4_t<T>* __restrict__ uref, T skin_floor,
-                                                      T skin_steps)
+                                                      T skin_steps, int32_t* __restrict__ before)
 {
     constexpr int kWaves = kSortThreads / 64;
     __shared__ int32_t quads[SCAN ? kSortScanCells / 4 : 1];
@@ -591,6 +591,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
     const T rho = src.rho[p];
     dst.rho[d] = rho;
     orig_out[d] = op;
+    if (before) before[d] = (int32_t)p;
     const T V = S.m * fast_rcp(rho);
     const T pr = tait(S, rho);
     const T pV = pr * V;
@@ -2246,12 +2247,14 @@ __global__ __launch_bounds__(256) void k_stage_cot(int64_t N, LinComb<T, DIM> L,
 // Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
 // (cin_sorted, cout_sorted): contiguous accesses, where the caller's order scatters them.
 // What the adjoint sweep of step t prepares for the adjoint of step t - 1 when both states share
-// the particle order (a step within one list-reuse interval): the prologue records of step t - 1
-// at the same sorted index, from the cotangents the sweep has just formed (null jdA: none).
+// the particle order (a step within one list-reuse interval), or when the sort of state t has kept each
+// particle's place in the order before it (`before`): the prologue records of step t - 1 at the particle's
+// index there, from the cotangents the sweep has just formed (null jdA: none).
 template <typename T>
 struct NextAdj {
     vec4_t<T>* jdA;
     const T* rho;   // densities of state t - 1, sorted order
+    const int32_t* before;   // null: the same order
 };
 
 template <typename T, int DIM>
@@ -2538,7 +2541,8 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
 #pragma unroll
         for (int d = 0; d < DIM; ++d) ab[d] = dt * (vn[d] + dt * xn[d]);
         const T rb = dt * rn;
-        na.jdA[k] = adjoint_record<T, DIM>(ab, rb, na.rho[k]);
+        const uint32_t q = na.before ? (uint32_t)na.before[k] : k;   // index in state t - 1
+        na.jdA[q] = adjoint_record<T, DIM>(ab, rb, na.rho[q]);
     }
 }
 
