@@ -776,7 +776,7 @@ constexpr int kCandTable = 2048;
 // instead of one reads the particle's position and count once per tile and leaves the chunks' tests
 // independent of each other: 18 vector and about as many scalar instructions per test of 64
 // candidates became 13 and 6.  Measured, one chunk at a time against tiles: 3D 64^3 with skins 267
-// and 195 us, 3D 40^3 exact 110 and 75 us, the 512-simulation 2D batch 285 and 229 us.
+// and 195 us, 3D 40^3 exact 110 and 75 us, the 512-simulation 2D batch 285 and 250 us.
 // With GROUP (2D) a wavefront serves a group of 2 x 2 cells (cell slots c, c + 1, c + B,
 // c + B + 1 of a block, B = 4) over their 6 x 6 (or 4 x 4) union stencil, in the same lexicographic order:
 // a particle's own stencil cells are a sub-grid of it in the same relative order, and the extra
@@ -903,8 +903,8 @@ __global__ __launch_bounds__(64) void k_build_list(const int32_t* __restrict__ c
             // Candidates past the stream are put out of every particle's reach (the squared distance
             // overflows).  In 3D, where a wavefront goes through several tiles for few particles, the
             // chunks' lookups and loads go side by side, with the last candidate in place of those past
-            // the stream; in 2D that costs registers and gains nothing (3D 40^3 75.1 and 70.7 us, 3D 64^3
-            // 195 and 189; the 2D batch 245 and 252).
+            // the stream (3D 40^3 75.1 and 70.6 us, 3D 64^3 195 and 189); in 2D that takes 10 registers more
+            // and gains nothing (2D 151^2 9.5 and 9.7).
             if (DIM == 3) {
                 int m[NC];
 #pragma unroll
@@ -1709,8 +1709,10 @@ struct NextCells {
 // do); its data return is busy 93 to 100 % of a large launch, and a quarter fewer vector instructions
 // changed little by themselves.  Small launches are bound by a wavefront's own chain.  Measured, before
 // (a load per list entry, a test of every position against the count and of every pair against the
-// support) and now: 2D 32^2 FP64 13.5 and 9.0 us, 2D 101^2 8.2 and 7.4, 2D 256^2 15.0 and 13.9, 3D 47^3
-// 86.5 and 83.0, 3D 64^3 222 and 214, 3D 20^3 FP64 27.3 and 21, 512-simulation batch 335 and 325.
+// support) and now: 2D 32^2 FP64 13.5 and 8.9 us, 2D 101^2 8.2 and 7.1, 2D 256^2 15.0 and 13.7, 3D 47^3
+// 86.5 and 83.0, 3D 64^3 222 and 213, 3D 20^3 FP64 27.3 and 20.7, 512-simulation batch 335 and 328.
+// Registers: 80 in FP32 2D, six wavefronts per SIMD (one more register costs the batch 3 %), hence the
+// 32-bit indices.
 // Copying a workgroup's reach to LDS first (10 to 12 clocks a gather) took twice as long: the copy's 39 to 58
 // KB leave too few wavefronts per CU.
 template <typename T, int DIM, int MODE, int LPP, bool RENORM>
@@ -2301,8 +2303,8 @@ struct AdjNbr {
 //
 // Bound: the gathers, as in k_sweep, three records per neighbour.  Dropping the second adjoint record
 // (u and the density are in jd0 and jd1), the common factor Phi (62 vector instructions per pair, 80 before) and
-// the walk of the rows: 2D 101^2 9.4 and 9.0 us, 2D 256^2 18.4 and 17.3, 3D 47^3 140 and 125, 3D 64^3 318 and
-// 317, 3D 20^3 FP64 25.9 and 22.3, 512-simulation batch 439 and 406; with renormalisation, the second pass
+// the walk of the rows: 2D 101^2 9.4 and 9.1 us, 2D 256^2 18.4 and 17.2, 3D 47^3 140 and 125, 3D 64^3 318 and
+// 318, 3D 20^3 FP64 25.9 and 22.1, 512-simulation batch 439 and 407; with renormalisation, the second pass
 // (k_renorm_adj, 3D 32^3) 42.8 and 25.1.
 template <typename T>
 struct AdjSelf {
@@ -2636,7 +2638,7 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
                 const T z = fma(bk[d], vP, fma(Gk[d], vb, fma(bj[d], wQ, Gj[d] * wb)));
                 ax[q][d] = fma(g, z, fma(he, e[d], ax[q][d]));
             }
-            ar[q] = fma(-g, vb + wb * fma(irk, Q, T(1)), ar[q]);
+            ar[q] = fma(-g, fma(wb, fma(irk, Q, T(1)), vb), ar[q]);
         });
     };
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
