@@ -505,7 +505,7 @@ sph_status build_lists(sph_plan* P, int slot, hipStream_t st, bool exact = false
     return SPH_OK;
 }
 
-// Lanes per particle that a sweep runs with.  Eight lanes fill the GPU with a small plan; from two
+// Lanes per particle that a pass over the lists runs with.  Eight lanes fill the GPU with a small plan; from two
 // wavefronts per SIMD on, four are faster in FP32 2D, where a row is two turns of eight lanes' 32
 // positions and the second is mostly empty (24 uneven simulations, 110 000 particles: forward 25.1 us
 // against 28.2, adjoint 32.8 against 36.5).  Results do not depend on it.
@@ -576,7 +576,7 @@ sph_status sweep(sph_plan* P, int slot, T* drho, T* acc, T* rhosum, hipStream_t 
                          wsp<vec4_t<T>>(P, P->o_uref)};
     }
     if (P->renorm) {
-        switch (P->lpp_fwd) {
+        switch (sweep_lanes<T, D>(P, P->lpp_fwd)) {
         case 2: launch_renorm<T, D, 2>(P, L, LL, st, false); break;
         case 8: launch_renorm<T, D, 8>(P, L, LL, st, false); break;
         default: launch_renorm<T, D, 4>(P, L, LL, st, false); break;
@@ -674,7 +674,7 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
     const SlotLayout& LL = P->slot[P->list_of[slot]];
     if (P->renorm) {
         // the step's renormalised gradients and L_i, recomputed from its sorted state
-        switch (P->lpp_adj) {
+        switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
         case 2: launch_renorm<T, D, 2>(P, L, LL, st, true); break;
         case 8: launch_renorm<T, D, 8>(P, L, LL, st, true); break;
         default: launch_renorm<T, D, 4>(P, L, LL, st, true); break;
@@ -696,7 +696,7 @@ sph_status adjoint(sph_plan* P, int slot, StatePtrs<T, D> cot, hipStream_t st, b
     }
     if (P->renorm) {
         ProfScope prof(P, st, SPH_KERN_OTHER);
-        switch (P->lpp_adj) {
+        switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
         case 2: launch_renorm_adj<T, D, 2>(P, L, LL, cot, st); break;
         case 8: launch_renorm_adj<T, D, 8>(P, L, LL, cot, st); break;
         default: launch_renorm_adj<T, D, 4>(P, L, LL, cot, st); break;
@@ -798,7 +798,7 @@ sph_status do_shift(sph_plan* P, sph_state* s, double beta, hipStream_t st)
     RC_TRY((sort_into<T, D>(P, u, nullptr, 0, st)));
     RC_TRY((build_lists<T, D>(P, 0, st)));
     ProfScope prof(P, st, SPH_KERN_OTHER);
-    switch (P->lpp_fwd) {
+    switch (sweep_lanes<T, D>(P, P->lpp_fwd)) {
     case 2: launch_shift<T, D, 2>(P, u, (T)beta, st); break;
     case 8: launch_shift<T, D, 8>(P, u, (T)beta, st); break;
     default: launch_shift<T, D, 4>(P, u, (T)beta, st); break;
@@ -818,7 +818,7 @@ sph_status do_shift_adjoint(sph_plan* P, const sph_state* s, sph_state* cot, dou
     k_pack_xbar<T, D><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, c, wsp<int32_t>(P, P->slot[0].orig),
                                                            wsp<vec4_t<T>>(P, P->o_jdA));
     LAUNCH_CHECK("pack_xbar");
-    switch (P->lpp_adj) {
+    switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
     case 2: launch_shift_adj<T, D, 2>(P, c, (T)beta, st); break;
     case 8: launch_shift_adj<T, D, 8>(P, c, (T)beta, st); break;
     default: launch_shift_adj<T, D, 4>(P, c, (T)beta, st); break;
@@ -1401,7 +1401,7 @@ sph_status do_density_adjoint(sph_plan* P, const sph_state* s, const T* g, T* xb
     ProfScope prof(P, st, SPH_KERN_ADJOINT);
     k_gather_sorted<T><<<grid_for(P->N, 256), 256, 0, st>>>(P->N, g, wsp<int32_t>(P, L.orig), gs);
     LAUNCH_CHECK("gather_sorted");
-    switch (P->lpp_adj) {
+    switch (sweep_lanes<T, D>(P, P->lpp_adj)) {
     case 2: launch_density_adj<T, D, 2>(P, L, gs, xbar, st); break;
     case 8: launch_density_adj<T, D, 8>(P, L, gs, xbar, st); break;
     default: launch_density_adj<T, D, 4>(P, L, gs, xbar, st); break;

@@ -2379,12 +2379,12 @@ __device__ __forceinline__ void adj_pair(const PairConst<T>& c, const AdjSelf<T>
 }
 
 // Wavefronts per SIMD the adjoint sweep's registers are held to: in FP32 2D five (96 registers instead of
-// 113: the 512-simulation batch 399 us a launch against 463).  In 3D the same limit spills.
-template <typename T, int DIM>
-constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 ? 5 : 1;
+// 113: the 512-simulation batch 399 us a launch against 463).  In 3D and with RENORM the same limit spills.
+template <typename T, int DIM, bool RENORM>
+constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 && !RENORM ? 5 : 1;
 
 template <typename T, int DIM, int LPP, bool RENORM>
-__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM>))
+__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM, RENORM>))
 void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                    const int32_t* __restrict__ nbr_count,
                                                    const vec4_t<T>* __restrict__ jd0,
