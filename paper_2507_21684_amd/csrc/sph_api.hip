@@ -187,6 +187,7 @@ struct sph_plan {
         // the forward tape the captured step call leaves (ftape_n == 0: none)
         int32_t ftape_n, ftape_every;
         std::vector<uintptr_t> ftape_ckpt;
+        std::vector<int> list_of;   // the table the captured call left
     };
     bool graphs = false;
     std::vector<GraphEntry> gcache;
@@ -1320,9 +1321,10 @@ sph_status run_graphed(sph_plan* P, std::vector<uintptr_t> key, hipStream_t st, 
             g.used = ++P->gclock;
             HIP_TRY(hipGraphLaunch(g.exec, st));
             // the replay rewrites slots without the host bookkeeping of a direct call: every slot
-            // gets a new generation, and what the captured call left (a retained sort, a forward
-            // tape) is recorded again with them
+            // gets a new generation, and what the captured call left (the slots of its lists, a
+            // retained sort, a forward tape) is recorded again with them
             P->touch_all();
+            P->list_of = g.list_of;
             P->ftape = false;
             if (g.kept_slot >= 0) P->keep(g.kept_slot);
             if (g.ftape_n > 0) {
@@ -1368,7 +1370,7 @@ sph_status run_graphed(sph_plan* P, std::vector<uintptr_t> key, hipStream_t st, 
     for (int32_t t = 0; tape_left && t < P->ftape_n; ++t) tape_left = P->slot_gen[(size_t)t] == P->ftape_gen[(size_t)t];
     P->gcache.push_back({std::move(key), graph, exec, ++P->gclock, kept, tape_left ? P->ftape_n : 0,
                          tape_left ? P->ftape_every : 0,
-                         tape_left ? P->ftape_ckpt : std::vector<uintptr_t>()});
+                         tape_left ? P->ftape_ckpt : std::vector<uintptr_t>(), P->list_of});
     HIP_TRY(hipGraphLaunch(exec, st));
     return SPH_OK;
 }
@@ -2129,6 +2131,9 @@ sph_status sph_rollout_backward(sph_plan* P, const sph_state* ckpt, int32_t nste
     std::vector<uintptr_t> key = {2u, (uintptr_t)nsteps, (uintptr_t)ckpt_every, (uintptr_t)use_tape};
     key_state(key, cot);
     for (int32_t k = 0; k < nseg; ++k) key_state(key, &ckpt[k]);
+    // the adjoint steps on the forward's tape read the lists that the forward built, whose slots follow the
+    // reuse interval of that call, not today's
+    for (int32_t t = 0; use_tape && t < nsteps; ++t) key.push_back((uintptr_t)P->list_of[(size_t)t]);
     return run_graphed(P, std::move(key), (hipStream_t)stream, [&](hipStream_t st) {
         return DISPATCH(P, do_rollout_backward, P, ckpt, nsteps, ckpt_every, cot, st, use_tape);
     });
