@@ -1277,6 +1277,44 @@ __device__ __forceinline__ void list_tail(const int32_t* __restrict__ row, int w
     }
 }
 
+// A neighbour past the support (lists with a skin) has t = 0 and so adds zero without a test, but only
+// while its records are finite: 0 times an infinity is NaN.  A particle whose sums come out non-finite
+// therefore forms them again from the pairs within the support alone, one at a time and in the same order, so
+// that nothing outside the support reaches it.  (A test of the finished sums is a few instructions per
+// particle: the sweeps of the 512-simulation batch took 366 and 481 us without it and 367 and 480 with it,
+// those of 2D 101^2 6.5 and 8.1 against 6.7 and 8.3.)
+template <int LPP, typename REC, typename GATHER, typename PAIR>
+__device__ __forceinline__ void walk_again(const int32_t* __restrict__ row, int width, int n, int r, GATHER&& gather,
+                                           PAIR&& pair)
+{
+    n = n < width ? n : width;
+    for (int k0 = r; k0 < n; k0 += 8) {
+#pragma unroll
+        for (int m = 0; m < 8 / LPP; ++m) {
+            const int k = k0 + LPP * m;
+            if (k < n) {
+                REC rec;
+                gather(row[list_offset(k, width)], rec);
+                pair(m, rec);
+            }
+        }
+    }
+}
+
+// Whether a simulation's lists hold pairs past the support.
+template <typename T>
+__device__ __forceinline__ bool past_support(const SimConst<T>& S) { return S.HL2 > S.H2; }
+
+// An index as a value the compiler knows nothing of.  A pass that forms a particle's sums again loads
+// everything anew through one: with the first walk's values kept for it, the walk itself ran out of
+// registers (2D adjoint of the 512-simulation batch: 503 us a launch against 481).
+template <typename I>
+__device__ __forceinline__ I opaque(I v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Positions the lanes of a particle visit for a row of n entries.
 template <typename T, int LPP>
 __device__ __forceinline__ int positions_visited(int n, int width)
@@ -1362,7 +1400,7 @@ template <>
 __device__ __forceinline__ float positive_part<float>(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
 // t = 1 - r / H, zero from the support on: every pair term carries a power of t, so a listed pair past
-// the support (lists with a skin) adds exactly zero without a test.
+// the support (lists with a skin) whose records are finite adds exactly zero without a test.
 template <typename T>
 __device__ __forceinline__ T kernel_t(T r2, T invH)
 {
@@ -1522,63 +1560,89 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
     n = n < width ? n : width;
     const int32_t* row = nbr + i * (int64_t)width;
     RenormAcc<T, DIM> acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-        for (int a = 0; a < 6; ++a) acc[q].M[a] = T(0);
-        acc[q].g[0] = acc[q].g[1] = acc[q].g[2] = T(0);
-    }
     auto gather = [&](int j, RenormNbr<T, DIM>& nb) {
         nb.a = ldo(jd0, (uint32_t)j);
         if (DIM == 2) nb.b = ldo(jd1, (uint32_t)j);
+    };
+    auto clear = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+            for (int a = 0; a < 6; ++a) acc[q].M[a] = T(0);
+            acc[q].g[0] = acc[q].g[1] = acc[q].g[2] = T(0);
+        }
+    };
+    auto add = [&](T rho, T invH, const RenormNbr<T, DIM>& nb, const T* d, T r2, RenormAcc<T, DIM>& A) {
+        const T tt = kernel_t(r2, invH);
+        const T t2 = tt * tt;
+        const T rj = (DIM == 3) ? nb.a.w : nb.b.z;
+        const T f = pair_weight<T, DIM>(nb.a) * (t2 * t2) * (tt * fma(T(-5), tt, T(6)));
+        T fd[3];
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) fd[k] = f * d[k];
+        if (DIM == 2) {
+            A.M[0] = fma(-fd[0], d[0], A.M[0]);
+            A.M[1] = fma(-fd[0], d[1], A.M[1]);
+            A.M[2] = fma(-fd[1], d[1], A.M[2]);
+        } else {
+            A.M[0] = fma(-fd[0], d[0], A.M[0]);
+            A.M[1] = fma(-fd[0], d[1], A.M[1]);
+            A.M[2] = fma(-fd[0], d[2], A.M[2]);
+            A.M[3] = fma(-fd[1], d[1], A.M[3]);
+            A.M[4] = fma(-fd[1], d[2], A.M[4]);
+            A.M[5] = fma(-fd[2], d[2], A.M[5]);
+        }
+        const T dr = rj - rho;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) A.g[k] = fma(dr, fd[k], A.g[k]);
     };
     auto pairs = [&](auto image, auto walk) {
         walk([&](int q, RenormNbr<T, DIM>& nb) {
             T d[3] = {0, 0, 0};
             const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
-            const T tt = kernel_t(r2, c.invH);
-            const T t2 = tt * tt;
-            const T rj = (DIM == 3) ? nb.a.w : nb.b.z;
-            const T f = pair_weight<T, DIM>(nb.a) * (t2 * t2) * (tt * fma(T(-5), tt, T(6)));
-            RenormAcc<T, DIM>& A = acc[q];
-            T fd[3];
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) fd[k] = f * d[k];
-            if (DIM == 2) {
-                A.M[0] = fma(-fd[0], d[0], A.M[0]);
-                A.M[1] = fma(-fd[0], d[1], A.M[1]);
-                A.M[2] = fma(-fd[1], d[1], A.M[2]);
-            } else {
-                A.M[0] = fma(-fd[0], d[0], A.M[0]);
-                A.M[1] = fma(-fd[0], d[1], A.M[1]);
-                A.M[2] = fma(-fd[0], d[2], A.M[2]);
-                A.M[3] = fma(-fd[1], d[1], A.M[3]);
-                A.M[4] = fma(-fd[1], d[2], A.M[4]);
-                A.M[5] = fma(-fd[2], d[2], A.M[5]);
-            }
-            const T dr = rj - rhoi;
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) A.g[k] = fma(dr, fd[k], A.g[k]);
+            add(rhoi, c.invH, nb, d, r2, acc[q]);
         });
     };
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, RenormNbr<T, DIM>>(row, width, n, r, (int)i, gather, pair); };
     auto tail = [&](auto&& pair) { list_tail<LPP, RenormNbr<T, DIM>>(row, width, n, r, (int)i, gather, pair); };
+    const T scale = (DIM == 3) ? c.kGF * S.m : c.kGF;
+    T M[6], g[3] = {0, 0, 0}, tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
+#pragma unroll
+        for (int e = 0; e < NM; ++e) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].M[e];
+            M[e] = scale * combine_leaves<LPP>(tmp);
+            sum += fabs(M[e]);
+        }
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].g[k];
+            g[k] = scale * combine_leaves<LPP>(tmp);
+            sum += fabs(g[k]);
+        }
+        return sum;
+    };
+    clear();
     if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    const T scale = (DIM == 3) ? c.kGF * S.m : c.kGF;
-    T M[6], g[3] = {0, 0, 0}, tmp[NQ];
-#pragma unroll
-    for (int e = 0; e < NM; ++e) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].M[e];
-        M[e] = scale * combine_leaves<LPP>(tmp);
-    }
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].g[k];
-        g[k] = scale * combine_leaves<LPP>(tmp);
+    if (!isfinite(combine()) && past_support(sims[psim[opaque(i)]])) {
+        const int64_t i2 = opaque(i);
+        const SimConst<T>& S2 = sims[psim[i2]];
+        const T invH2 = S2.invH, rho2 = (DIM == 3) ? rho3[i2] : jd1[i2].z;
+        T u2[3] = {0, 0, 0};
+        unpack_u<T, DIM>(jd0[i2], u2);
+        clear();
+        walk_again<LPP, RenormNbr<T, DIM>>(
+            nbr + i2 * width, width, nbr_count[i2], r, gather, [&](int q, RenormNbr<T, DIM>& nb) {
+                T d[3] = {0, 0, 0};
+                const T r2 = r2_exact<T, DIM>(u2, nb.a, S2.L, S2.invL, d);
+                if (r2 < S2.H2) add(rho2, invH2, nb, d, r2, acc[q]);
+            });
+        combine();
     }
     if (r != 0) return;
     T L[6] = {0, 0, 0, 0, 0, 0}, G[3] = {0, 0, 0};
@@ -1623,6 +1687,13 @@ struct FwdNbr {
     }
 };
 
+template <typename T>
+struct FwdSelf {
+    T u[3], v[3];
+    T rho, p;
+    T G[3];   // renormalised density gradient
+};
+
 // Forward pair terms of (i, j), added to acc:
 //   a_i    += ((alpha H c0 rho0 pi_ij - p_i) V_j - p_j V_j) gW
 //   drho_i += V_j (v_i - v_j).gW     (times rho_i later)   and   V_j (rho_i - rho_j) x_ij.gW / (r^2 + eps H^2)
@@ -1633,13 +1704,13 @@ struct FwdNbr {
 // pair).  In 2D jd0 = (u, V, p V) and jd1 = (v, rho, p), and V_j gW is formed per pair.  Two records
 // per neighbour either way: the sweep is bound by its gathers, not by arithmetic.  d and r2 are the
 // pair vector x_ij and its square.  The particle itself (also in the places past its count) has d = 0,
-// equal velocities and densities, and adds exactly zero; a neighbour past the support has t = 0.  No
-// implicit contraction: the products that are fused are written as fma, so a pair rounds the same in
+// equal velocities and densities, and adds exactly zero; a neighbour past the support has t = 0 (and see
+// walk_again).  No implicit contraction: the products that are fused are written as fma, so a pair rounds the same in
 // every copy of the loop.
 template <typename T, int DIM, bool RHOSUM, bool RENORM>
-__device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T rhoi, T pi,
-                                         const FwdNbr<T, DIM, RENORM>& nb, const T* Gi, const T* d, T r2,
-                                         int self, FwdAcc<T, DIM>& acc)
+__device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const FwdSelf<T>& K,
+                                         const FwdNbr<T, DIM, RENORM>& nb, const T* d, T r2, int self,
+                                         FwdAcc<T, DIM>& acc)
 {
 #pragma clang fp contract(off)
     T vj[3];
@@ -1652,9 +1723,9 @@ __device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T r
         Vj = nb.a.z; pVj = nb.a.w;
         vj[0] = nb.b.x; vj[1] = nb.b.y; rhoj = nb.b.z;
     }
-    T ue = (vi[0] - vj[0]) * d[0];
+    T ue = (K.v[0] - vj[0]) * d[0];
 #pragma unroll
-    for (int k = 1; k < DIM; ++k) ue = fma(vi[k] - vj[k], d[k], ue);
+    for (int k = 1; k < DIM; ++k) ue = fma(K.v[k] - vj[k], d[k], ue);
     const T q = fast_sqrt(r2) * c.invH;
     const T t = positive_part(T(1) - q);
     const T t2 = t * t;
@@ -1665,25 +1736,25 @@ __device__ __forceinline__ void fwd_pair(const PairConst<T>& c, const T* vi, T r
     if (RENORM) {
         // V_j (G_i + G_j) . grad_i W_ij of the renormalised diffusion
         const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z};
-        sg = (Gi[0] + Gj[0]) * d[0];
+        sg = (K.G[0] + Gj[0]) * d[0];
 #pragma unroll
-        for (int k = 1; k < DIM; ++k) sg = fma(Gi[k] + Gj[k], d[k], sg);
+        for (int k = 1; k < DIM; ++k) sg = fma(K.G[k] + Gj[k], d[k], sg);
     }
     if (DIM == 3) {
         const T g = (Vj * t4) * (t * fma(T(-5), t, T(6)));   // 5 q + 1 = 6 - 5 t
-        const T cg = fma(c.cA, pij, -(pi + pVj)) * g;
+        const T cg = fma(c.cA, pij, -(K.p + pVj)) * g;
 #pragma unroll
         for (int k = 0; k < DIM; ++k) acc.ax[k] = fma(cg, d[k], acc.ax[k]);
         acc.rdv = fma(g, ue, acc.rdv);
-        acc.rdd = fma((rhoi - rhoj) * (r2 * inv), g, acc.rdd);
+        acc.rdd = fma((K.rho - rhoj) * (r2 * inv), g, acc.rdd);
         if (RENORM) acc.rdg = fma(g, sg, acc.rdg);
     } else {
         const T gF = c.kGF * (t4 * t * fma(T(5), q, T(1)));  // grad W = gF x_ij
-        const T cg = fma(fma(c.cA, pij, -pi), Vj, -pVj) * gF;
+        const T cg = fma(fma(c.cA, pij, -K.p), Vj, -pVj) * gF;
 #pragma unroll
         for (int k = 0; k < DIM; ++k) acc.ax[k] = fma(cg, d[k], acc.ax[k]);
         acc.rdv = fma(Vj, gF * ue, acc.rdv);
-        acc.rdd = fma(Vj * (rhoi - rhoj), gF * r2 * inv, acc.rdd);
+        acc.rdd = fma(Vj * (K.rho - rhoj), gF * r2 * inv, acc.rdd);
         if (RENORM) acc.rdg = fma(Vj, gF * sg, acc.rdg);
     }
     if (RHOSUM) {
@@ -1738,32 +1809,40 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     if (i < N) {
     const int s = sim_of(psim, i);
     FwdAcc<T, DIM> acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
-        acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
-    }
     const PairConst<T> c = pair_const_of(sims, s);
-    const vec4_t<T> ra = jd0[i], rb = jd1[i];
-    T ui[3] = {0, 0, 0};
-    unpack_u<T, DIM>(ra, ui);
-    const T vi[3] = {rb.x, rb.y, (DIM == 3) ? rb.z : T(0)};
-    const T rhoi = (DIM == 3) ? ra.w : rb.z;
-    const T pi = rb.w;
-    T Gi[3] = {0, 0, 0};
-    if (RENORM) {
-        const vec4_t<T> g = jdG[i];
-        Gi[0] = g.x;
-        Gi[1] = g.y;
-        Gi[2] = g.z;
-    }
+    auto load_self = [&](uint32_t i0, FwdSelf<T>& K0) {
+        const vec4_t<T> a = jd0[i0], b = jd1[i0];
+        K0.u[2] = K0.v[2] = T(0);
+        unpack_u<T, DIM>(a, K0.u);
+        K0.v[0] = b.x;
+        K0.v[1] = b.y;
+        if (DIM == 3) K0.v[2] = b.z;
+        K0.rho = (DIM == 3) ? a.w : b.z;
+        K0.p = b.w;
+        K0.G[0] = K0.G[1] = K0.G[2] = T(0);
+        if (RENORM) {
+            const vec4_t<T> g = jdG[i0];
+            K0.G[0] = g.x;
+            K0.G[1] = g.y;
+            K0.G[2] = g.z;
+        }
+    };
+    FwdSelf<T> K;
+    load_self(i, K);
     int n = nbr_count[i];
     n = n < width ? n : width;
     const int32_t* row = nbr + (int64_t)i * width;
     // the particle's own entry and the places past the count, at r2 = 0, are counted by the loop
     if (r == 0 && n > 0) accepted = n - positions_visited<T, LPP>(n, width) - 1;
-    // W(0) = 1 of the particle itself
-    if (MODE == kModeRhs && r == 0 && n > 0) acc[0].rs = T(1);
+    auto clear = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
+            acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
+        }
+        // W(0) = 1 of the particle itself
+        if (MODE == kModeRhs && r == 0 && n > 0) acc[0].rs = T(1);
+    };
     using Nbr = FwdNbr<T, DIM, RENORM>;
     auto gather = [&](int j, Nbr& nb) {
         nb.j = j;
@@ -1774,39 +1853,58 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     auto pairs = [&](auto image, auto walk) {
         walk([&](int q, Nbr& nb) {
             T d[3];
-            const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(K.u, nb.a, c.L, c.invL, d);
             accepted += r2 < c.H2 ? 1 : 0;
-            fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, vi, rhoi, pi, nb, Gi, d, r2, (int)i, acc[q]);
+            fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, K, nb, d, r2, (int)i, acc[q]);
         });
     };
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
     auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
-    if (wave_inside<T, DIM>(ui, c.H, c.L)) pairs(std::false_type{}, groups);
+    T ax[3] = {0, 0, 0}, rdv = 0, rdd = 0, rs = 0, rdg = 0;
+    T tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].ax[k];
+            ax[k] = combine_leaves<LPP>(tmp);
+            sum += fabs(ax[k]);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdv;
+        rdv = combine_leaves<LPP>(tmp);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdd;
+        rdd = combine_leaves<LPP>(tmp);
+        if (MODE == kModeRhs) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rs;
+            rs = combine_leaves<LPP>(tmp);
+        }
+        if (RENORM) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdg;
+            rdg = combine_leaves<LPP>(tmp);
+        }
+        return sum + fabs(rdv) + fabs(rdd) + fabs(rdg);
+    };
+    clear();
+    if (wave_inside<T, DIM>(K.u, c.H, c.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    T ax[3] = {0, 0, 0}, rs = 0, rdg = 0;
-    T tmp[NQ];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].ax[k];
-        ax[k] = combine_leaves<LPP>(tmp);
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdv;
-    T rdv = combine_leaves<LPP>(tmp);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdd;
-    T rdd = combine_leaves<LPP>(tmp);
-    if (MODE == kModeRhs) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rs;
-        rs = combine_leaves<LPP>(tmp);
-    }
-    if (RENORM) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdg;
-        rdg = combine_leaves<LPP>(tmp);
+    if (!isfinite(combine()) && past_support(sims[s])) {
+        const uint32_t i2 = opaque(i);
+        const PairConst<T> c2 = pair_const(sims[opaque(s)]);
+        FwdSelf<T> K2;
+        load_self(i2, K2);
+        clear();
+        walk_again<LPP, Nbr>(nbr + (int64_t)i2 * width, width, nbr_count[i2], r, gather, [&](int q, Nbr& nb) {
+            T d[3];
+            const T r2 = r2_exact<T, DIM>(K2.u, nb.a, c2.L, c2.invL, d);
+            if (r2 < c2.H2) fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c2, K2, nb, d, r2, (int)i2, acc[q]);
+        });
+        combine();
     }
     if (r == 0) {
     const SimConst<T>& S = sims[s];
@@ -1819,12 +1917,12 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
         rdd = scale * rdd;
         rdg = scale * rdg;
     }
-    const T invrho = fast_rcp(rhoi);
+    const T invrho = fast_rcp(K.rho);
     T a[3];
 #pragma unroll
     for (int k = 0; k < DIM; ++k) a[k] = ax[k] * invrho;
     // renormalised diffusion: -delta H c0 sum_j V_j (G_i + G_j) . grad_i W_ij, cD = 2 delta H c0
-    const T drho = RENORM ? rhoi * rdv + S.cD * rdd - T(0.5) * S.cD * rdg : rhoi * rdv + S.cD * rdd;
+    const T drho = RENORM ? K.rho * rdv + S.cD * rdd - T(0.5) * S.cD * rdg : K.rho * rdv + S.cD * rdd;
     if (MODE == kModeStep) {
         bool bad = !isfinite(drho);
         const T dt = S.dt;
@@ -1832,14 +1930,14 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
         T xn[3] = {0, 0, 0}, vn[3] = {0, 0, 0};
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
-            vn[k] = vi[k] + dt * a[k];
+            vn[k] = K.v[k] + dt * a[k];
             xn[k] = cur.x[k][i] + dt * vn[k];
             dst.v[k][i] = vn[k];
             dst.x[k][i] = xn[k];
             bad = bad || !isfinite(vn[k]) || !isfinite(xn[k]);
             cc[k] = cell_coord(wrap_pos(isfinite(xn[k]) ? xn[k] : T(0), S.L, S.invL), S.cinv, S.nc);
         }
-        const T rhon = rhoi + dt * drho;
+        const T rhon = K.rho + dt * drho;
         dst.rho[i] = rhon;
         if (bad) atomicOr(&status[s], kFlagNonfinite);
         if (next.cell_count) {
@@ -1947,16 +2045,19 @@ __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, c
     n = n < width ? n : width;
     const int32_t* row = nbr + i * (int64_t)width;
     T acc[NQ][3];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
     auto gather = [&](int j, DensNbr<T>& nb) {
         nb.a = ldo(jd0, (uint32_t)j);
         nb.g = ldo(gs, (uint32_t)j);
     };
-    auto pairs = [&](auto image, auto walk) {
+    auto clear = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
+    };
+    auto pairs = [&](auto image, auto within, auto walk) {
         walk([&](int q, DensNbr<T>& nb) {
             T d[3] = {0, 0, 0};
             const T r2 = pair_vector<T, DIM, decltype(image)::value>(ui, nb.a, c.L, c.invL, d);
+            if (decltype(within)::value && !(r2 < c.H2)) return;
             const T tt = kernel_t(r2, c.invH);
             const T t2 = tt * tt;
             const T w = (gi + nb.g) * ((t2 * t2) * (tt * fma(T(-5), tt, T(6))));
@@ -1966,16 +2067,28 @@ __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, c
     };
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, DensNbr<T>>(row, width, n, r, (int)i, gather, pair); };
     auto tail = [&](auto&& pair) { list_tail<LPP, DensNbr<T>>(row, width, n, r, (int)i, gather, pair); };
-    if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, groups);
-    else pairs(std::true_type{}, groups);
-    pairs(std::true_type{}, tail);
     T out[3] = {0, 0, 0};
     T tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
+        for (int k = 0; k < DIM; ++k) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q][k];
-        out[k] = combine_leaves<LPP>(tmp);
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q][k];
+            out[k] = combine_leaves<LPP>(tmp);
+            sum += fabs(out[k]);
+        }
+        return sum;
+    };
+    clear();
+    if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, std::false_type{}, groups);
+    else pairs(std::true_type{}, std::false_type{}, groups);
+    pairs(std::true_type{}, std::false_type{}, tail);
+    if (!isfinite(combine()) && past_support(S)) {
+        clear();
+        pairs(std::true_type{}, std::true_type{},
+              [&](auto&& pair) { walk_again<LPP, DensNbr<T>>(row, width, n, r, gather, pair); });
+        combine();
     }
     if (r != 0) return;
     const int o = orig[i];
@@ -2406,32 +2519,27 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     if (k >= N) return;
     const int s = sim_of(psim, k);
     AdjAcc<T, DIM> acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) acc[q].gx[d] = acc[q].gv[d] = acc[q].Gb[d] = T(0);
-        acc[q].s1 = acc[q].s2 = T(0);
-    }
     const PairConst<T> c = pair_const_of(sims, s);
+    auto load_self = [&](int64_t k0, T* u, AdjSelf<T>& K0) {
+        const vec4_t<T> a = jd0[k0], b = jd1[k0], A = jdA[k0];
+        unpack_u<T, DIM>(a, u);
+        K0.v[0] = b.x; K0.v[1] = b.y; K0.v[2] = (DIM == 3) ? b.z : T(0);
+        K0.a[0] = A.x; K0.a[1] = A.y; K0.a[2] = (DIM == 3) ? A.z : T(0);
+        K0.rho = (DIM == 3) ? a.w : b.z;
+        K0.p = b.w;
+        K0.Q = (DIM == 3) ? A.w : A.z;
+        K0.R = (DIM == 3) ? A.w * a.w : A.w;
+        K0.G[0] = K0.G[1] = K0.G[2] = T(0);
+        if (RENORM) {
+            const vec4_t<T> g = jdG[k0];
+            K0.G[0] = g.x;
+            K0.G[1] = g.y;
+            K0.G[2] = g.z;
+        }
+    };
     T uk[3] = {0, 0, 0};
     AdjSelf<T> K;
-    {
-        const vec4_t<T> a = jd0[k], b = jd1[k], A = jdA[k];
-        unpack_u<T, DIM>(a, uk);
-        K.v[0] = b.x; K.v[1] = b.y; K.v[2] = (DIM == 3) ? b.z : T(0);
-        K.a[0] = A.x; K.a[1] = A.y; K.a[2] = (DIM == 3) ? A.z : T(0);
-        K.rho = (DIM == 3) ? a.w : b.z;
-        K.p = b.w;
-        K.Q = (DIM == 3) ? A.w : A.z;
-        K.R = (DIM == 3) ? A.w * a.w : A.w;
-    }
-    K.G[0] = K.G[1] = K.G[2] = T(0);
-    if (RENORM) {
-        const vec4_t<T> g = jdG[k];
-        K.G[0] = g.x;
-        K.G[1] = g.y;
-        K.G[2] = g.z;
-    }
+    load_self(k, uk, K);
     int n = nbr_count[k];
     n = n < width ? n : width;
     const int32_t* row = nbr + k * (int64_t)width;
@@ -2441,6 +2549,14 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
         nb.b = ldo(jd1, (uint32_t)j);
         nb.A = ldo(jdA, (uint32_t)j);
         if (RENORM) nb.G = ldo(jdG, (uint32_t)j);
+    };
+    auto clear = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) acc[q].gx[d] = acc[q].gv[d] = acc[q].Gb[d] = T(0);
+            acc[q].s1 = acc[q].s2 = T(0);
+        }
     };
     auto pairs = [&](auto image, auto walk) {
         walk([&](int q, Nbr& nb) {
@@ -2454,31 +2570,51 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
         sweep_list<(sizeof(T) == 8 || RENORM), LPP, Nbr>(row, width, n, r, (int)k, gather, pair);
     };
     auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
+    T gx[3] = {0, 0, 0}, gv[3] = {0, 0, 0}, Gb[3] = {0, 0, 0}, s1 = 0, s2 = 0;
+    T tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gx[d];
+            gx[d] = combine_leaves<LPP>(tmp);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gv[d];
+            gv[d] = combine_leaves<LPP>(tmp);
+            if (RENORM) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].Gb[d];
+                Gb[d] = combine_leaves<LPP>(tmp);
+            }
+            sum += fabs(gx[d]) + fabs(gv[d]) + fabs(Gb[d]);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s1;
+        s1 = combine_leaves<LPP>(tmp);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s2;
+        s2 = combine_leaves<LPP>(tmp);
+        return sum + fabs(s1) + fabs(s2);
+    };
+    clear();
     if (wave_inside<T, DIM>(uk, c.H, c.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    T gx[3] = {0, 0, 0}, gv[3] = {0, 0, 0}, Gb[3] = {0, 0, 0};
-    T tmp[NQ];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gx[d];
-        gx[d] = combine_leaves<LPP>(tmp);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gv[d];
-        gv[d] = combine_leaves<LPP>(tmp);
-        if (RENORM) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].Gb[d];
-            Gb[d] = combine_leaves<LPP>(tmp);
-        }
+    if (!isfinite(combine()) && past_support(sims[s])) {
+        const int64_t k2 = opaque(k);
+        const PairConst<T> c2 = pair_const(sims[opaque(s)]);
+        T u2[3] = {0, 0, 0};
+        AdjSelf<T> K2;
+        load_self(k2, u2, K2);
+        clear();
+        walk_again<LPP, Nbr>(nbr + k2 * width, width, nbr_count[k2], r, gather, [&](int q, Nbr& nb) {
+            T e[3];
+            const T r2 = r2_exact<T, DIM>(u2, nb.a, c2.L, c2.invL, e);
+            if (r2 < c2.H2) adj_pair<T, DIM, RENORM>(c2, K2, nb, e, r2, acc[q]);
+        });
+        combine();
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s1;
-    const T s1 = combine_leaves<LPP>(tmp);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s2;
-    const T s2 = combine_leaves<LPP>(tmp);
     if (r != 0) return;
     const SimConst<T>& S = sims[s];
     // the particle's factor of Phi = m / (rho_k rho_j) and the kernel constant (the neighbour's factor
@@ -2558,6 +2694,12 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
 //     xbar_k += V_k [gbar_j (G_j.w) + Jg G_j (gbar_j.e)] - V_k (rho_k - rho_j) Jg gbar_j
 //     rbar_k += -V_k (gbar_j.w) + (V_k / rho_k) [(rho_k - rho_j)(gbar_j.w) - (e.gbar_j)(G_j.w)]
 // added to the cotangents (original order).  Same list traversal and partial sums.
+template <typename T>
+struct RenormAdjSelf {
+    T u[3], G[3], b[3];   // position, G_k, gbar_k
+    T V, rho, ir;
+};
+
 template <typename T, int DIM>
 struct RenormAdjNbr {
     vec4_t<T> a, b, G, gb;
@@ -2587,20 +2729,26 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
     if (k >= N) return;
     const SimConst<T>& S = sims[psim[k]];
     const PairConst<T> c = pair_const(S);
-    const vec4_t<T> a0 = jd0[k];
-    T uk[3] = {0, 0, 0};
-    unpack_u<T, DIM>(a0, uk);
-    const T Vk = rec_volume<T, DIM>(a0, S.m);
-    const T rhok = (DIM == 3) ? a0.w : jd1[k].z;
-    const T irk = T(1) / rhok;
-    const vec4_t<T> g4 = jdG[k], b4 = gbar[k];
-    const T Gk[3] = {g4.x, g4.y, g4.z}, bk[3] = {b4.x, b4.y, b4.z};
+    auto load_self = [&](int64_t k0, RenormAdjSelf<T>& K0) {
+        const vec4_t<T> a = jd0[k0], g4 = jdG[k0], b4 = gbar[k0];
+        K0.u[2] = T(0);
+        unpack_u<T, DIM>(a, K0.u);
+        K0.V = rec_volume<T, DIM>(a, sims[psim[k0]].m);
+        K0.rho = (DIM == 3) ? a.w : jd1[k0].z;
+        K0.ir = T(1) / K0.rho;
+        K0.G[0] = g4.x; K0.G[1] = g4.y; K0.G[2] = g4.z;
+        K0.b[0] = b4.x; K0.b[1] = b4.y; K0.b[2] = b4.z;
+    };
+    RenormAdjSelf<T> K;
+    load_self(k, K);
     int n = nbr_count[k];
     n = n < width ? n : width;
     const int32_t* row = nbr + k * (int64_t)width;
     T ax[NQ][3], ar[NQ];
+    auto clear = [&]() {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
+        for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
+    };
     using Nbr = RenormAdjNbr<T, DIM>;
     auto gather = [&](int j, Nbr& nb) {
         nb.a = ldo(jd0, (uint32_t)j);
@@ -2608,54 +2756,76 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
         nb.G = ldo(jdG, (uint32_t)j);
         nb.gb = ldo(gbar, (uint32_t)j);
     };
+    auto add = [&](const RenormAdjSelf<T>& K0, T m, T invH, T hc, const Nbr& nb, const T* e, T r2, T* x, T& a) {
+        const T tt = kernel_t(r2, invH);
+        const T t2 = tt * tt;
+        const T t4 = t2 * t2;
+        const T g = t4 * (tt * fma(T(-5), tt, T(6)));   // Jg v = kGF (g v + h (e.v) e)
+        const T h = hc * t4;
+        const T Vj = rec_volume<T, DIM>(nb.a, m);
+        const T rhoj = (DIM == 3) ? nb.a.w : nb.b.z;
+        const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z}, bj[3] = {nb.gb.x, nb.gb.y, nb.gb.z};
+        T bke = K0.b[0] * e[0], bje = bj[0] * e[0], Gke = K0.G[0] * e[0], Gje = Gj[0] * e[0];
+#pragma unroll
+        for (int d = 1; d < DIM; ++d) {
+            Gke = fma(K0.G[d], e[d], Gke);
+            bke = fma(K0.b[d], e[d], bke);
+            Gje = fma(Gj[d], e[d], Gje);
+            bje = fma(bj[d], e[d], bje);
+        }
+        // own terms carry G_k.e + (rho_j - rho_k), the neighbour's G_j.e + (rho_j - rho_k)
+        const T drk = rhoj - K0.rho;
+        const T P = Gke + drk, Q = Gje + drk;
+        const T vP = Vj * P, vb = Vj * bke, wQ = K0.V * Q, wb = K0.V * bje;
+        const T he = h * fma(vb, P, wb * Q);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            const T z = fma(K0.b[d], vP, fma(K0.G[d], vb, fma(bj[d], wQ, Gj[d] * wb)));
+            x[d] = fma(g, z, fma(he, e[d], x[d]));
+        }
+        a = fma(-g, fma(wb, fma(K0.ir, Q, T(1)), vb), a);
+    };
     auto pairs = [&](auto image, auto walk) {
         walk([&](int q, Nbr& nb) {
             T e[3] = {0, 0, 0};
-            const T r2 = pair_vector<T, DIM, decltype(image)::value>(uk, nb.a, c.L, c.invL, e);
-            const T tt = kernel_t(r2, c.invH);
-            const T t2 = tt * tt;
-            const T t4 = t2 * t2;
-            const T g = t4 * (tt * fma(T(-5), tt, T(6)));   // Jg v = kGF (g v + h (e.v) e)
-            const T h = c.hc * t4;
-            const T Vj = rec_volume<T, DIM>(nb.a, S.m);
-            const T rhoj = (DIM == 3) ? nb.a.w : nb.b.z;
-            const T Gj[3] = {nb.G.x, nb.G.y, nb.G.z}, bj[3] = {nb.gb.x, nb.gb.y, nb.gb.z};
-            T bke = bk[0] * e[0], bje = bj[0] * e[0], Gke = Gk[0] * e[0], Gje = Gj[0] * e[0];
-#pragma unroll
-            for (int d = 1; d < DIM; ++d) {
-                Gke = fma(Gk[d], e[d], Gke);
-                bke = fma(bk[d], e[d], bke);
-                Gje = fma(Gj[d], e[d], Gje);
-                bje = fma(bj[d], e[d], bje);
-            }
-            // own terms carry G_k.e + (rho_j - rho_k), the neighbour's G_j.e + (rho_j - rho_k)
-            const T drk = rhoj - rhok;
-            const T P = Gke + drk, Q = Gje + drk;
-            const T vP = Vj * P, vb = Vj * bke, wQ = Vk * Q, wb = Vk * bje;
-            const T he = h * fma(vb, P, wb * Q);
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                const T z = fma(bk[d], vP, fma(Gk[d], vb, fma(bj[d], wQ, Gj[d] * wb)));
-                ax[q][d] = fma(g, z, fma(he, e[d], ax[q][d]));
-            }
-            ar[q] = fma(-g, fma(wb, fma(irk, Q, T(1)), vb), ar[q]);
+            const T r2 = pair_vector<T, DIM, decltype(image)::value>(K.u, nb.a, c.L, c.invL, e);
+            add(K, S.m, c.invH, c.hc, nb, e, r2, ax[q], ar[q]);
         });
     };
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
     auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
-    if (wave_inside<T, DIM>(uk, S.H, S.L)) pairs(std::false_type{}, groups);
+    T gx[3] = {0, 0, 0}, gr = 0, tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
+            gx[d] = c.kGF * combine_leaves<LPP>(tmp);
+            sum += fabs(gx[d]);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
+        gr = c.kGF * combine_leaves<LPP>(tmp);
+        return sum + fabs(gr);
+    };
+    clear();
+    if (wave_inside<T, DIM>(K.u, S.H, S.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    T gx[3] = {0, 0, 0}, tmp[NQ];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
-        gx[d] = c.kGF * combine_leaves<LPP>(tmp);
+    if (!isfinite(combine()) && past_support(sims[psim[opaque(k)]])) {
+        const int64_t k2 = opaque(k);
+        const PairConst<T> c2 = pair_const(sims[psim[k2]]);
+        RenormAdjSelf<T> K2;
+        load_self(k2, K2);
+        clear();
+        walk_again<LPP, Nbr>(nbr + k2 * width, width, nbr_count[k2], r, gather, [&](int q, Nbr& nb) {
+            T e[3] = {0, 0, 0};
+            const T r2 = r2_exact<T, DIM>(K2.u, nb.a, c2.L, c2.invL, e);
+            if (r2 < c2.H2) add(K2, c2.m, c2.invH, c2.hc, nb, e, r2, ax[q], ar[q]);
+        });
+        combine();
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
-    const T gr = c.kGF * combine_leaves<LPP>(tmp);
     if (r != 0) return;
     const int o = orig[k];
 #pragma unroll
@@ -2697,12 +2867,15 @@ __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const i
     n = n < width ? n : width;
     const int32_t* row = nbr + i * (int64_t)width;
     T acc[NQ][3];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
     auto gather = [&](int j, ShiftNbr<T>& nb) { nb.a = ldo(jd0, (uint32_t)j); };
-    auto pair = [&](int q, ShiftNbr<T>& nb) {
+    auto clear = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q][0] = acc[q][1] = acc[q][2] = T(0);
+    };
+    auto pair = [&](auto within, int q, ShiftNbr<T>& nb) {
         T d[3] = {0, 0, 0};
         const T r2 = r2_exact<T, DIM>(ui, nb.a, c.L, c.invL, d);
+        if (decltype(within)::value && !(r2 < c.H2)) return;
         const T tt = kernel_t(r2, c.invH);
         const T qq = fast_sqrt(r2) * c.invH;
         const T t2 = tt * tt;
@@ -2714,14 +2887,27 @@ __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const i
 #pragma unroll
         for (int k = 0; k < DIM; ++k) acc[q][k] = fma(f, d[k], acc[q][k]);
     };
-    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, pair);
-    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, pair);
+    auto every = [&](int q, ShiftNbr<T>& nb) { pair(std::false_type{}, q, nb); };
     T sum[3] = {0, 0, 0}, tmp[NQ];
+    auto combine = [&]() -> T {
+        T mag = T(0);
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
+        for (int k = 0; k < DIM; ++k) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q][k];
-        sum[k] = combine_leaves<LPP>(tmp);
+            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q][k];
+            sum[k] = combine_leaves<LPP>(tmp);
+            mag += fabs(sum[k]);
+        }
+        return mag;
+    };
+    clear();
+    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, every);
+    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, every);
+    if (!isfinite(combine()) && past_support(S)) {
+        clear();
+        walk_again<LPP, ShiftNbr<T>>(row, width, n, r, gather,
+                                     [&](int q, ShiftNbr<T>& nb) { pair(std::true_type{}, q, nb); });
+        combine();
     }
     if (r != 0) return;
     const int o = orig[i];
@@ -2778,16 +2964,19 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
     n = n < width ? n : width;
     const int32_t* row = nbr + k * (int64_t)width;
     T ax[NQ][3], ar[NQ];
+    auto clear = [&]() {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
+        for (int q = 0; q < NQ; ++q) ax[q][0] = ax[q][1] = ax[q][2] = ar[q] = T(0);
+    };
     auto gather = [&](int j, ShiftNbr<T>& nb) {
         nb.a = ldo(jd0, (uint32_t)j);
         nb.b = ldo(xs, (uint32_t)j);
     };
-    auto pair = [&](int q, ShiftNbr<T>& nb) {
+    auto pair = [&](auto within, int q, ShiftNbr<T>& nb) {
 #pragma clang fp contract(off)
         T e[3] = {0, 0, 0};
         const T r2 = r2_exact<T, DIM>(uk, nb.a, c.L, c.invL, e);
+        if (decltype(within)::value && !(r2 < c.H2)) return;
         const T tt = kernel_t(r2, c.invH);
         const T qq = fast_sqrt(r2) * c.invH;
         const T t2 = tt * tt;
@@ -2815,18 +3004,31 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
         for (int d = 0; d < DIM; ++d) ax[q][d] = fma(pg, z[d], fma(ce, e[d], ax[q][d]));
         ar[q] = fma(pg, exj, ar[q]);
     };
-    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, pair);
-    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, pair);
-    T gx[3] = {0, 0, 0}, tmp[NQ];
+    auto every = [&](int q, ShiftNbr<T>& nb) { pair(std::false_type{}, q, nb); };
+    T gx[3] = {0, 0, 0}, gr = 0, tmp[NQ];
+    auto combine = [&]() -> T {
+        T sum = T(0);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
+        for (int d = 0; d < DIM; ++d) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
-        gx[d] = combine_leaves<LPP>(tmp);
+            for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
+            gx[d] = combine_leaves<LPP>(tmp);
+            sum += fabs(gx[d]);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
+        gr = combine_leaves<LPP>(tmp);
+        return sum + fabs(gr);
+    };
+    clear();
+    sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, every);
+    list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, every);
+    if (!isfinite(combine()) && past_support(S)) {
+        clear();
+        walk_again<LPP, ShiftNbr<T>>(row, width, n, r, gather,
+                                     [&](int q, ShiftNbr<T>& nb) { pair(std::true_type{}, q, nb); });
+        combine();
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
-    const T gr = combine_leaves<LPP>(tmp);
     if (r != 0) return;
     const int o = orig[k];
     const T cs = -beta * S.H2 * c.kGF;
