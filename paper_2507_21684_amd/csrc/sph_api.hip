@@ -427,26 +427,39 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
     int32_t* orig_out = wsp<int32_t>(P, L.orig);
     if (orig_in == orig_out) return fail(SPH_ERR_STATE, "sort source and destination slot coincide");
     const unsigned g = grid_for(N, 256);
+    const bool scan = P->ncell <= kSortScanCells;
+    const bool by_dest = !orig_in && !scan;
+    CellMembers members = cell_members(P);
+    if (by_dest) members.cap = 0;
     ProfScope prof(P, st, SPH_KERN_SORT);
     if (!assigned) {
-        k_assign<T, D><<<g, 256, 0, st>>>(N, src, psim, simc, blk_rank, cell_count, cell_of, cell_members(P), orig_in,
-                                          status);
+        k_assign<T, D><<<g, 256, 0, st>>>(N, src, psim, simc, blk_rank, cell_count, cell_of, members, orig_in, status);
         LAUNCH_CHECK("assign");
     }
     unsigned int* ticket = wsp<unsigned int>(P, P->o_ticket);
-    const bool scan = P->ncell <= kSortScanCells;
     if (!scan)
         RC_TRY(scan_exclusive<int32_t>(cell_count, P->ncell, wsp<int32_t>(P, P->o_part), ticket, cell_start, true, st));
-    if (P->members_cap == 0) {
-        k_scatter<<<g, 256, 0, st>>>(N, cell_of, cell_start, orig_in, cell_members(P));
+    if (members.cap == 0) {
+        k_scatter<<<g, 256, 0, st>>>(N, cell_of, cell_start, orig_in, members);
         LAUNCH_CHECK("scatter");
     }
+    const SortedSlot<T> out{orig_out,
+                            wsp<vec4_t<T>>(P, L.jd0),
+                            wsp<vec4_t<T>>(P, L.jd1),
+                            P->filter ? wsp<vec4_t<T>>(P, P->o_uref) : nullptr,
+                            (T)(P->speed_skins ? kSkinFloor : 1.0),
+                            (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0),
+                            order_before(P, slot)};
+    if (by_dest) {
+        k_order_gather<T, D><<<g, 256, 0, st>>>(N, members.rows, cell_of, cell_start, src, ws_state<T, D>(P, L.SA),
+                                                out, sim_table(P), simc);
+        LAUNCH_CHECK("order_gather");
+        return SPH_OK;
+    }
     auto kernel = scan ? k_sort_gather<T, D, true> : k_sort_gather<T, D, false>;
-    kernel<<<grid_for(N, kSortThreads), kSortThreads, 0, st>>>(
-        N, (int32_t)P->ncell, cell_count, cell_start, ticket, cell_of, cell_members(P), orig_in, src,
-        ws_state<T, D>(P, L.SA), orig_out, wsp<vec4_t<T>>(P, L.jd0), wsp<vec4_t<T>>(P, L.jd1), sim_table(P), simc,
-        P->filter ? wsp<vec4_t<T>>(P, P->o_uref) : nullptr, (T)(P->speed_skins ? kSkinFloor : 1.0),
-        (T)(P->speed_skins ? kSkinMargin * P->reuse : 0.0), order_before(P, slot));
+    kernel<<<grid_for(N, kSortThreads), kSortThreads, 0, st>>>(N, (int32_t)P->ncell, cell_count, cell_start, ticket,
+                                                               cell_of, members, orig_in, src,
+                                                               ws_state<T, D>(P, L.SA), out, sim_table(P), simc);
     LAUNCH_CHECK("sort_gather");
     return SPH_OK;
 }

@@ -302,9 +302,10 @@ __global__ void k_fill(I* __restrict__ p, int64_t n, I val)
 // first cap - 1 arrivals in row c of `rows`; later ones (dense clusters) are chained, the chain's head in
 // the row's last place and the links, by position in the source order, in `link`.  A chain's length
 // follows from the cell's count, so neither rows nor links are ever cleared.  cap is 1 or a multiple of 4;
-// or 0 in plans of many cells, whose arrivals keep their place in the cell in `link` and are scattered into
-// contiguous `rows` once the cell starts are known (k_scatter): the scattered stores of a padded row cost
-// the 512-simulation batch, 3.1 million particles, more than that launch does.
+// or 0 where arrivals keep their place in the cell in `link` and are scattered into contiguous `rows` once the
+// cell starts are known (k_scatter): for the sort by destination, and in plans of many cells (the
+// scattered stores of a padded row cost the 512-simulation batch, 1.96 million particles, more than that
+// launch does).
 struct CellMembers {
     int32_t* rows;
     int32_t* link;
@@ -458,6 +459,94 @@ __global__ __launch_bounds__(256) void k_scatter(int64_t N, const int32_t* __res
     members.rows[cell_start[cell_of[p]] + members.link[p]] = orig_in ? orig_in[p] : (int32_t)p;
 }
 
+// What a sort writes for a particle besides its state: the original index, the packed records that the
+// neighbour sweeps read (wrapped position, volume V = m / rho, p V, velocity), with list reuse the position
+// the lists are built from and the half skin, and the place in the source order.
+template <typename T>
+struct SortedSlot {
+    int32_t* orig;
+    vec4_t<T>* jd0;
+    vec4_t<T>* jd1;
+    vec4_t<T>* uref;   // null: no list reuse
+    T skin_floor, skin_steps;
+    int32_t* before;   // null: not kept
+};
+
+// Source particle p, of original index op, put at sorted position d.
+template <typename T, int DIM>
+__device__ __forceinline__ void put_sorted(int64_t p, int d, int op, const SimConst<T>& S,
+                                           const StatePtrs<T, DIM>& src, const StatePtrs<T, DIM>& dst,
+                                           const SortedSlot<T>& slot)
+{
+    T x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, u[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        x[k] = src.x[k][p];
+        v[k] = src.v[k][p];
+        dst.x[k][d] = x[k];
+        dst.v[k][d] = v[k];
+        u[k] = wrap_pos(isfinite(x[k]) ? x[k] : T(0), S.L, S.invL);
+    }
+    const T rho = src.rho[p];
+    dst.rho[d] = rho;
+    slot.orig[d] = op;
+    if (slot.before) slot.before[d] = (int32_t)p;
+    const T V = S.m * fast_rcp(rho);
+    const T pr = tait(S, rho);
+    const T pV = pr * V;
+    vec4_t<T> a, b;
+    if (DIM == 3) {
+        a.x = u[0]; a.y = u[1]; a.z = u[2]; a.w = rho;
+        b.x = v[0]; b.y = v[1]; b.z = v[2]; b.w = pr;
+    } else {
+        a.x = u[0]; a.y = u[1]; a.z = V; a.w = pV;
+        b.x = v[0]; b.y = v[1]; b.z = rho; b.w = pr;
+    }
+    slot.jd0[d] = a;
+    slot.jd1[d] = b;
+    if (slot.uref) {
+        // the positions the lists are built from and the particle's half skin (list reuse):
+        // speed-scaled with skin_floor = kSkinFloor, skin_steps = kSkinMargin R, uniform (hmax)
+        // with skin_floor = 1, skin_steps = 0
+        T v2 = T(0);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) v2 += v[k] * v[k];
+        const T hv = slot.skin_floor * S.hmax + slot.skin_steps * S.dt * sqrt(v2);
+        const T h = hv < S.hmax ? hv : S.hmax;   // a non-finite speed keeps hmax
+        vec4_t<T> r;
+        r.x = u[0]; r.y = u[1]; r.z = u[2]; r.w = h;
+        slot.uref[d] = r;
+    }
+}
+
+// The sort by destination, of a state in the caller's order (original index = place in the source order) whose
+// indices k_scatter has put into `rows`: one thread per place there, so that the scattered accesses are
+// loads, which the L2 serves (a cell's particles share lines with its neighbours'), and the stores are
+// coalesced.  One thread per source particle (k_sort_gather) scatters the stores instead, which costs
+// little while the source is the sorted state of the step before, and little in a small plan.  Whole
+// sorts by source and by destination, in us: 2D 512^2 34.0 and 30.8, 2D 1000^2 79.4 and 67.3, 2D 1400^2 143
+// and 114, 3D 100^3 97 and 83 in lattice order, shuffled 2D 512^2 62.6 and 45.2, 3D 64^3 67.8 and 52.2;
+// around the line 2D 290^2 (20 736 cells) 23.8 and 23.6, shuffled 30.1 and 27.0, 3D 56^3 30.1 and
+// 29.5, shuffled 50.9 and 40.1.
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_order_gather(int64_t N, const int32_t* __restrict__ rows,
+                                                      const int32_t* __restrict__ cell_of,
+                                                      const int32_t* __restrict__ cell_start, StatePtrs<T, DIM> src,
+                                                      StatePtrs<T, DIM> dst, SortedSlot<T> slot,
+                                                      const int32_t* __restrict__ psim,
+                                                      const SimConst<T>* __restrict__ sims)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= N) return;
+    const int p = rows[q];
+    const int c = cell_of[p];
+    const int s0 = cell_start[c], s1 = cell_start[c + 1];
+    int rank = 0;
+#pragma unroll 4
+    for (int e = s0; e < s1; ++e) rank += rows[e] < p ? 1 : 0;
+    put_sorted<T, DIM>(p, s0 + rank, p, sims[sim_of(psim, q)], src, dst, slot);
+}
+
 // Threads of k_sort_gather, and the most cells whose counts each of its workgroups scans by itself.  Up to
 // there the sort is one launch behind the counting; past it the counts go through the two scan launches
 // first, as every workgroup reads them all (16 384 cells: 10.3 us against 16 and two launches more; the
@@ -481,12 +570,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
                                                       unsigned int* __restrict__ ticket,
                                                       const int32_t* __restrict__ cell_of, CellMembers members,
                                                       const int32_t* __restrict__ orig_in, StatePtrs<T, DIM> src,
-                                                      StatePtrs<T, DIM> dst, int32_t* __restrict__ orig_out,
-                                                      vec4_t<T>* __restrict__ jd0, vec4_t<T>* __restrict__ jd1,
+                                                      StatePtrs<T, DIM> dst, SortedSlot<T> slot,
                                                       const int32_t* __restrict__ psim,
-                                                      const SimConst<T>* __restrict__ sims,
-                                                      vec4_t<T>* __restrict__ uref, T skin_floor,
-                                                      T skin_steps, int32_t* __restrict__ before)
+                                                      const SimConst<T>* __restrict__ sims)
 {
     constexpr int kWaves = kSortThreads / 64;
     __shared__ int32_t quads[SCAN ? kSortScanCells / 4 : 1];
@@ -578,46 +664,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
         }
     }
     const int d = s0 + rank;
-    const SimConst<T>& S = sims[sim_of(psim, p)];
-    T x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, u[3] = {0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-        x[k] = src.x[k][p];
-        v[k] = src.v[k][p];
-        dst.x[k][d] = x[k];
-        dst.v[k][d] = v[k];
-        u[k] = wrap_pos(isfinite(x[k]) ? x[k] : T(0), S.L, S.invL);
-    }
-    const T rho = src.rho[p];
-    dst.rho[d] = rho;
-    orig_out[d] = op;
-    if (before) before[d] = (int32_t)p;
-    const T V = S.m * fast_rcp(rho);
-    const T pr = tait(S, rho);
-    const T pV = pr * V;
-    vec4_t<T> a, b;
-    if (DIM == 3) {
-        a.x = u[0]; a.y = u[1]; a.z = u[2]; a.w = rho;
-        b.x = v[0]; b.y = v[1]; b.z = v[2]; b.w = pr;
-    } else {
-        a.x = u[0]; a.y = u[1]; a.z = V; a.w = pV;
-        b.x = v[0]; b.y = v[1]; b.z = rho; b.w = pr;
-    }
-    jd0[d] = a;
-    jd1[d] = b;
-    if (uref) {
-        // the positions the lists are built from and the particle's half skin (list reuse):
-        // speed-scaled with skin_floor = kSkinFloor, skin_steps = kSkinMargin R, uniform (hmax)
-        // with skin_floor = 1, skin_steps = 0
-        T v2 = T(0);
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) v2 += v[k] * v[k];
-        const T hv = skin_floor * S.hmax + skin_steps * S.dt * sqrt(v2);
-        const T h = hv < S.hmax ? hv : S.hmax;   // a non-finite speed keeps hmax
-        vec4_t<T> r;
-        r.x = u[0]; r.y = u[1]; r.z = u[2]; r.w = h;
-        uref[d] = r;
-    }
+    put_sorted<T, DIM>(p, d, op, sims[sim_of(psim, p)], src, dst, slot);
     }
     if (SCAN) {
         if (threadIdx.x == 0) is_last = done == gridDim.x - 1;

@@ -1,0 +1,55 @@
+"""The sort by destination (states in the caller's order, in plans past one scan per workgroup) against the sort
+by source: simulations in one large plan and each in a small plan of its own give bitwise the same states,
+gradients and lists, in lattice order and shuffled, with exact lists and with reused ones."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21684_amd.inputs import SimSpec, make_state
+from paper_2507_21684_amd.lib import Plan
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda", 0)
+
+
+def _job(specs, states, dtype, R):
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    st = [torch.tensor(np.concatenate([s[k] for s in states], axis=-1), dtype=tdt, device=DEV).contiguous()
+          for k in range(3)]
+    plan = Plan([s.params() for s in specs], [s.n for s in specs], dtype, tape_depth=2, device=DEV,
+                skin=0.3 if R > 1 else 0.0, rebuild_every=R, speed_skins=R > 1)
+    off, nbr = plan.neighbors(*st)
+    ck = [plan.empty_state() for _ in range(2)]
+    a = [t.clone() for t in st]
+    plan.step(*a, 4, ck, 2)
+    c = [torch.full_like(t, 0.3) for t in st]
+    plan.rollout_backward(ck, 4, 2, *c)
+    torch.cuda.synchronize()
+    assert np.all(plan.poll() == 0)
+    return off, nbr, a, c
+
+
+@pytest.mark.parametrize("dim,sides,dtype,R,shuffled", [(2, (180, 17, 160, 140), "f32", 1, False),
+                                                        (2, (180, 17, 160, 140), "f32", 2, True),
+                                                        (2, (200, 150, 33), "f64", 2, False),
+                                                        (3, (44, 16, 48), "f32", 2, True)])
+def test_one_plan_and_one_each(dim, sides, dtype, R, shuffled):
+    specs = [SimSpec(dim, s, amplitude=0.8 + 0.1 * k) for k, s in enumerate(sides)]
+    rng = np.random.default_rng(17)
+    states = []
+    for k, spec in enumerate(specs):
+        st = make_state(spec, k)
+        perm = rng.permutation(spec.n) if shuffled else np.arange(spec.n)
+        states.append([a[..., perm] for a in st])
+    off, nbr, a, c = _job(specs, states, dtype, R)
+    first = 0
+    for spec, st in zip(specs, states):
+        o1, n1, a1, c1 = _job([spec], [st], dtype, R)
+        rows = slice(first, first + spec.n)
+        lo, hi = int(off[first]), int(off[first + spec.n])
+        assert torch.equal(off[first:first + spec.n + 1] - lo, o1)
+        assert torch.equal(nbr[lo:hi] - first, n1)
+        for big, one in zip(a + c, a1 + c1):
+            assert torch.equal(big[..., rows], one)
+        first += spec.n
