@@ -427,7 +427,7 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
     int32_t* orig_out = wsp<int32_t>(P, L.orig);
     if (orig_in == orig_out) return fail(SPH_ERR_STATE, "sort source and destination slot coincide");
     const unsigned g = grid_for(N, 256);
-    const bool scan = P->ncell <= kSortScanCells;
+    const bool scan = P->ncell <= kSortScanCells && P->ncell * grid_for(N, kSortThreads) <= kSortScanReads;
     const bool by_dest = !orig_in && !scan;
     CellMembers members = cell_members(P);
     if (by_dest) members.cap = 0;

@@ -547,12 +547,16 @@ __global__ __launch_bounds__(256) void k_order_gather(int64_t N, const int32_t* 
     put_sorted<T, DIM>(p, s0 + rank, p, sims[sim_of(psim, q)], src, dst, slot);
 }
 
-// Threads of k_sort_gather, and the most cells whose counts each of its workgroups scans by itself.  Up to
-// there the sort is one launch behind the counting; past it the counts go through the two scan launches
-// first, as every workgroup reads them all (16 384 cells: 10.3 us against 16 and two launches more; the
-// reads grow with the square of the plan).
+// Threads of k_sort_gather, and where each of its workgroups scans the counts of all cells by itself: up to
+// kSortScanCells cells (their prefixes fit its LDS) and kSortScanReads counts read by all workgroups together.
+// There the sort is one launch behind the counting; past either the counts go through the two scan launches
+// first.  Sorts behind a step, scanned in the gather and by the launches, us: 2D 320^2 with H = 6 dx
+// (11 664 cells, 4.7 M reads) 15.9 against 19.6, 2D 364^2 with H = 6 dx (15 376 cells, 8.0 M reads) 17.9 and 20.2, 3D
+// 56^3 with H = 5 dx (7.3 M) 21.0 and 21.1, 2D 450^2 with H = 8 dx (9.9 M) 22.6 and 21.4, 3D 64^3 with H = 6
+// dx (10.9 M) 27.1 and 24.0, 2D 1000^2 with H = 16 dx (60 M) 82 and 53.
 constexpr int kSortThreads = 256;
 constexpr int kSortScanCells = 16384;
+constexpr int64_t kSortScanReads = 1 << 23;
 
 // Final sorted position = cell start + rank of the particle's original index among its cell's
 // members; moves the state there and packs the per-particle data that the neighbour sweeps read

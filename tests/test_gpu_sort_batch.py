@@ -53,3 +53,26 @@ def test_one_plan_and_one_each(dim, sides, dtype, R, shuffled):
         for big, one in zip(a + c, a1 + c1):
             assert torch.equal(big[..., rows], one)
         first += spec.n
+
+
+@pytest.mark.parametrize("n", [131072, 131073])
+def test_where_the_scan_leaves_the_gather(orc, n):
+    """16 384 cells: 512 workgroups scan them in the gather, 513 leave that to the scan launches."""
+    spec = SimSpec(2, 256)
+    rng = np.random.default_rng(23)
+    x = rng.uniform(size=(2, n)).astype(np.float32)
+    st = [x, (0.1 * rng.normal(size=(2, n))).astype(np.float32), np.ones(n, dtype=np.float32)]
+    gpu = lambda: [torch.tensor(a, device=DEV).contiguous() for a in st]
+    off_r, nbr_r = orc.neighbors(x.astype(np.float64), spec.box, spec.H, "f32")
+    plan = Plan([spec.params()], [n], "f32", max_neighbors=int(np.diff(off_r).max()) + 40, tape_depth=0, device=DEV)
+    for _ in range(2):   # the counts are cleared for the next sort
+        off, nbr = plan.neighbors(*gpu())
+        np.testing.assert_array_equal(off.cpu().numpy(), off_r)
+        np.testing.assert_array_equal(nbr.cpu().numpy(), nbr_r)
+    a, b = gpu(), gpu()
+    plan.step(*a, 3)
+    for _ in range(3):
+        plan.step(*b, 1)
+    assert np.all(plan.poll() == 0)
+    for p, q in zip(a, b):
+        assert torch.equal(p, q)
