@@ -76,3 +76,36 @@ def test_where_the_scan_leaves_the_gather(orc, n):
     assert np.all(plan.poll() == 0)
     for p, q in zip(a, b):
         assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("dtype,n", [("f32", 700), ("f32", 1700), ("f64", 1700)])
+def test_cells_around_their_places(orc, dtype, n):
+    """1024 cells with 1 (700 particles), 8 and 16 places: clusters of 1 to 26 particles in cells of their own
+    fill the row and the four chains behind it to every length."""
+    spec = SimSpec(2, 62)
+    npdt, tdt = (np.float32, torch.float32) if dtype == "f32" else (np.float64, torch.float64)
+    rng = np.random.default_rng(29)
+    x = rng.uniform(size=(2, n))
+    side = 1.0 / 30     # cells of half the support
+    first = 0
+    for m in range(1, 27):
+        cell = np.array([[3 + 4 * ((m - 1) % 6)], [3 + 4 * ((m - 1) // 6)]])
+        x[:, first:first + m] = side * (cell + 0.1 + 0.8 * rng.uniform(size=(2, m)))
+        first += m
+    perm = rng.permutation(n)
+    x = x[:, perm].astype(npdt)
+    st = [x, (0.1 * rng.normal(size=(2, n))).astype(npdt), np.ones(n, dtype=npdt)]
+    gpu = lambda: [torch.tensor(a, dtype=tdt, device=DEV).contiguous() for a in st]
+    off_r, nbr_r = orc.neighbors(x.astype(np.float64), spec.box, spec.H, dtype)
+    plan = Plan([spec.params()], [n], dtype, max_neighbors=int(np.diff(off_r).max()) + 40, tape_depth=0, device=DEV)
+    for _ in range(2):
+        off, nbr = plan.neighbors(*gpu())
+        np.testing.assert_array_equal(off.cpu().numpy(), off_r)
+        np.testing.assert_array_equal(nbr.cpu().numpy(), nbr_r)
+    a, b = gpu(), gpu()
+    plan.step(*a, 3)
+    for _ in range(3):
+        plan.step(*b, 1)
+    assert np.all(plan.poll() == 0)
+    for p, q in zip(a, b):
+        assert torch.equal(p, q)
