@@ -47,7 +47,8 @@ sph_status fail(sph_status code, const std::string& msg)
 
 constexpr double kCellMargin = 1.0 + 1.0 / 1024.0;  // cell side exceeds H/sub by more than rounding
 constexpr size_t kMaxMembers = 64;                   // places per cell for its members, at most
-constexpr int64_t kMemberCells = 131072;              // plans with this many cells collect them in rows of places
+constexpr int64_t kMemberCells = 131072;              // plans of at most this many cells collect them in rows of
+                                                      // places; larger ones scatter them after the scan
 constexpr int64_t kGroupedBuildCells = 65536;         // 2D plans with this many cell slots build by 2 x 2 groups
 
 // 3D builds with fewer wavefronts than kBuildWaves (eight on every SIMD) let up to four share a cell's
@@ -427,9 +428,10 @@ sph_status sort_into(sph_plan* P, StatePtrs<T, D> src, const int32_t* orig_in, i
     int32_t* orig_out = wsp<int32_t>(P, L.orig);
     if (orig_in == orig_out) return fail(SPH_ERR_STATE, "sort source and destination slot coincide");
     const unsigned g = grid_for(N, 256);
-    const bool scan = P->ncell <= kSortScanCells && P->ncell * grid_for(N, kSortThreads) <= kSortScanReads;
-    const bool by_dest = !orig_in && !scan;
     CellMembers members = cell_members(P);
+    const bool scan = members.cap > 0 && P->ncell <= kSortScanCells &&
+                      P->ncell * grid_for(N, kSortThreads) <= kSortScanReads;
+    const bool by_dest = !orig_in && !scan;
     if (by_dest) members.cap = 0;
     ProfScope prof(P, st, SPH_KERN_SORT);
     if (!assigned) {
@@ -1683,8 +1685,11 @@ sph_status sph_plan_create(const sph_params* sims, int32_t nsims, const int64_t*
     P->o_SB = take(T * N * (2 * d + 1));
     P->o_jdA = take(V4 * N);
     P->o_jdA2 = take(V4 * N);
+    // rows of places for the cells' members, also where that takes a little more room than the cotangents
+    // (one place per cell: up to 24 bytes per particle); a plan of fewer particles, in a mostly empty box,
+    // scatters its members instead of growing by four bytes per cell
     const size_t cots = T * N * (2 * d + 1);
-    const bool rows = P->ncell > 0 && P->ncell <= kMemberCells;
+    const bool rows = P->ncell > 0 && P->ncell <= kMemberCells && (size_t)P->ncell <= 6 * N;
     P->o_cots = take(rows ? std::max<size_t>(cots, 4 * (size_t)P->ncell) : cots);
     if (rows) {
         const size_t cap = std::min<size_t>(cots / (4 * (size_t)P->ncell), kMaxMembers) & ~(size_t)3;
