@@ -1155,6 +1155,30 @@ __device__ __forceinline__ T combine_leaves(T* a /* [kLeaves / LPP] */)
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
+// The same for NV sums at once, level by level, so that their shuffles are in flight together (one sum after
+// the other waits for each of its own).
+template <int LPP, int NV, typename T>
+__device__ __forceinline__ void combine_leaves(T (&a)[NV][kLeaves / LPP], T (&out)[NV])
+{
+    constexpr int NQ = kLeaves / LPP;
+#pragma unroll
+    for (int o = 1; o < LPP; o <<= 1) {
+        T b[NV][NQ];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) b[v][q] = __shfl_xor(a[v][q], o, 64);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) a[v][q] = a[v][q] + b[v][q];
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        out[v] = NQ == 1 ? a[v][0] : NQ == 2 ? a[v][0] + a[v][1 % NQ]
+                                             : (a[v][0] + a[v][1 % NQ]) + (a[v][2 % NQ] + a[v][3 % NQ]);
+}
+
 // ---------------------------------------------------------------- gathers and fast arithmetic
 
 // Element `idx` of an array whose byte size fits 32 bits: a 32-bit byte offset from the
@@ -1345,7 +1369,7 @@ __device__ __forceinline__ void list_tail(const int32_t* __restrict__ row, int w
 // therefore forms them again from the pairs within the support alone, one at a time and in the same order, so
 // that nothing outside the support reaches it.  (A test of the finished sums is a few instructions per
 // particle: the sweeps of the 512-simulation batch took 366 and 481 us without it and 367 and 480 with it,
-// those of 2D 101^2 6.5 and 8.1 against 6.7 and 8.3.)
+// those of 2D 101^2 6.5 and 8.4 against 6.5 and 8.1.)
 template <int LPP, typename REC, typename GATHER, typename PAIR>
 __device__ __forceinline__ void walk_again(const int32_t* __restrict__ row, int width, int n, int r, GATHER&& gather,
                                            PAIR&& pair)
@@ -1515,7 +1539,7 @@ __device__ __forceinline__ PairConst<T> pair_const(const SimConst<T>& S)
 
 // ---------------------------------------------------------------- forward sweep
 
-// Workgroup of the forward and adjoint sweeps.  In FP32 3D with eight lanes 512, i.e. 64 particles, whose
+// Largest workgroup of the forward and adjoint sweeps.  In FP32 3D with eight lanes 512, i.e. 64 particles, whose
 // neighbourhoods overlap in the vector L1 (3D 64^3: 213 and 317 us against 229 and 326 with 256; with
 // four lanes, where 256 lanes are 64 particles, 512 is no faster, and neither is it in 2D).
 template <typename T, int DIM, int LPP>
@@ -1692,7 +1716,7 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
     if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    if (!isfinite(combine()) && past_support(sims[psim[opaque(i)]])) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[psim[opaque(i)]])) {
         const int64_t i2 = opaque(i);
         const SimConst<T>& S2 = sims[psim[i2]];
         const T invH2 = S2.invH, rho2 = (DIM == 3) ? rho3[i2] : jd1[i2].z;
@@ -1924,39 +1948,36 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
     auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
     T ax[3] = {0, 0, 0}, rdv = 0, rdd = 0, rs = 0, rdg = 0;
-    T tmp[NQ];
     auto combine = [&]() -> T {
+        constexpr bool kSum = MODE == kModeRhs;
+        constexpr int NV = DIM + 2 + (kSum ? 1 : 0) + (RENORM ? 1 : 0);
+        T leaf[NV][NQ], out[NV];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) leaf[k][q] = acc[q].ax[k];
+            leaf[DIM][q] = acc[q].rdv;
+            leaf[DIM + 1][q] = acc[q].rdd;
+            if (kSum) leaf[DIM + 2][q] = acc[q].rs;
+            if (RENORM) leaf[NV - 1][q] = acc[q].rdg;
+        }
+        combine_leaves<LPP, NV>(leaf, out);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) ax[k] = out[k];
+        rdv = out[DIM];
+        rdd = out[DIM + 1];
+        if (kSum) rs = out[DIM + 2];
+        if (RENORM) rdg = out[NV - 1];
         T sum = T(0);
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].ax[k];
-            ax[k] = combine_leaves<LPP>(tmp);
-            sum += fabs(ax[k]);
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdv;
-        rdv = combine_leaves<LPP>(tmp);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdd;
-        rdd = combine_leaves<LPP>(tmp);
-        if (MODE == kModeRhs) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rs;
-            rs = combine_leaves<LPP>(tmp);
-        }
-        if (RENORM) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].rdg;
-            rdg = combine_leaves<LPP>(tmp);
-        }
-        return sum + fabs(rdv) + fabs(rdd) + fabs(rdg);
+        for (int v = 0; v < NV; ++v) sum += fabs(out[v]);
+        return sum;
     };
     clear();
     if (wave_inside<T, DIM>(K.u, c.H, c.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    if (!isfinite(combine()) && past_support(sims[s])) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[s])) {
         const uint32_t i2 = opaque(i);
         const PairConst<T> c2 = pair_const(sims[opaque(s)]);
         FwdSelf<T> K2;
@@ -2147,7 +2168,7 @@ __global__ __launch_bounds__(256) void k_density_adj(int64_t N, int32_t width, c
     if (wave_inside<T, DIM>(ui, S.H, S.L)) pairs(std::false_type{}, std::false_type{}, groups);
     else pairs(std::true_type{}, std::false_type{}, groups);
     pairs(std::true_type{}, std::false_type{}, tail);
-    if (!isfinite(combine()) && past_support(S)) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(S)) {
         clear();
         pairs(std::true_type{}, std::true_type{},
               [&](auto&& pair) { walk_again<LPP, DensNbr<T>>(row, width, n, r, gather, pair); });
@@ -2634,37 +2655,39 @@ void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     };
     auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)k, gather, pair); };
     T gx[3] = {0, 0, 0}, gv[3] = {0, 0, 0}, Gb[3] = {0, 0, 0}, s1 = 0, s2 = 0;
-    T tmp[NQ];
     auto combine = [&]() -> T {
-        T sum = T(0);
+        constexpr int NV = (RENORM ? 3 : 2) * DIM + 2;
+        T leaf[NV][NQ], out[NV];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+                leaf[d][q] = acc[q].gx[d];
+                leaf[DIM + d][q] = acc[q].gv[d];
+                if (RENORM) leaf[2 * DIM + d][q] = acc[q].Gb[d];
+            }
+            leaf[NV - 2][q] = acc[q].s1;
+            leaf[NV - 1][q] = acc[q].s2;
+        }
+        combine_leaves<LPP, NV>(leaf, out);
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gx[d];
-            gx[d] = combine_leaves<LPP>(tmp);
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].gv[d];
-            gv[d] = combine_leaves<LPP>(tmp);
-            if (RENORM) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].Gb[d];
-                Gb[d] = combine_leaves<LPP>(tmp);
-            }
-            sum += fabs(gx[d]) + fabs(gv[d]) + fabs(Gb[d]);
+            gx[d] = out[d];
+            gv[d] = out[DIM + d];
+            if (RENORM) Gb[d] = out[2 * DIM + d];
         }
+        s1 = out[NV - 2];
+        s2 = out[NV - 1];
+        T sum = T(0);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s1;
-        s1 = combine_leaves<LPP>(tmp);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].s2;
-        s2 = combine_leaves<LPP>(tmp);
-        return sum + fabs(s1) + fabs(s2);
+        for (int v = 0; v < NV; ++v) sum += fabs(out[v]);
+        return sum;
     };
     clear();
     if (wave_inside<T, DIM>(uk, c.H, c.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    if (!isfinite(combine()) && past_support(sims[s])) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[s])) {
         const int64_t k2 = opaque(k);
         const PairConst<T> c2 = pair_const(sims[opaque(s)]);
         T u2[3] = {0, 0, 0};
@@ -2876,7 +2899,7 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
     if (wave_inside<T, DIM>(K.u, S.H, S.L)) pairs(std::false_type{}, groups);
     else pairs(std::true_type{}, groups);
     pairs(std::true_type{}, tail);
-    if (!isfinite(combine()) && past_support(sims[psim[opaque(k)]])) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[psim[opaque(k)]])) {
         const int64_t k2 = opaque(k);
         const PairConst<T> c2 = pair_const(sims[psim[k2]]);
         RenormAdjSelf<T> K2;
@@ -2966,7 +2989,7 @@ __global__ __launch_bounds__(256) void k_shift(int64_t N, int32_t width, const i
     clear();
     sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, every);
     list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)i, gather, every);
-    if (!isfinite(combine()) && past_support(S)) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(S)) {
         clear();
         walk_again<LPP, ShiftNbr<T>>(row, width, n, r, gather,
                                      [&](int q, ShiftNbr<T>& nb) { pair(std::true_type{}, q, nb); });
@@ -3086,7 +3109,7 @@ __global__ __launch_bounds__(256) void k_shift_adj(int64_t N, int32_t width, con
     clear();
     sweep_list<(sizeof(T) == 8), LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, every);
     list_tail<LPP, ShiftNbr<T>>(row, width, n, r, (int)k, gather, every);
-    if (!isfinite(combine()) && past_support(S)) {
+    if (__builtin_expect(!isfinite(combine()), 0) && past_support(S)) {
         clear();
         walk_again<LPP, ShiftNbr<T>>(row, width, n, r, gather,
                                      [&](int q, ShiftNbr<T>& nb) { pair(std::true_type{}, q, nb); });
