@@ -531,6 +531,19 @@ int sweep_lanes(const sph_plan* P, int set)
     return sizeof(T) == 4 && D == 2 && set == 8 && P->N * 4 >= 64 * 2048 ? 4 : set;
 }
 
+// Workgroup of a forward or adjoint sweep over N particles: kSweepThreads, but in a small plan 256 where
+// the 256 CUs' turns of 32 particles come out odd, since workgroups of 64 then leave the busiest CU with
+// more (FP32 3D with eight lanes and a skin, 512 and 256 threads, us forward and adjoint: 16^3 14.7, 22.2
+// and 12.9, 16.9; 20^3 15.3, 22.6 and 13.7, 18.0; 26^3 27.0, 41.5 and 22.6, 33.1; 28^3 27.4, 40.6 and 22.3,
+// 34.3.  With even turns 512 is the faster or equal: exact lists 25^3 16.0, 19.1 and 17.4, 19.4; 32^3 25.3,
+// 30.7 and 27.7, 31.0; 40^3 46.0, 62.7 and 51.9, 63.4.)
+template <typename T, int D, int LPP>
+int sweep_threads(int64_t N)
+{
+    constexpr int wide = kSweepThreads<T, D, LPP>;
+    return wide > 256 && N < 32768 && (N + 8191) / 8192 % 2 == 1 ? 256 : wide;
+}
+
 // Renormalised density gradient of the state sorted into L, with the lists of LL (and L_i
 // when `with_l`, for the adjoint).
 template <typename T, int D, int LPP>
@@ -550,7 +563,7 @@ void launch_sweep(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, StateP
                   T* rhosum, NextCells next, NextSlot<T> ns, hipStream_t st, ProfScope* prof)
 {
     const int64_t lanes = P->N * LPP;
-    constexpr int threads = kSweepThreads<T, D, LPP>;
+    const int threads = sweep_threads<T, D, LPP>(P->N);
     if (P->renorm) {
         launch_k(prof, k_sweep<T, D, MODE, LPP, true>, dim3(grid_for(lanes, threads)), dim3(threads), st,
             P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),
@@ -627,7 +640,7 @@ void launch_adj(sph_plan* P, const SlotLayout& L, const SlotLayout& LL, StatePtr
                 StatePtrs<T, D> cout, bool cout_sorted, hipStream_t st, bool vjp, ProfScope* prof, NextAdj<T> na)
 {
     const int64_t lanes = P->N * LPP;
-    constexpr int threads = kSweepThreads<T, D, LPP>;
+    const int threads = sweep_threads<T, D, LPP>(P->N);
     if (P->renorm) {
         launch_k(prof, k_adj_sweep<T, D, LPP, true>, dim3(grid_for(lanes, threads)), dim3(threads), st,
             P->N, P->width, wsp<int32_t>(P, LL.nbr), wsp<int32_t>(P, LL.cnt), wsp<vec4_t<T>>(P, L.jd0),

@@ -1,0 +1,34 @@
+"""Workgroups of the FP32 3D sweeps with eight lanes, either side of the sizes where they change: bitwise the
+results of four lanes, whose workgroups do not."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21684_amd.inputs import SimSpec, make_state
+from paper_2507_21684_amd.lib import Plan
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda", 0)
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 16384, 16385, 24577])
+def test_eight_lanes_and_four(n):
+    spec = SimSpec(3, 30)
+    rng = np.random.default_rng(n)
+    keep = np.sort(rng.permutation(spec.n)[:n])
+    st = [torch.tensor(a[..., keep].astype(np.float32), device=DEV).contiguous() for a in make_state(spec, 3)]
+    out = []
+    for lanes in (4, 8):
+        plan = Plan([spec.params()], [n], "f32", tape_depth=2, device=DEV, skin=0.2, rebuild_every=2)
+        plan.set_tuning(lanes, lanes)
+        ck = [plan.empty_state()]
+        s = [t.clone() for t in st]
+        plan.step(*s, 2, ck, 2)
+        c = [torch.full_like(t, 0.2) for t in st]
+        plan.rollout_backward(ck, 2, 2, *c)
+        torch.cuda.synchronize()
+        assert np.all(plan.poll() == 0)
+        out.append(s + c)
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
