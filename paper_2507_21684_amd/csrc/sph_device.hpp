@@ -1291,6 +1291,12 @@ __device__ __forceinline__ void sweep_burst(const int32_t* __restrict__ row, int
     }
 }
 
+// Whether sweep_piped keeps the next gathers ahead of the pair terms.  Left to itself the compiler lets them
+// sink among the terms in some copies of the loop (3D 16^3 FP64, four lanes, right-hand side: 35.6 us a sweep,
+// 33.2 with them held; 3D 30^3 60.7 and 56.7).
+template <typename REC>
+constexpr bool kGatherFirst = true;
+
 // The same pairs two at a time, the records of the next two gathered while these are computed, the
 // list entries two groups ahead: for FP64, whose pair terms take several times as long as FP32's, so
 // that a wavefront hides its own gathers (2D 32^2, 64 wavefronts: 13.5 us a sweep with four at a time,
@@ -1326,6 +1332,7 @@ __device__ __forceinline__ void sweep_piped(const int32_t* __restrict__ row, int
             }
             gather(j0, rec[(s + 1) & 1][0]);
             gather(j1, rec[(s + 1) & 1][1]);
+            if (kGatherFirst<REC>) __builtin_amdgcn_sched_barrier(0);
             if (last) {
                 c = nx;
                 nx = load_group<LPP>(row, g + 2 < groups ? g + 2 : 0, r);
@@ -2477,6 +2484,10 @@ struct AdjNbr {
         if (RENORM) pin<3>(G);
     }
 };
+
+// (four records per neighbour: held, they cost 2D more than the wait; 32^2 FP64 13.2 us against 11.5)
+template <typename T, int DIM>
+constexpr bool kGatherFirst<AdjNbr<T, DIM, true>> = false;
 
 // Adjoint pair terms, gather form.  For particle k and a neighbour j != k: the partial
 // derivatives, with respect to k's position, velocity and density, of the two directed pair
