@@ -139,8 +139,8 @@ sph_status sph_plan_info(const sph_plan* plan, int64_t* total_particles, int32_t
  * (2, 4 or 8; default 4).  A particle's pair sums are always formed as eight
  * partial sums over list positions k mod 8 combined by the balanced tree
  * ((s0 + s1) + (s2 + s3)) + ((s4 + s5) + (s6 + s7)), so results are bitwise
- * the same for every setting; only speed changes (large FP32 2D plans run four
- * lanes where eight are set, which is faster there).  INVALID_ARG otherwise. */
+ * the same for every setting; only speed changes (large 2D plans run four lanes
+ * where eight are set, which is faster there).  INVALID_ARG otherwise. */
 sph_status sph_set_tuning(sph_plan* plan, int32_t lanes_fwd, int32_t lanes_adj);
 sph_status sph_get_tuning(const sph_plan* plan, int32_t* lanes_fwd, int32_t* lanes_adj);
 

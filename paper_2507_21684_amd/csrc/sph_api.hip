@@ -521,14 +521,17 @@ sph_status build_lists(sph_plan* P, int slot, hipStream_t st, bool exact = false
     return SPH_OK;
 }
 
-// Lanes per particle that a pass over the lists runs with.  Eight lanes fill the GPU with a small plan; from two
-// wavefronts per SIMD on, four are faster in FP32 2D, where a row is two turns of eight lanes' 32
-// positions and the second is mostly empty (24 uneven simulations, 110 000 particles: forward 25.1 us
-// against 28.2, adjoint 32.8 against 36.5).  Results do not depend on it.
+// Lanes per particle that a pass over the lists runs with.  Eight lanes fill the GPU with a small plan; in 2D, where
+// a row is two turns of eight lanes' 32 positions (FP64: three of 16) and the last is mostly empty, four are
+// faster in a larger one: in FP32 from two wavefronts per SIMD on, in FP64, which hides its own gathers, from
+// one.  Four and eight lanes, us forward and adjoint: FP32 2D 151^2 7.7, 9.6 and 8.3, 8.7; 200^2 9.4, 12.5 and
+// 10.9, 11.5; 256^2 12.1, 14.8 and 16.9, 17.0; FP64 90^2 7.7, 9.6 and 6.9, 8.4; 128^2 8.0, 10.2 and 8.9, 11.1;
+// 256^2 22.0, 26.3 and 26.5, 36.4; 400^2 46, 63 and 62, 90.  Results do not depend on it.
 template <typename T, int D>
 int sweep_lanes(const sph_plan* P, int set)
 {
-    return sizeof(T) == 4 && D == 2 && set == 8 && P->N * 4 >= 64 * 2048 ? 4 : set;
+    constexpr int64_t waves = sizeof(T) == 8 ? 1024 : 2048;
+    return D == 2 && set == 8 && P->N * 4 >= 64 * waves ? 4 : set;
 }
 
 // Workgroup of a forward or adjoint sweep over N particles: kSweepThreads, but in a small plan 256 where

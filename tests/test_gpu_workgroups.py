@@ -32,3 +32,26 @@ def test_eight_lanes_and_four(n):
         out.append(s + c)
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [16383, 16384])
+def test_fp64_lanes_around_their_line(n):
+    """2D FP64 plans of 16 384 particles run four lanes where eight are set."""
+    spec = SimSpec(2, 130)
+    st = [torch.tensor(a[..., :n], dtype=torch.float64, device=DEV).contiguous() for a in make_state(spec, 4)]
+    out = []
+    for lanes in (2, 4, 8):
+        plan = Plan([spec.params()], [n], "f64", tape_depth=2, device=DEV)
+        plan.set_tuning(lanes, lanes)
+        assert plan.get_tuning() == (lanes, lanes)
+        ck = [plan.empty_state()]
+        s = [t.clone() for t in st]
+        plan.step(*s, 2, ck, 2)
+        c = [torch.full_like(t, 0.2) for t in st]
+        plan.rollout_backward(ck, 2, 2, *c)
+        torch.cuda.synchronize()
+        assert np.all(plan.poll() == 0)
+        out.append(s + c)
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.equal(a, b)
