@@ -119,13 +119,21 @@ def _store(table: Dict[str, list]) -> None:
         pass
 
 
+def lane_choices(plan: Plan) -> Tuple[int, ...]:
+    """The settings worth timing: the library runs four lanes where eight are set in 2D plans of this
+    size (sweep_lanes in sph_api.hip), so timing eight would time four twice and might keep either."""
+    if plan.dim == 2 and plan.N >= (16384 if plan.dtype == "f64" else 32768):
+        return LANE_CHOICES[:2]
+    return LANE_CHOICES
+
+
 def measure(plan: Plan, x, v, rho, steps: int = 4, reps: int = 2) -> Dict[int, Tuple[float, float]]:
     """{lanes: (forward-sweep ms per launch, adjoint-sweep ms per launch)} on copies of the state."""
     out = {}
     R = getattr(plan, "rebuild_every", 1)
     K = min(steps, max(1, plan.tape_depth))
     K = R * max(1, K // R)          # checkpoint intervals are multiples of the rebuild interval
-    for lanes in LANE_CHOICES:
+    for lanes in lane_choices(plan):
         plan.set_tuning(lanes, lanes)
         best_f, best_a = float("inf"), float("inf")
         for _ in range(reps):

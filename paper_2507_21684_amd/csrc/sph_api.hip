@@ -526,7 +526,8 @@ sph_status build_lists(sph_plan* P, int slot, hipStream_t st, bool exact = false
 // faster in a larger one: in FP32 from two wavefronts per SIMD on, in FP64, which hides its own gathers, from
 // one.  Four and eight lanes, us forward and adjoint: FP32 2D 151^2 7.7, 9.6 and 8.3, 8.7; 200^2 9.4, 12.5 and
 // 10.9, 11.5; 256^2 12.1, 14.8 and 16.9, 17.0; FP64 90^2 7.7, 9.6 and 6.9, 8.4; 128^2 8.0, 10.2 and 8.9, 11.1;
-// 256^2 22.0, 26.3 and 26.5, 36.4; 400^2 46, 63 and 62, 90.  Results do not depend on it.
+// 256^2 22.0, 26.3 and 26.5, 36.4; 400^2 46, 63 and 62, 90.  Results do not depend on it.  (lane_choices in
+// autotune.py knows these sizes.)
 template <typename T, int D>
 int sweep_lanes(const sph_plan* P, int set)
 {
