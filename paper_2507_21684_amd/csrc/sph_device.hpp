@@ -1707,14 +1707,14 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
         for (int e = 0; e < NM; ++e) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].M[e];
-            M[e] = scale * combine_leaves<LPP>(tmp);
+            M[e] = combine_leaves<LPP>(tmp);
             sum += fabs(M[e]);
         }
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) tmp[q] = acc[q].g[k];
-            g[k] = scale * combine_leaves<LPP>(tmp);
+            g[k] = combine_leaves<LPP>(tmp);
             sum += fabs(g[k]);
         }
         return sum;
@@ -1739,6 +1739,10 @@ __global__ __launch_bounds__(256) void k_renorm(int64_t N, int32_t width, const 
         combine();
     }
     if (r != 0) return;
+#pragma unroll
+    for (int e = 0; e < NM; ++e) M[e] = scale * M[e];
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) g[k] = scale * g[k];
     T L[6] = {0, 0, 0, 0, 0, 0}, G[3] = {0, 0, 0};
     if (inv_sym<T, DIM>(M, L)) sym_mul<T, DIM>(L, g, G);
     vec4_t<T> o;
@@ -2898,12 +2902,12 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
         for (int d = 0; d < DIM; ++d) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) tmp[q] = ax[q][d];
-            gx[d] = c.kGF * combine_leaves<LPP>(tmp);
+            gx[d] = combine_leaves<LPP>(tmp);
             sum += fabs(gx[d]);
         }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tmp[q] = ar[q];
-        gr = c.kGF * combine_leaves<LPP>(tmp);
+        gr = combine_leaves<LPP>(tmp);
         return sum + fabs(gr);
     };
     clear();
@@ -2926,8 +2930,8 @@ __global__ __launch_bounds__(256) void k_renorm_adj(int64_t N, int32_t width, co
     if (r != 0) return;
     const int o = orig[k];
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) cot.x[d][o] += gx[d];
-    cot.rho[o] += gr;
+    for (int d = 0; d < DIM; ++d) cot.x[d][o] += c.kGF * gx[d];
+    cot.rho[o] += c.kGF * gr;
 }
 
 // ---------------------------------------------------------------- particle shifting
