@@ -228,7 +228,9 @@ const int32_t* sim_table(const sph_plan* P) { return P->nsims == 1 ? nullptr : w
 // Each particle's place in the order that the sort into `slot` started from, for the adjoint's hand-over to
 // the step before; null for a slot without room for it.  Plans with exact lists sort every step and have
 // no use for the references of list reuse (o_uref), whose room the first of them share.
-constexpr int kOrderSlots = 2;   // further ones
+// Further ones: two, of 4 bytes per particle.  A step whose slot has none runs its prologue as a launch (2D
+// 101^2, eight slots, so two such steps a segment: 1162 us a pass, 1187 with a prologue for every step).
+constexpr int kOrderSlots = 2;
 int32_t* order_before(const sph_plan* P, int slot)
 {
     if (P->filter || slot >= P->order_slots) return nullptr;
@@ -344,7 +346,6 @@ void fill_simconst(const sph_plan* P, std::vector<unsigned char>& out)
         c.dt = (T)q.dt;
         c.kW = (T)(cd / std::pow(q.support, d));
         c.kG = (T)(cd / std::pow(q.support, d + 2));
-        c.kH = (T)(560.0 * cd / std::pow(q.support, d + 4));
         c.epsH2 = (T)(q.eps * q.support * q.support);
         c.cA = (T)(q.alpha * q.support * q.c0 * q.rho0);
         c.cD = (T)(2.0 * q.delta * q.support * q.c0);
@@ -1773,9 +1774,8 @@ namespace {
 
 // The optional workspace regions after the plan's base workspace, in a fixed order, each
 // present once reserved: the renormalised-gradient records (G, L_i, gbar), then the stage
-// storage (stage states, rates and cotangents, the output cotangent and a state tape of
-// tape_depth blocks), then a tape of as many rate blocks (the symplectic scheme's re-used
-// rates).  Setters that reserve call it before the workspace is bound.
+// storage (stage states, rates and cotangents and a state tape of tape_depth blocks), then the
+// symplectic scheme's output cotangent and a tape of as many rate blocks (its re-used rates).  Setters that reserve call it before the workspace is bound.
 void layout_extras(sph_plan* P)
 {
     size_t off = P->bytes_base;
@@ -1800,11 +1800,11 @@ void layout_extras(sph_plan* P)
     off += kMaxStages * sb;
     P->o_rkUb = off;
     off += kMaxStages * sb;
-    P->o_rkB0 = off;
-    off += sb;
     P->o_rkTape = off;
     off += depth * sb;
     if (P->rate_tape) {
+        P->o_rkB0 = off;
+        off += sb;
         P->o_rkRate = off;
         off += depth * sb;
     }

@@ -51,7 +51,6 @@ struct SimConst {
     T m, rho0, inv_rho0, c0sq, dt;
     T kW;       // C_d / H^d
     T kG;       // C_d / H^(d+2)
-    T kH;       // 560 C_d / H^(d+4): second coefficient of the kernel Hessian
     T epsH2;    // eps H^2
     T cA;       // alpha H c0 rho0
     T cD;       // 2 delta H c0
@@ -650,37 +649,37 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_gather(int64_t N, int32_t
         n = cell_start[c + 1] - s0;
     }
     if (active) {
-    int rank = 0;
-    if (!SCAN && members.cap == 0) {
-        const int32_t* row = members.rows + s0;
+        int rank = 0;
+        if (!SCAN && members.cap == 0) {
+            const int32_t* row = members.rows + s0;
 #pragma unroll 4
-        for (int e = 0; e < n; ++e) rank += row[e] < op ? 1 : 0;
-    } else {
-        const int32_t* row = members.rows + (int64_t)c * members.cap;
-        const int places = members.places(), listed = n < places ? n : places;
-        for (int e = 0; e < listed; e += 4) {
-            const int4 o = *reinterpret_cast<const int4*>(row + e);
-            rank += (o.x < op) + (e + 1 < listed && o.y < op) + (e + 2 < listed && o.z < op) +
-                    (e + 3 < listed && o.w < op);
-        }
-        if (n > listed) {
-            const int chains = members.chains();
-            int j[4];
+            for (int e = 0; e < n; ++e) rank += row[e] < op ? 1 : 0;
+        } else {
+            const int32_t* row = members.rows + (int64_t)c * members.cap;
+            const int places = members.places(), listed = n < places ? n : places;
+            for (int e = 0; e < listed; e += 4) {
+                const int4 o = *reinterpret_cast<const int4*>(row + e);
+                rank += (o.x < op) + (e + 1 < listed && o.y < op) + (e + 2 < listed && o.z < op) +
+                        (e + 3 < listed && o.w < op);
+            }
+            if (n > listed) {
+                const int chains = members.chains();
+                int j[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) j[q] = q < chains ? row[places + q] : 0;   // heads past the count: unused
-            for (int k = places; k < n; k += chains) {
+                for (int q = 0; q < 4; ++q) j[q] = q < chains ? row[places + q] : 0;   // heads past the count: unused
+                for (int k = places; k < n; k += chains) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (q < chains && k + q < n) {
-                        rank += (orig_in ? orig_in[j[q]] : j[q]) < op ? 1 : 0;
-                        if (k + q + chains < n) j[q] = members.link[j[q]];
+                    for (int q = 0; q < 4; ++q) {
+                        if (q < chains && k + q < n) {
+                            rank += (orig_in ? orig_in[j[q]] : j[q]) < op ? 1 : 0;
+                            if (k + q + chains < n) j[q] = members.link[j[q]];
+                        }
                     }
                 }
             }
         }
-    }
-    const int d = s0 + rank;
-    put_sorted<T, DIM>(p, d, op, sims[sim_of(psim, p)], src, dst, slot);
+        const int d = s0 + rank;
+        put_sorted<T, DIM>(p, d, op, sims[sim_of(psim, p)], src, dst, slot);
     }
     if (SCAN) {
         if (threadIdx.x == 0) is_last = done == gridDim.x - 1;
@@ -1423,7 +1422,7 @@ template <typename T>
 struct PairConst {
     T L, invL, H, invH, epsH2, cA, cD, H2, m;
     T kGF;  // kG (-56/3): grad W = kGF t^5 (1 + 5 q) x_ij = kGF t^5 (6 - 5 t) x_ij
-    T hc;   // kH / kGF = -30 / H^2: the kernel Hessian is kGF (t^5 (6 - 5 t) I + hc t^4 x x^T)
+    T hc;   // -30 / H^2 (the Hessian's 560 C_d / H^(d+4) over kGF): it is kGF (t^5 (6 - 5 t) I + hc t^4 x x^T)
 };
 
 // Squared distance of a listed pair with the arithmetic of the neighbour predicate (per
@@ -1905,180 +1904,180 @@ void k_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
     const int r = (int)(t % LPP);
     int accepted = 0;  // listed pairs with r < H (lists with a skin)
     if (i < N) {
-    const int s = sim_of(psim, i);
-    FwdAcc<T, DIM> acc[NQ];
-    const PairConst<T> c = pair_const_of(sims, s);
-    auto load_self = [&](uint32_t i0, FwdSelf<T>& K0) {
-        const vec4_t<T> a = jd0[i0], b = jd1[i0];
-        K0.u[2] = K0.v[2] = T(0);
-        unpack_u<T, DIM>(a, K0.u);
-        K0.v[0] = b.x;
-        K0.v[1] = b.y;
-        if (DIM == 3) K0.v[2] = b.z;
-        K0.rho = (DIM == 3) ? a.w : b.z;
-        K0.p = b.w;
-        K0.G[0] = K0.G[1] = K0.G[2] = T(0);
-        if (RENORM) {
-            const vec4_t<T> g = jdG[i0];
-            K0.G[0] = g.x;
-            K0.G[1] = g.y;
-            K0.G[2] = g.z;
-        }
-    };
-    FwdSelf<T> K;
-    load_self(i, K);
-    int n = nbr_count[i];
-    n = n < width ? n : width;
-    const int32_t* row = nbr + (int64_t)i * width;
-    // the particle's own entry and the places past the count, at r2 = 0, are counted by the loop
-    if (r == 0 && n > 0) accepted = n - positions_visited<T, LPP>(n, width) - 1;
-    auto clear = [&]() {
+        const int s = sim_of(psim, i);
+        FwdAcc<T, DIM> acc[NQ];
+        const PairConst<T> c = pair_const_of(sims, s);
+        auto load_self = [&](uint32_t i0, FwdSelf<T>& K0) {
+            const vec4_t<T> a = jd0[i0], b = jd1[i0];
+            K0.u[2] = K0.v[2] = T(0);
+            unpack_u<T, DIM>(a, K0.u);
+            K0.v[0] = b.x;
+            K0.v[1] = b.y;
+            if (DIM == 3) K0.v[2] = b.z;
+            K0.rho = (DIM == 3) ? a.w : b.z;
+            K0.p = b.w;
+            K0.G[0] = K0.G[1] = K0.G[2] = T(0);
+            if (RENORM) {
+                const vec4_t<T> g = jdG[i0];
+                K0.G[0] = g.x;
+                K0.G[1] = g.y;
+                K0.G[2] = g.z;
+            }
+        };
+        FwdSelf<T> K;
+        load_self(i, K);
+        int n = nbr_count[i];
+        n = n < width ? n : width;
+        const int32_t* row = nbr + (int64_t)i * width;
+        // the particle's own entry and the places past the count, at r2 = 0, are counted by the loop
+        if (r == 0 && n > 0) accepted = n - positions_visited<T, LPP>(n, width) - 1;
+        auto clear = [&]() {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
-            acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
-        }
-        // W(0) = 1 of the particle itself
-        if (MODE == kModeRhs && r == 0 && n > 0) acc[0].rs = T(1);
-    };
-    using Nbr = FwdNbr<T, DIM, RENORM>;
-    auto gather = [&](int j, Nbr& nb) {
-        nb.j = j;
-        nb.a = ldo(jd0, (uint32_t)j);
-        nb.b = ldo(jd1, (uint32_t)j);
-        if (RENORM) nb.G = ldo(jdG, (uint32_t)j);
-    };
-    auto pairs = [&](auto image, auto walk) {
-        walk([&](int q, Nbr& nb) {
-            T d[3];
-            const T r2 = pair_vector<T, DIM, decltype(image)::value>(K.u, nb.a, c.L, c.invL, d);
-            accepted += r2 < c.H2 ? 1 : 0;
-            fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, K, nb, d, r2, (int)i, acc[q]);
-        });
-    };
-    auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
-    auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
-    T ax[3] = {0, 0, 0}, rdv = 0, rdd = 0, rs = 0, rdg = 0;
-    auto combine = [&]() -> T {
-        constexpr bool kSum = MODE == kModeRhs;
-        constexpr int NV = DIM + 2 + (kSum ? 1 : 0) + (RENORM ? 1 : 0);
-        T leaf[NV][NQ], out[NV];
+            for (int q = 0; q < NQ; ++q) {
+                acc[q].ax[0] = acc[q].ax[1] = acc[q].ax[2] = T(0);
+                acc[q].rdv = acc[q].rdd = acc[q].rs = acc[q].rdg = T(0);
+            }
+            // W(0) = 1 of the particle itself
+            if (MODE == kModeRhs && r == 0 && n > 0) acc[0].rs = T(1);
+        };
+        using Nbr = FwdNbr<T, DIM, RENORM>;
+        auto gather = [&](int j, Nbr& nb) {
+            nb.j = j;
+            nb.a = ldo(jd0, (uint32_t)j);
+            nb.b = ldo(jd1, (uint32_t)j);
+            if (RENORM) nb.G = ldo(jdG, (uint32_t)j);
+        };
+        auto pairs = [&](auto image, auto walk) {
+            walk([&](int q, Nbr& nb) {
+                T d[3];
+                const T r2 = pair_vector<T, DIM, decltype(image)::value>(K.u, nb.a, c.L, c.invL, d);
+                accepted += r2 < c.H2 ? 1 : 0;
+                fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c, K, nb, d, r2, (int)i, acc[q]);
+            });
+        };
+        auto groups = [&](auto&& pair) { sweep_list<(sizeof(T) == 8), LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
+        auto tail = [&](auto&& pair) { list_tail<LPP, Nbr>(row, width, n, r, (int)i, gather, pair); };
+        T ax[3] = {0, 0, 0}, rdv = 0, rdd = 0, rs = 0, rdg = 0;
+        auto combine = [&]() -> T {
+            constexpr bool kSum = MODE == kModeRhs;
+            constexpr int NV = DIM + 2 + (kSum ? 1 : 0) + (RENORM ? 1 : 0);
+            T leaf[NV][NQ], out[NV];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
+            for (int q = 0; q < NQ; ++q) {
 #pragma unroll
-            for (int k = 0; k < DIM; ++k) leaf[k][q] = acc[q].ax[k];
-            leaf[DIM][q] = acc[q].rdv;
-            leaf[DIM + 1][q] = acc[q].rdd;
-            if (kSum) leaf[DIM + 2][q] = acc[q].rs;
-            if (RENORM) leaf[NV - 1][q] = acc[q].rdg;
-        }
-        combine_leaves<LPP, NV>(leaf, out);
+                for (int k = 0; k < DIM; ++k) leaf[k][q] = acc[q].ax[k];
+                leaf[DIM][q] = acc[q].rdv;
+                leaf[DIM + 1][q] = acc[q].rdd;
+                if (kSum) leaf[DIM + 2][q] = acc[q].rs;
+                if (RENORM) leaf[NV - 1][q] = acc[q].rdg;
+            }
+            combine_leaves<LPP, NV>(leaf, out);
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) ax[k] = out[k];
-        rdv = out[DIM];
-        rdd = out[DIM + 1];
-        if (kSum) rs = out[DIM + 2];
-        if (RENORM) rdg = out[NV - 1];
-        T sum = T(0);
+            for (int k = 0; k < DIM; ++k) ax[k] = out[k];
+            rdv = out[DIM];
+            rdd = out[DIM + 1];
+            if (kSum) rs = out[DIM + 2];
+            if (RENORM) rdg = out[NV - 1];
+            T sum = T(0);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) sum += fabs(out[v]);
-        return sum;
-    };
-    clear();
-    if (wave_inside<T, DIM>(K.u, c.H, c.L)) pairs(std::false_type{}, groups);
-    else pairs(std::true_type{}, groups);
-    pairs(std::true_type{}, tail);
-    if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[s])) {
-        const uint32_t i2 = opaque(i);
-        const PairConst<T> c2 = pair_const(sims[opaque(s)]);
-        FwdSelf<T> K2;
-        load_self(i2, K2);
+            for (int v = 0; v < NV; ++v) sum += fabs(out[v]);
+            return sum;
+        };
         clear();
-        walk_again<LPP, Nbr>(nbr + (int64_t)i2 * width, width, nbr_count[i2], r, gather, [&](int q, Nbr& nb) {
-            T d[3];
-            const T r2 = r2_exact<T, DIM>(K2.u, nb.a, c2.L, c2.invL, d);
-            if (r2 < c2.H2) fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c2, K2, nb, d, r2, (int)i2, acc[q]);
-        });
-        combine();
-    }
-    if (r == 0) {
-    const SimConst<T>& S = sims[s];
-    if (DIM == 3) {
-        // the constants that the 3D pair terms leave out (V_j gW = scale g)
-        const T scale = S.kG * T(-56.0 / 3.0) * S.m;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) ax[k] = scale * ax[k];
-        rdv = scale * rdv;
-        rdd = scale * rdd;
-        rdg = scale * rdg;
-    }
-    const T invrho = fast_rcp(K.rho);
-    T a[3];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) a[k] = ax[k] * invrho;
-    // renormalised diffusion: -delta H c0 sum_j V_j (G_i + G_j) . grad_i W_ij, cD = 2 delta H c0
-    const T drho = RENORM ? K.rho * rdv + S.cD * rdd - T(0.5) * S.cD * rdg : K.rho * rdv + S.cD * rdd;
-    if (MODE == kModeStep) {
-        bool bad = !isfinite(drho);
-        const T dt = S.dt;
-        int cc[3] = {0, 0, 0};
-        T xn[3] = {0, 0, 0}, vn[3] = {0, 0, 0};
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            vn[k] = K.v[k] + dt * a[k];
-            xn[k] = cur.x[k][i] + dt * vn[k];
-            dst.v[k][i] = vn[k];
-            dst.x[k][i] = xn[k];
-            bad = bad || !isfinite(vn[k]) || !isfinite(xn[k]);
-            cc[k] = cell_coord(wrap_pos(isfinite(xn[k]) ? xn[k] : T(0), S.L, S.invL), S.cinv, S.nc);
+        if (wave_inside<T, DIM>(K.u, c.H, c.L)) pairs(std::false_type{}, groups);
+        else pairs(std::true_type{}, groups);
+        pairs(std::true_type{}, tail);
+        if (__builtin_expect(!isfinite(combine()), 0) && past_support(sims[s])) {
+            const uint32_t i2 = opaque(i);
+            const PairConst<T> c2 = pair_const(sims[opaque(s)]);
+            FwdSelf<T> K2;
+            load_self(i2, K2);
+            clear();
+            walk_again<LPP, Nbr>(nbr + (int64_t)i2 * width, width, nbr_count[i2], r, gather, [&](int q, Nbr& nb) {
+                T d[3];
+                const T r2 = r2_exact<T, DIM>(K2.u, nb.a, c2.L, c2.invL, d);
+                if (r2 < c2.H2) fwd_pair<T, DIM, MODE == kModeRhs, RENORM>(c2, K2, nb, d, r2, (int)i2, acc[q]);
+            });
+            combine();
         }
-        const T rhon = K.rho + dt * drho;
-        dst.rho[i] = rhon;
-        if (bad) atomicOr(&status[s], kFlagNonfinite);
-        if (next.cell_count) {
-            const int gcell = global_cell<T, DIM>(S, next.blk_rank, cc[0], cc[1], cc[2]);
-            next.cell_of[i] = gcell;
-            add_member(next.members, gcell, atomicAdd(&next.cell_count[gcell], 1), (int32_t)i, orig[i]);
-        }
-        if (ns.jd0) {
-            // packed records of the next step, as the sort would write them
-            T u[3] = {0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) u[k] = wrap_pos(isfinite(xn[k]) ? xn[k] : T(0), S.L, S.invL);
-            const T V = S.m * fast_rcp(rhon);
-            const T pn = tait(S, rhon);
-            const T pV = pn * V;
-            vec4_t<T> pa, pb;
+        if (r == 0) {
+            const SimConst<T>& S = sims[s];
             if (DIM == 3) {
-                pa.x = u[0]; pa.y = u[1]; pa.z = u[2]; pa.w = rhon;
-                pb.x = vn[0]; pb.y = vn[1]; pb.z = vn[2]; pb.w = pn;
+                // the constants that the 3D pair terms leave out (V_j gW = scale g)
+                const T scale = S.kG * T(-56.0 / 3.0) * S.m;
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) ax[k] = scale * ax[k];
+                rdv = scale * rdv;
+                rdd = scale * rdd;
+                rdg = scale * rdg;
+            }
+            const T invrho = fast_rcp(K.rho);
+            T a[3];
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) a[k] = ax[k] * invrho;
+            // renormalised diffusion: -delta H c0 sum_j V_j (G_i + G_j) . grad_i W_ij, cD = 2 delta H c0
+            const T drho = RENORM ? K.rho * rdv + S.cD * rdd - T(0.5) * S.cD * rdg : K.rho * rdv + S.cD * rdd;
+            if (MODE == kModeStep) {
+                bool bad = !isfinite(drho);
+                const T dt = S.dt;
+                int cc[3] = {0, 0, 0};
+                T xn[3] = {0, 0, 0}, vn[3] = {0, 0, 0};
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) {
+                    vn[k] = K.v[k] + dt * a[k];
+                    xn[k] = cur.x[k][i] + dt * vn[k];
+                    dst.v[k][i] = vn[k];
+                    dst.x[k][i] = xn[k];
+                    bad = bad || !isfinite(vn[k]) || !isfinite(xn[k]);
+                    cc[k] = cell_coord(wrap_pos(isfinite(xn[k]) ? xn[k] : T(0), S.L, S.invL), S.cinv, S.nc);
+                }
+                const T rhon = K.rho + dt * drho;
+                dst.rho[i] = rhon;
+                if (bad) atomicOr(&status[s], kFlagNonfinite);
+                if (next.cell_count) {
+                    const int gcell = global_cell<T, DIM>(S, next.blk_rank, cc[0], cc[1], cc[2]);
+                    next.cell_of[i] = gcell;
+                    add_member(next.members, gcell, atomicAdd(&next.cell_count[gcell], 1), (int32_t)i, orig[i]);
+                }
+                if (ns.jd0) {
+                    // packed records of the next step, as the sort would write them
+                    T u[3] = {0, 0, 0};
+#pragma unroll
+                    for (int k = 0; k < DIM; ++k) u[k] = wrap_pos(isfinite(xn[k]) ? xn[k] : T(0), S.L, S.invL);
+                    const T V = S.m * fast_rcp(rhon);
+                    const T pn = tait(S, rhon);
+                    const T pV = pn * V;
+                    vec4_t<T> pa, pb;
+                    if (DIM == 3) {
+                        pa.x = u[0]; pa.y = u[1]; pa.z = u[2]; pa.w = rhon;
+                        pb.x = vn[0]; pb.y = vn[1]; pb.z = vn[2]; pb.w = pn;
+                    } else {
+                        pa.x = u[0]; pa.y = u[1]; pa.z = V; pa.w = pV;
+                        pb.x = vn[0]; pb.y = vn[1]; pb.z = rhon; pb.w = pn;
+                    }
+                    ns.jd0[i] = pa;
+                    ns.jd1[i] = pb;
+                    ns.orig[i] = orig[i];
+                    // displacement since the lists were built (minimum image)
+                    const vec4_t<T> ref = ns.uref[i];
+                    const T rr[3] = {ref.x, ref.y, ref.z};
+                    T d2 = T(0);
+#pragma unroll
+                    for (int k = 0; k < DIM; ++k) {
+                        T d = u[k] - rr[k];
+                        d -= S.L * rint(d * S.invL);
+                        d2 += d * d;
+                    }
+                    if (!(d2 <= ref.w * ref.w)) atomicOr(&status[s], kFlagSkin);
+                }
             } else {
-                pa.x = u[0]; pa.y = u[1]; pa.z = V; pa.w = pV;
-                pb.x = vn[0]; pb.y = vn[1]; pb.z = rhon; pb.w = pn;
-            }
-            ns.jd0[i] = pa;
-            ns.jd1[i] = pb;
-            ns.orig[i] = orig[i];
-            // displacement since the lists were built (minimum image)
-            const vec4_t<T> ref = ns.uref[i];
-            const T rr[3] = {ref.x, ref.y, ref.z};
-            T d2 = T(0);
+                const int o = orig[i];
+                drho_out[o] = drho;
 #pragma unroll
-            for (int k = 0; k < DIM; ++k) {
-                T d = u[k] - rr[k];
-                d -= S.L * rint(d * S.invL);
-                d2 += d * d;
+                for (int k = 0; k < DIM; ++k) acc_out[(int64_t)k * N + o] = a[k];
+                if (rhosum_out) rhosum_out[o] = S.m * S.kW * rs;
             }
-            if (!(d2 <= ref.w * ref.w)) atomicOr(&status[s], kFlagSkin);
         }
-    } else {
-        const int o = orig[i];
-        drho_out[o] = drho;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) acc_out[(int64_t)k * N + o] = a[k];
-        if (rhosum_out) rhosum_out[o] = S.m * S.kW * rs;
-    }
-    }
     }
     if (pair_counter) {
         // wave total of the filtered pairs, one integer atomic per wavefront
@@ -2384,8 +2383,7 @@ __global__ __launch_bounds__(256) void k_unsort(int64_t N, StatePtrs<T, DIM> src
 
 // ---------------------------------------------------------------- adjoint
 
-// Gathers the output cotangents into sorted order, with vt = v'_bar + dt x'_bar, abar = dt vt,
-// rbar = dt rho'_bar: (abar, rbar rho) in 3D, (abar, rbar rho, rbar rho^2) in 2D.
+// A particle's adjoint record: (abar, rbar rho) in 3D, (abar, rbar rho, rbar rho^2) in 2D.
 template <typename T, int DIM>
 __device__ __forceinline__ vec4_t<T> adjoint_record(const T* ab, T rb, T rho)
 {
@@ -2398,6 +2396,8 @@ __device__ __forceinline__ vec4_t<T> adjoint_record(const T* ab, T rb, T rho)
     return a;
 }
 
+// Gathers the output cotangents into sorted order, with vt = v'_bar + dt x'_bar, abar = dt vt,
+// rbar = dt rho'_bar.
 template <typename T, int DIM>
 __global__ __launch_bounds__(256) void k_adj_prologue(int64_t N, const int32_t* __restrict__ orig,
                                                       StatePtrs<T, DIM> cot, StatePtrs<T, DIM> cur,
@@ -2454,8 +2454,6 @@ __global__ __launch_bounds__(256) void k_stage_cot(int64_t N, LinComb<T, DIM> L,
     jdA[d] = adjoint_record<T, DIM>(kv, kr, rho);
 }
 
-// Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
-// (cin_sorted, cout_sorted): contiguous accesses, where the caller's order scatters them.
 // What the adjoint sweep of step t prepares for the adjoint of step t - 1 when both states share
 // the particle order (a step within one list-reuse interval), or when the sort of state t has kept each
 // particle's place in the order before it (`before`): the prologue records of step t - 1 at the particle's
@@ -2591,10 +2589,14 @@ __device__ __forceinline__ void adj_pair(const PairConst<T>& c, const AdjSelf<T>
 }
 
 // Wavefronts per SIMD the adjoint sweep's registers are held to: in FP32 2D five (96 registers instead of
-// 113: the 512-simulation batch 399 us a launch against 463).  In 3D and with RENORM the same limit spills.
+// 113: the 512-simulation batch 399 us a launch against 463, although 7 registers spill with four lanes, 26 with
+// two and 4 with eight).  Not in 3D, which spills under it, nor with RENORM (2D 256^2, 64 steps and their adjoint: 8.6
+// ms with the limit, 7.2 without).
 template <typename T, int DIM, bool RENORM>
 constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 && !RENORM ? 5 : 1;
 
+// Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
+// (cin_sorted, cout_sorted): contiguous accesses, where the caller's order scatters them.
 template <typename T, int DIM, int LPP, bool RENORM>
 __global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM, RENORM>))
 void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
