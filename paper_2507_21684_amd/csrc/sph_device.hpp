@@ -51,13 +51,13 @@ struct SimConst {
     T m, rho0, inv_rho0, c0sq, dt;
     T kW;       // C_d / H^d
     T kG;       // C_d / H^(d+2)
+    T invW0;    // 1 / W(dx), dx = (m / rho0)^(1/dim) the initial spacing (particle shifting)
     T epsH2;    // eps H^2
     T cA;       // alpha H c0 rho0
     T cD;       // 2 delta H c0
     T Bt;       // rho0 c0^2 / 7
     T HL2;      // (H (1 + skin))^2: list radius squared (= H2 without a skin)
     T hmax;     // skin H / 2: the largest half skin of a particle (the cells are sized for it)
-    T invW0;    // 1 / W(dx), dx = (m / rho0)^(1/dim) the initial spacing (particle shifting)
     int64_t p0, n;      // packed particle range
     int32_t cell0;      // first global cell slot
     int32_t blk0;       // first global cell block
@@ -2589,16 +2589,17 @@ __device__ __forceinline__ void adj_pair(const PairConst<T>& c, const AdjSelf<T>
 }
 
 // Wavefronts per SIMD the adjoint sweep's registers are held to: in FP32 2D five (96 registers instead of
-// 113: the 512-simulation batch 399 us a launch against 463, although 7 registers spill with four lanes, 26 with
-// two and 4 with eight).  Not in 3D, which spills under it, nor with RENORM (2D 256^2, 64 steps and their adjoint: 8.6
-// ms with the limit, 7.2 without).
-template <typename T, int DIM, bool RENORM>
-constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 && !RENORM ? 5 : 1;
+// 113: the 512-simulation batch 399 us a launch against 463, although 7 registers spill with four lanes and 4
+// with eight), with two lanes four (118 registers: 588 us against 726 and more, where five left 19 to 26 spilt).
+// Not in 3D, which spills under it, nor with RENORM (2D 256^2, 64 steps and their adjoint: 8.6 ms with the limit,
+// 7.2 without).
+template <typename T, int DIM, int LPP, bool RENORM>
+constexpr int kAdjWaves = sizeof(T) == 4 && DIM == 2 && !RENORM ? (LPP == 2 ? 4 : 5) : 1;
 
 // Within one list-reuse interval consecutive adjoint sweeps hand the cotangents on in sorted order
 // (cin_sorted, cout_sorted): contiguous accesses, where the caller's order scatters them.
 template <typename T, int DIM, int LPP, bool RENORM>
-__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM, RENORM>))
+__global__ __launch_bounds__((kSweepThreads<T, DIM, LPP>), (kAdjWaves<T, DIM, LPP, RENORM>))
 void k_adj_sweep(int64_t N, int32_t width, const int32_t* __restrict__ nbr,
                                                    const int32_t* __restrict__ nbr_count,
                                                    const vec4_t<T>* __restrict__ jd0,
