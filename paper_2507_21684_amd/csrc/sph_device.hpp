@@ -838,7 +838,8 @@ constexpr int kCandTable = 2048;
 // instead of one reads the particle's position and count once per tile and leaves the chunks' tests
 // independent of each other: 18 vector and about as many scalar instructions per test of 64
 // candidates became 13 and 6.  Measured, one chunk at a time against tiles: 3D 64^3 with skins 267
-// and 195 us, 3D 40^3 exact 110 and 75 us, the 512-simulation 2D batch 285 and 250 us.
+// and 195 us, 3D 40^3 exact 110 and 75 us, the 512-simulation 2D batch 285 and 229 us (252 with the rows
+// transposed and filled up for the sweeps).
 // With GROUP (2D) a wavefront serves a group of 2 x 2 cells (cell slots c, c + 1, c + B,
 // c + B + 1 of a block, B = 4) over their 6 x 6 (or 4 x 4) union stencil, in the same lexicographic order:
 // a particle's own stencil cells are a sub-grid of it in the same relative order, and the extra
@@ -1872,10 +1873,12 @@ struct NextCells {
 // LPP lanes share a particle and walk its row with sweep_list; wavefronts whose particles all lie more
 // than the support inside the box run a copy of the pair loop without the periodic image (the same
 // roundings), 6 of 45 (2D) instructions per pair less.
-// Bound: the gathers.  The texture path returns 64 bytes a clock, so a wavefront's 16-byte gather takes 16
-// clocks at the least (17.9 where quads of lanes read consecutive records, as list positions mostly
-// do); its data return is busy 93 to 100 % of a large launch, and a quarter fewer vector instructions
-// changed little by themselves.  Small launches are bound by a wavefront's own chain.  Measured, before
+// Bound: the vector memory path, but no one rate of it.  Of a large launch (512-simulation batch, 3D 64^3)
+// the gathers take 56 to 66 % at 17.9 clocks each (64 bytes a clock are 16 for a wavefront's 16-byte gather;
+// 17.9 measured where quads of lanes read consecutive records, as list positions mostly do), the vector
+// L1's lines 73 to 77 % at one a clock, and vector issue 54 to 56 %; the data return is busy 89 to 94 %, two
+// fifths of that waiting for the L1.  What is left is latency at four to six wavefronts per SIMD: more
+// gathers in flight helped, a quarter fewer vector instructions changed little by themselves.  Small launches are bound by a wavefront's own chain.  Measured, before
 // (a load per list entry, a test of every position against the count and of every pair against the
 // support) and now: 2D 32^2 FP64 13.5 and 8.9 us, 2D 101^2 8.2 and 7.1, 2D 256^2 15.0 and 13.7, 3D 47^3
 // 86.5 and 83.0, 3D 64^3 222 and 213, 3D 20^3 FP64 27.3 and 20.7, 512-simulation batch 335 and 328.
@@ -2511,7 +2514,8 @@ constexpr bool kGatherFirst<AdjNbr<T, DIM, true>> = false;
 // (c = -delta H c0) adds, with the gradients held fixed and s = G_k + G_j: xbar += Phi c (Q_k - Q_j) Jg s,
 // Gbar += Phi c (Q_k - Q_j) gF e, rbar += Phi c Q_j gF s.e / rho_k.
 //
-// Bound: the gathers, as in k_sweep, three records per neighbour.  Dropping the second adjoint record
+// Bound: as in k_sweep (reads 53 to 71 %, L1 lines 72 to 88 %, vector issue 63 to 70 % of a large launch), three
+// records per neighbour.  Dropping the second adjoint record
 // (u and the density are in jd0 and jd1), the common factor Phi (62 vector instructions per pair, 80 before) and
 // the walk of the rows: 2D 101^2 9.4 and 9.1 us, 2D 256^2 18.4 and 17.2, 3D 47^3 140 and 125, 3D 64^3 318 and
 // 318, 3D 20^3 FP64 25.9 and 22.1, 512-simulation batch 439 and 407; with renormalisation, the second pass
