@@ -47,8 +47,11 @@ sph_status fail(sph_status code, const std::string& msg)
 
 constexpr double kCellMargin = 1.0 + 1.0 / 1024.0;  // cell side exceeds H/sub by more than rounding
 constexpr size_t kMaxMembers = 64;                   // places per cell for its members, at most
-constexpr int64_t kMemberCells = 131072;              // plans of at most this many cells collect them in rows of
-                                                      // places; larger ones scatter them after the scan
+// Plans of at most this many cells collect them in rows of places; larger ones scatter them after the scan.  The
+// rows save the sort a launch and cost the sweep before it scattered stores, which come to the same in a
+// large plan.  A step's sort and sweep with rows and scattered, us: 2D 400^2 (40 000 cells) 42.7 and 44.3, 700^2
+// (123 904) 99.8 and 100.4, 820^2 133.8 and 134.0, 1400^2 366 and 364, 3D 120^3 1233 and 1232.
+constexpr int64_t kMemberCells = 131072;
 constexpr int64_t kGroupedBuildCells = 65536;         // 2D plans with this many cell slots build by 2 x 2 groups
 
 // 3D builds with fewer wavefronts than kBuildWaves (eight on every SIMD) let up to four share a cell's

@@ -304,9 +304,7 @@ __global__ void k_fill(I* __restrict__ p, int64_t n, I val)
 // (Four, because a chain is a load after the other: a sort of 10 000 particles with 1000 of them in one cell
 // took 153 us with one chain, 115 with four.)  cap is a multiple of 4; or 1, a single chain;
 // or 0 where arrivals keep their place in the cell in `link` and are scattered into contiguous `rows` once the
-// cell starts are known (k_scatter): for the sort by destination, and in plans of many cells (the
-// scattered stores of a padded row cost the 512-simulation batch, 1.96 million particles, more than that
-// launch does).
+// cell starts are known (k_scatter): for the sort by destination, and in plans of many cells.
 struct CellMembers {
     int32_t* rows;
     int32_t* link;
@@ -1874,9 +1872,9 @@ struct NextCells {
 // than the support inside the box run a copy of the pair loop without the periodic image (the same
 // roundings), 6 of 45 (2D) instructions per pair less.
 // Bound: the vector memory path, but no one rate of it.  Of a large launch (512-simulation batch, 3D 64^3)
-// the gathers take 56 to 66 % at 17.9 clocks each (64 bytes a clock are 16 for a wavefront's 16-byte gather;
+// the gathers take 56 to 70 % at 17.9 clocks each (64 bytes a clock are 16 for a wavefront's 16-byte gather;
 // 17.9 measured where quads of lanes read consecutive records, as list positions mostly do), the vector
-// L1's lines 73 to 77 % at one a clock, and vector issue 54 to 56 %; the data return is busy 89 to 94 %, two
+// L1's lines 73 to 77 % at one a clock, and vector issue 54 to 57 %; the data return is busy 89 to 94 %, two
 // fifths of that waiting for the L1.  What is left is latency at four to six wavefronts per SIMD: more
 // gathers in flight helped, a quarter fewer vector instructions changed little by themselves.  Small launches are bound by a wavefront's own chain.  Measured, before
 // (a load per list entry, a test of every position against the count and of every pair against the
